@@ -200,7 +200,12 @@ size_t rocketkv_workspace_bytes(int32_t op, const rocketkv_cache_t* cache, int32
       return attend_plan_for(v, cache->pages_cap, false).total_bytes;
     case ROCKETKV_OP_ATTEND:
       if (a < 0) { fail(ROCKETKV_INVALID_ARG, "rocketkv_workspace_bytes: pages_row_len must be >= 0"); return 0; }
-      return attend_plan_for(v, a > 0 ? a : cache->pages_cap, a > 0).total_bytes;
+      {
+        // a row as long as the table may also be passed without a list (every page)
+        const size_t list = a > 0 ? attend_plan_for(v, a, true).total_bytes : 0;
+        const size_t dense = a >= cache->pages_cap || a == 0 ? attend_plan_for(v, cache->pages_cap, false).total_bytes : 0;
+        return list > dense ? list : dense;
+      }
     case ROCKETKV_OP_SNAPKV:
       if (a < 1 || b <= a) { fail(ROCKETKV_INVALID_ARG, "rocketkv_workspace_bytes: need 1 <= window < keep_budget"); return 0; }
       return plan_snapkv(v, a, b).total_bytes;

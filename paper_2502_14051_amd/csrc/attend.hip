@@ -23,6 +23,19 @@ void attend_mfma_kernel(CacheView c, AttendArgs a) {
   attend_block<WAVES, NP, STREAM_K, CB>(c, a, unit, split, cs, n, list, smem, &s_last, none);
 }
 
+// The Full-KV baseline: the identity list, divided by the lengths the sequences have (dense_share).
+template <int WAVES>
+__global__ __launch_bounds__(WAVES* kWave) __attribute__((amdgpu_waves_per_eu(2)))
+void dense_mfma_kernel(CacheView c, AttendArgs a, DenseGrid grid) {
+  extern __shared__ float smem[];
+  __shared__ int s_last;
+  const DenseShare s = dense_share(c, grid, 2 * WAVES, blockIdx.x);
+  if (s.b < 0) return;
+  dense_args(a, c, grid, s, blockIdx.y, WAVES);
+  const TailPatch none = {-1, 0, nullptr, nullptr};
+  attend_block<WAVES, 1, false, 8>(c, a, s.b * c.n_kv_heads + blockIdx.y, s.split, 0, s.tokens, nullptr, smem, &s_last, none);
+}
+
 __global__ void zero_u32_kernel(uint32_t* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
@@ -70,6 +83,23 @@ AttendPlan plan_attend(const CacheView& c, int row_len, bool gather) {
   // softmax step of the unit), 22.1 against 22.3 us without and 24.6 against 23.8 us with the token
   // append at the benchmark shape, and is not used.
   p.n_csplit = 1;
+  p.dense_aim = p.dense_limit = 0;
+  if (!gather && (int64_t)units * ((row_len + 2 * waves - 1) / (2 * waves)) > kComputeUnits) {
+    // The workgroups divide the pages that are there between them (dense_share), so the launch only
+    // has to hold as many as that division can make: the aim, or two per sequence.  Below this size
+    // every workgroup has the smallest share whatever the lengths are and all of them run at once:
+    // nothing to balance, and the division would only cost its time (10.2 against 10.8 us for four
+    // sequences of 1000 tokens, 10.4 against 11.1 us for one of 2048 over token-major V).
+    const int64_t shares = (int64_t)c.batch * row_len / kDensePages;
+    const int64_t most = (int64_t)c.batch * (row_len / (2 * waves) + 2);  // a pair per wavefront is the least
+    const int slots = kComputeUnits * 8 / waves;  // the chip holds two wavefronts per SIMD of these kernels (registers)
+    p.dense_aim = slots / c.n_kv_heads > 1 ? slots / c.n_kv_heads : 1;
+    int64_t limit = p.dense_aim;
+    if (shares >= kDenseRounds * limit) limit = shares < kMaxWorkgroups / c.n_kv_heads ? shares : kMaxWorkgroups / c.n_kv_heads;
+    if (limit > most) limit = most;
+    if (limit < 2 * c.batch) limit = 2 * c.batch;
+    p.dense_limit = (int)limit;
+  }
   if (gather && !c.v_token_major && waves == 8 && (int64_t)units * n_wg * 2 <= kComputeUnits) p.n_csplit = 2;
   int chunk = (row_len + n_wg - 1) / n_wg;
   int per_wave = (chunk + waves - 1) / waves;
@@ -83,7 +113,8 @@ AttendPlan plan_attend(const CacheView& c, int row_len, bool gather) {
   p.counter_off = off;  // always first: the part rocketkv_workspace_init clears
   off += ROCKETKV_WS_HEADER_BYTES;
   p.partial_off = off;
-  off += ((size_t)units * p.n_csplit * p.n_split * c.group * kPartialStride * sizeof(float) + 255) / 256 * 256;
+  const size_t parts = p.dense_limit ? (size_t)p.dense_limit * c.n_kv_heads : (size_t)units * p.n_csplit * p.n_split;
+  off += (parts * c.group * kPartialStride * sizeof(float) + 255) / 256 * 256;
   p.total_bytes = off;
   return p;
 }
@@ -121,6 +152,15 @@ hipError_t launch_attend(const CacheView& c, const bf16_t* q, const int32_t* pag
     return hipGetLastError();
   }
   const size_t smem = (size_t)plan.waves * c.group * (kHeadDim + 2) * sizeof(float);
+  if (plan.dense_limit) {
+    const DenseGrid dg = {plan.dense_aim, plan.dense_limit};
+    const dim3 dgrid(plan.dense_limit, c.n_kv_heads);
+    if (plan.waves == 8)
+      hipLaunchKernelGGL(dense_mfma_kernel<8>, dgrid, dim3(8 * kWave), smem, st, c, a, dg);
+    else
+      hipLaunchKernelGGL(dense_mfma_kernel<4>, dgrid, dim3(4 * kWave), smem, st, c, a, dg);
+    return hipGetLastError();
+  }
   const dim3 grid(plan.n_split, units);
   const bool stream_k = pages != nullptr && wants_stream_k(c, row_len);  // a large gather, not the dense read
 #define RKV_LAUNCH_ATTEND(W, S) \

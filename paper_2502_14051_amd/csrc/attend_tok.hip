@@ -18,6 +18,24 @@ void attend_tokens_kernel(CacheView c, AttendArgs a, TokenRun t) {
   attend_tokens_block<WAVES, INDEXED>(c, a, t, unit, split, n, list, smem, &s_last, none);
 }
 
+// The Full-KV baseline over token-major caches: the tokens that are there, divided in 16-slot entries
+// as dense_share does it.
+template <int WAVES>
+__global__ __launch_bounds__(WAVES* kWave) __attribute__((amdgpu_waves_per_eu(2)))
+void dense_tokens_kernel(CacheView c, AttendArgs a, TokenRun t, DenseGrid grid) {
+  extern __shared__ float smem[];
+  __shared__ int s_last;
+  const DenseShare s = dense_share(c, grid, 2 * WAVES, blockIdx.x);
+  if (s.b < 0) return;
+  dense_args(a, c, grid, s, blockIdx.y, WAVES);
+  t.tokens = a.row_len * kAttnPage;
+  a.chunk *= kAttnPage;
+  a.per_wave *= kAttnPage;
+  const TokenPatch none = {-1, nullptr, nullptr};
+  attend_tokens_block<WAVES, false>(c, a, t, s.b * c.n_kv_heads + blockIdx.y, s.split, s.tokens, nullptr, smem, &s_last,
+                                    none);
+}
+
 hipError_t launch_attend_tokens(const CacheView& c, const bf16_t* q, const int32_t* pages, int row_len,
                                 bf16_t* out, float* out_lse, void* ws, const AttendPlan& plan,
                                 const LogicalView* lv, hipStream_t st) {
@@ -42,6 +60,15 @@ hipError_t launch_attend_tokens(const CacheView& c, const bf16_t* q, const int32
   t.n_logical = lv ? lv->n_indexed : nullptr;
   t.logical_pages_cap = lv ? lv->pages_cap : 0;
   const size_t smem = (size_t)plan.waves * c.group * (kHeadDim + 2) * sizeof(float);
+  if (plan.dense_limit) {
+    const DenseGrid dg = {plan.dense_aim, plan.dense_limit};
+    const dim3 dgrid(plan.dense_limit, c.n_kv_heads);
+    if (plan.waves == 8)
+      hipLaunchKernelGGL(dense_tokens_kernel<8>, dgrid, dim3(8 * kWave), smem, st, c, a, t, dg);
+    else
+      hipLaunchKernelGGL(dense_tokens_kernel<4>, dgrid, dim3(4 * kWave), smem, st, c, a, t, dg);
+    return hipGetLastError();
+  }
   const dim3 grid(plan.n_split, units);
   if (plan.waves == 8) {
     if (lv)

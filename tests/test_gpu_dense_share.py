@@ -1,0 +1,47 @@
+"""The Full-KV baseline divides the pages the sequences hold between its workgroups (dense_share in
+attend_core.h): unequal, empty and over-long lengths, fewer and more units than workgroups fit the
+chip at once, more than 64 sequences, against the fp64 oracle.
+
+Bar: 1e-2 absolute / relative (bf16 operands and weights, fp32 sums, bf16 results)."""
+import numpy as np
+import pytest
+
+from paper_2502_14051_amd import workloads as wl
+from helpers import assert_attention_close, to_device_cache
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hq,hkv,lens,ps,layout", [
+    (4, 1, (1,), 16, 0),                                   # one page: one share
+    (4, 1, (255, 256, 257), 16, 0),                        # around the smallest share of eight wavefronts
+    (32, 8, (0, 5000, 17, 1), 16, 0),                      # an empty sequence among unequal ones
+    (15, 5, (3001, 150, 1600), 16, 0),                     # heads that do not divide the workgroups
+    (16, 16, tuple(5 + 37 * i for i in range(20)), 16, 0),  # more units than compute units
+    (2, 2, tuple((97 * i) % 700 for i in range(70)), 16, 0),  # a second block of 64 sequences
+    (16, 1, (2000, 31), 16, 0),                            # the largest group: four wavefronts
+    (8, 2, (40000, 700), 16, 0),
+    (8, 2, (4097, 0, 333), 3, 1),                          # token-major, pages that do not divide 16
+    (32, 8, (2500, 16, 1111), 16, 1),
+    (6, 6, tuple(3 + 11 * i for i in range(66)), 1, 1),
+])
+def test_unequal_lengths(oracle, hq, hkv, lens, ps, layout):
+    import torch
+    from paper_2502_14051_amd import rocketkv as rk
+    print("[case] dense share", hq, hkv, lens, ps, layout, flush=True)
+    dev = torch.device("cuda:0")
+    w = wl.scaled(wl.CONFIGS["tiny"], batch=len(lens), n_q_heads=hq, n_kv_heads=hkv, context=max(lens), page_size=ps,
+                  n_heavy=0)
+    d = wl.generate(w)
+    d["seq_lens"] = np.asarray(lens, dtype=np.int32)
+    cache, q = to_device_cache(rk, torch, d, hq, ps, dev, shuffle_rng=np.random.default_rng(5), extra_pages=3,
+                               v_layout=layout)
+    out = torch.full((len(lens), hq, 128), 7.0, dtype=torch.bfloat16, device=dev)
+    lse = torch.full((len(lens), hq), 7.0, dtype=torch.float32, device=dev)
+    ws = rk.alloc_workspace(rk.OP_DENSE_DECODE, cache)
+    want_y, want_lse = oracle.dense_decode(d["q"], d["K"], d["V"], d["seq_lens"])
+    for _ in range(2):  # the second call finds the counters as the first one left them
+        rk.dense_decode(cache, q, out, lse, ws)
+        torch.cuda.synchronize()
+        assert_attention_close(wl.to_bits(out), want_y, "dense y")
+        np.testing.assert_allclose(lse.cpu().numpy(), want_lse, rtol=1e-3, atol=1e-3)
