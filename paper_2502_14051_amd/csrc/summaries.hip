@@ -13,19 +13,27 @@ namespace rkv {
 constexpr int kSumPages = 64;   // pages per workgroup
 constexpr int kSumPad = 66;     // LDS row pitch in bf16 (33 dwords: conflict-free column writes)
 
+// PAGES per workgroup; ROWS: rows of a page in flight per 16-lane group.  Many pages: 64 with four rows,
+// whose other wavefronts cover the wait.  Where those would leave compute units without a workgroup, 16
+// with every row of a 16-token page: one round trip instead of four, on four times the workgroups
+// (pages of 16 tokens, 8 / 32 units of 256 pages: 9.9 / 15.3 -> 4.2 / 8.1 us).  From one workgroup per
+// compute unit on the 32-byte runs that 16 pages make of a summary row cost more than that gains (8
+// units of 2048 pages: 18.6 against 20.9 us, 32: 52 against 69).
+template <int PAGES, int ROWS>
 __global__ __launch_bounds__(256) void page_summaries_kernel(CacheView c, bf16_t* __restrict__ kmax,
                                                              bf16_t* __restrict__ kmin,
                                                              int first_page, int last_page) {
-  __shared__ bf16_t tmax[kHeadDim * kSumPad];
-  __shared__ bf16_t tmin[kHeadDim * kSumPad];
+  constexpr int kPad = PAGES + 2;  // LDS row pitch in bf16: an odd number of dwords, conflict-free column writes
+  __shared__ bf16_t tmax[kHeadDim * kPad];
+  __shared__ bf16_t tmin[kHeadDim * kPad];
   const int unit = blockIdx.y;
   const int b = unit / c.n_kv_heads, g = unit % c.n_kv_heads;
   const int n = c.seq_lens[b];
   const int ps = c.page_size;
   int P = (n + ps - 1) / ps;
   if (P > c.pages_cap) P = c.pages_cap;
-  const int p0 = first_page + blockIdx.x * kSumPages;
-  const int pend = min(min(p0 + kSumPages, last_page), P);
+  const int p0 = first_page + blockIdx.x * PAGES;
+  const int pend = min(min(p0 + PAGES, last_page), P);
   if (p0 >= pend) return;
   const int npg = pend - p0;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -41,13 +49,13 @@ __global__ __launch_bounds__(256) void page_summaries_kernel(CacheView c, bf16_t
     for (int i = 0; i < 8; ++i) { mx[i] = -INFINITY; mn[i] = INFINITY; }
     if (pp >= 0) {
       const bf16_t* tile = c.k_pool + pp * c.stride_page + (int64_t)g * c.stride_head + cl * 8;
-      for (int t0 = 0; t0 < ntok; t0 += 4) {
-        uint4 v[4];
+      for (int t0 = 0; t0 < ntok; t0 += ROWS) {
+        uint4 v[ROWS];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < ROWS; ++u)
           v[u] = ld16<true>(tile + min(t0 + u, ntok - 1) * kHeadDim);  // read once: streamed; a repeat is harmless
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < ROWS; ++u) {
           const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -62,18 +70,18 @@ __global__ __launch_bounds__(256) void page_summaries_kernel(CacheView c, bf16_t
     for (int i = 0; i < 8; ++i) {
       // an absent page contributes neutral zeros
       const float a = pp >= 0 ? mx[i] : 0.f, z = pp >= 0 ? mn[i] : 0.f;
-      tmax[(cl * 8 + i) * kSumPad + pl] = (bf16_t)(__float_as_uint(a) >> 16);
-      tmin[(cl * 8 + i) * kSumPad + pl] = (bf16_t)(__float_as_uint(z) >> 16);
+      tmax[(cl * 8 + i) * kPad + pl] = (bf16_t)(__float_as_uint(a) >> 16);
+      tmin[(cl * 8 + i) * kPad + pl] = (bf16_t)(__float_as_uint(z) >> 16);
     }
   }
   __syncthreads();
   const int64_t row0 = (int64_t)unit * kHeadDim;
-  for (int idx = threadIdx.x; idx < kHeadDim * kSumPages; idx += 256) {
-    const int ch = idx / kSumPages, pl = idx % kSumPages;
+  for (int idx = threadIdx.x; idx < kHeadDim * PAGES; idx += 256) {
+    const int ch = idx / PAGES, pl = idx % PAGES;
     if (pl < npg) {
       const int64_t o = (row0 + ch) * c.pages_cap + p0 + pl;
-      kmax[o] = tmax[ch * kSumPad + pl];
-      kmin[o] = tmin[ch * kSumPad + pl];
+      kmax[o] = tmax[ch * kPad + pl];
+      kmin[o] = tmin[ch * kPad + pl];
     }
   }
 }
@@ -83,8 +91,17 @@ hipError_t launch_page_summaries(const CacheView& c, bf16_t* kmax, bf16_t* kmin,
   int last = (n_pages < 0) ? c.pages_cap : first_page + n_pages;
   if (last > c.pages_cap) last = c.pages_cap;
   if (first_page >= last) return hipSuccess;
-  dim3 grid((last - first_page + kSumPages - 1) / kSumPages, c.batch * c.n_kv_heads);
-  hipLaunchKernelGGL(page_summaries_kernel, grid, dim3(256), 0, st, c, kmax, kmin, first_page, last);
+  const int units = c.batch * c.n_kv_heads;
+  const int wide = (last - first_page + kSumPages - 1) / kSumPages;
+  if ((int64_t)wide * units >= 256) {
+    hipLaunchKernelGGL((page_summaries_kernel<kSumPages, 4>), dim3(wide, units), dim3(256), 0, st, c, kmax, kmin, first_page, last);
+  } else {
+    const int narrow = (last - first_page + 15) / 16;
+    if (c.page_size <= 4)  // rows past the end of a page are read again rather than skipped
+      hipLaunchKernelGGL((page_summaries_kernel<16, 4>), dim3(narrow, units), dim3(256), 0, st, c, kmax, kmin, first_page, last);
+    else
+      hipLaunchKernelGGL((page_summaries_kernel<16, 16>), dim3(narrow, units), dim3(256), 0, st, c, kmax, kmin, first_page, last);
+  }
   return hipGetLastError();
 }
 
