@@ -4,8 +4,9 @@
 //           whole prompt, split along the key axis, then merged;
 //   pass 2  probabilities recomputed from the statistics and summed over heads and window rows into
 //           one vote per prefix token;
-//   pool    stride-1 max-pool of the votes (odd kernel, clipped at the ends);
-//   select  exact top-(N-W) of the pooled votes by radix select, ties to the lower position, emitted
+//   pool    stride-1 max-pool of the votes (odd kernel, clipped at the ends), written as votes and as
+//           runs of equal votes;
+//   select  exact top-(N-W) of the pooled votes from the runs, ties to the lower position, emitted
 //           ascending, followed by the W window positions;
 //   gather  K rows and V columns of the kept tokens copied into the destination cache.
 // The two score passes are the one dense contraction of the method (G*W query rows against every
@@ -31,6 +32,9 @@ union FragS {
   bf16x8 v;
 };
 
+constexpr int kSelBins = 4096;    // histogram of the pooled votes
+constexpr int kCountStride = 64;  // uint32 between the run counters of two units
+
 struct SnapArgs {
   const bf16_t* qobs;
   int W, NC, CG, n_chunks, chunk_pages, keep, s_cap, pool_r;
@@ -42,8 +46,10 @@ struct SnapArgs {
   int32_t* kept_user; // optional copy for the caller, rows of kept_stride entries
   int kept_stride;
   int32_t* n_out;     // [batch]: number of tokens kept per sequence
-  uint32_t* sel_hist; // split select: [units][4][256] digit counts, then [units][sel_split][2] slice counts
-  int sel_split;
+  uint2* runs;        // [units][s_cap]: the pooled votes as runs of equal ones
+  uint32_t* n_runs;   // [units], kCountStride apart
+  uint32_t* hist;     // [units][kSelBins]: pooled votes per bin
+  int sel_split;      // workgroups a unit's row is divided between in the select
 };
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -344,6 +350,9 @@ __global__ __launch_bounds__(kStatsT) void snap_stats_kernel(CacheView c, SnapAr
   const int b = unit / c.n_kv_heads;
   const int S = c.seq_lens[b];
   if (S <= a.keep || S > c.pages_cap * kAttnPage) return;
+  // the pool, two launches on, counts into these
+  if (tid == 0) a.n_runs[unit * kCountStride] = 0;
+  for (int i = tid; i < kSelBins; i += kStatsT) a.hist[(int64_t)unit * kSelBins + i] = 0;
   const int chunks = ((S + kAttnPage - 1) / kAttnPage + a.chunk_pages - 1) / a.chunk_pages;
   int ncp = 64;
   while (ncp < a.NC) ncp <<= 1;  // NC <= 256 (host)
@@ -379,13 +388,45 @@ __global__ __launch_bounds__(kStatsT) void snap_stats_kernel(CacheView c, SnapAr
   }
 }
 
-// stride-1 max-pool over the prefix votes, window [j-r, j+r] clipped to [0, L).  Window maxima by
-// doubling in LDS: M_1 = the votes, M_2w[i] = max(M_w[i], M_w[i+w]) up to the largest power of two
-// p <= 2r+1, then two overlapping windows of p cover the 2r+1 (a maximum is exact, so the order of
-// taking it does not matter): 3 log2(p) + 2 LDS accesses per vote instead of 2r+1.
-constexpr int kPoolTile = 1024;
-__global__ __launch_bounds__(256) void snap_pool_kernel(CacheView c, SnapArgs a) {
-  extern __shared__ float tile[];  // two arrays of kPoolTile + 2r
+__device__ __forceinline__ uint32_t order_key(float f) {
+  const uint32_t u = __float_as_uint(f);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// Stride-1 max-pool over the prefix votes, window [j-r, j+r] clipped to [0, L), and the list of runs
+// the select works from.  A workgroup pools kPoolTile positions, a thread eight neighbours: their
+// windows share [j0+7-r, j0+r], which is 2q+1 whole groups of eight (their maxima stand in LDS) and a
+// few elements at either end; what the eight windows do not share is seven elements on each side,
+// walked once.  At kernel 63 that is 21 LDS reads for eight votes (window maxima by doubling take 17
+// for each).  A maximum is exact, so the order of taking it does not matter.
+//
+// Pooling repeats every local maximum up to 2r+1 times, so the pooled row is written once more as runs
+// of equal votes, cut at multiples of eight: (ordered bits of the vote, group * 16 + length), in no
+// particular order, and counted into the unit's histogram of kSelBins bins, 64 to the octave (votes are
+// small probabilities under a few heavy tokens: equal-width bins would put nearly all into the lowest).
+// The select starts from those: about a sixth of the votes, and its first counting pass done.  The
+// counters of different units sit in lines of their own (adds to one line queue up: 128 units sharing
+// four lines took 27 us here and 8 units of 131072 votes sharing one 16.5; 17.8 and 10.2 apart).
+constexpr uint32_t kBinBase = (127u + 8u - 64u) << 6;  // bins cover 2^-56 .. 2^8; the first and the last take the rest
+
+__device__ __forceinline__ uint32_t vote_bin(uint32_t key) {  // monotone in the ordered bits
+  if (!(key & 0x80000000u)) return 0u;
+  const int x = (int)((key & 0x7fffffffu) >> 17) - (int)kBinBase;
+  return (uint32_t)min(max(x, 0), kSelBins - 1);
+}
+// the keys of a bin: [lo, lo + span]
+__device__ __forceinline__ void bin_range(uint32_t bin, uint32_t& lo, uint32_t& span) {
+  lo = bin == 0u ? 0u : (0x80000000u | ((bin + kBinBase) << 17));
+  const uint32_t last = bin == (uint32_t)kSelBins - 1u ? 0xffffffffu : (0x80000000u | ((bin + 1u + kBinBase) << 17)) - 1u;
+  span = last - lo;
+}
+
+constexpr int kPoolT = 256;
+constexpr int kPoolTile = kPoolT * 8;
+__global__ __launch_bounds__(kPoolT) void snap_pool_kernel(CacheView c, SnapArgs a) {
+  extern __shared__ float smem[];  // raw[], one float of padding per eight, then the groups' maxima
+  __shared__ uint32_t s_wave[kPoolT / kWave], s_base;
+  __shared__ uint32_t hist[kSelBins];
   const int unit = blockIdx.y;
   const int b = unit / c.n_kv_heads;
   const int S = c.seq_lens[b];
@@ -393,51 +434,262 @@ __global__ __launch_bounds__(256) void snap_pool_kernel(CacheView c, SnapArgs a)
   const int L = S - a.W, r = a.pool_r;
   const int j0 = blockIdx.x * kPoolTile;
   if (j0 >= L) return;
-  const int n = kPoolTile + 2 * r;
-  float* cur = tile;
-  float* nxt = tile + n;
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int HG = (r + 7) / 8;           // halo in groups of eight
+  const int groups = kPoolT + 2 * HG;   // groups of the tile with its halo
+  float* raw = smem;                    // group x, element i at x * 9 + i: no bank conflicts
+  float* gmax = smem + groups * 9;
   const float* v = a.votes + (int64_t)unit * a.s_cap;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const int j = j0 - r + i;
-    cur[i] = (j >= 0 && j < L) ? v[j] : -INFINITY;
+  for (int i = tid; i < kSelBins; i += kPoolT) hist[i] = 0;
+  for (int x = tid; x < groups; x += kPoolT) {
+    const int j = j0 + (x - HG) * 8;
+    float e[8], m = -INFINITY;
+    if (j >= 0 && j < L) {  // rows hold a multiple of eight floats: a group that begins below L is in bounds
+      const float4 lo = *reinterpret_cast<const float4*>(v + j), hi = *reinterpret_cast<const float4*>(v + j + 4);
+      e[0] = lo.x; e[1] = lo.y; e[2] = lo.z; e[3] = lo.w;
+      e[4] = hi.x; e[5] = hi.y; e[6] = hi.z; e[7] = hi.w;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (j < 0 || j + i >= L) e[i] = -INFINITY;
+      m = fmaxf(m, e[i]);
+      raw[x * 9 + i] = e[i];
+    }
+    gmax[x] = m;
   }
   __syncthreads();
-  int p = 1;
-  while (2 * p <= 2 * r + 1) {
-    for (int i = threadIdx.x; i < n; i += 256) nxt[i] = fmaxf(cur[i], i + p < n ? cur[i + p] : -INFINITY);
-    __syncthreads();
-    float* t = cur;
-    cur = nxt;
-    nxt = t;
-    p *= 2;
+  const int t = tid + HG;  // this thread's group
+  const auto at = [&](int x) { return raw[x + (x >> 3)]; };  // element x of the tile, the halo's first is 0
+  float o[8];
+  if (r >= 7) {
+    const int q = (r - 7) / 8, e = r - 8 * q - 7;  // 2q+1 whole groups, e elements beyond them at either end
+    float core = gmax[t];
+    for (int x = 1; x <= q; ++x) core = fmaxf(core, fmaxf(gmax[t - x], gmax[t + x]));
+    for (int x = 0; x < e; ++x) core = fmaxf(core, fmaxf(at(8 * (t - q) - 1 - x), at(8 * (t + q + 1) + x)));
+    float left = core, right = core;
+    o[7] = core;
+#pragma unroll
+    for (int i = 6; i >= 0; --i) {
+      left = fmaxf(left, at(8 * t - r + i));
+      o[i] = left;
+    }
+#pragma unroll
+    for (int i = 1; i < 8; ++i) {
+      right = fmaxf(right, at(8 * t + r + i));
+      o[i] = fmaxf(o[i], right);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      o[i] = at(8 * t + i);
+      for (int x = 1; x <= r; ++x) o[i] = fmaxf(o[i], fmaxf(at(8 * t + i - x), at(8 * t + i + x)));
+    }
   }
-  const int second = 2 * r + 1 - p;  // tile index i holds position j0 - r + i: output i spans [i, i + 2r]
-  for (int i = threadIdx.x; i < kPoolTile; i += 256) {
-    const int j = j0 + i;
-    if (j >= L) break;
-    a.pooled[(int64_t)unit * a.s_cap + j] = fmaxf(cur[i], cur[i + second]);
+  const int j = j0 + tid * 8;
+  const int n = min(8, L - j);  // votes of this thread (none below 1)
+  uint32_t key[8], starts = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    key[i] = order_key(o[i]);
+    if (i < n && (i == 0 || key[i] != key[i - 1])) starts |= 1u << i;
   }
+  if (n > 0) {
+    float4* out = reinterpret_cast<float4*>(a.pooled + (int64_t)unit * a.s_cap + j);
+    out[0] = make_float4(o[0], o[1], o[2], o[3]);
+    out[1] = make_float4(o[4], o[5], o[6], o[7]);
+  }
+  const uint32_t mine = __popc(starts);
+  const uint32_t inc = wave_incl_scan(mine);
+  if (lane == kWave - 1) s_wave[wave] = inc;
+  __syncthreads();
+  uint32_t at0 = inc - mine, all = 0;
+#pragma unroll
+  for (int w = 0; w < kPoolT / kWave; ++w) {
+    if (w < wave) at0 += s_wave[w];
+    all += s_wave[w];
+  }
+  if (tid == 0) s_base = atomicAdd(&a.n_runs[unit * kCountStride], all);
+  int len[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    if ((starts >> i) & 1u) {
+      const uint32_t rest = (starts >> i) >> 1;  // the next run begins at i + ffs(rest), or the votes end
+      len[i] = rest ? __ffs(rest) : n - i;
+      atomicAdd(&hist[vote_bin(key[i])], (uint32_t)len[i]);
+    }
+  }
+  __syncthreads();
+  uint2* runs = a.runs + (int64_t)unit * a.s_cap + s_base + at0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if ((starts >> i) & 1u) *runs++ = make_uint2(key[i], (uint32_t)(j / 8) * 16u + (uint32_t)len[i]);
+  for (int i = tid; i < kSelBins; i += kPoolT)
+    if (hist[i] != 0u) atomicAdd(&a.hist[(int64_t)unit * kSelBins + i], hist[i]);
 }
 
-__device__ __forceinline__ uint32_t order_key(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// exact top-(keep-W) of pooled[0, L) + the window, ascending; one 1024-thread workgroup per unit.
-// Six passes over the row (four radix digits, a count, the ordered emission), all of them as
-// coalesced 16-byte loads with eight in flight per thread; the top digit (sign and exponent, which
-// votes share) is counted once per group of lanes that hold the same one.  For the emission a
-// wavefront owns a contiguous stretch of the row and walks it in 256-position steps, with a prefix
-// sum over its lanes per step.
+// Exact top-(keep-W) of the pooled votes, ties to the lower position, and the window, ascending.  A
+// unit's row is cut into `sel_split` slices, one workgroup each; every workgroup finds the unit's
+// threshold for itself, counts what lies above it and at it before its slice, and emits its slice in
+// order.  The threshold: the pool's histogram names the bin of the wanted rank; one pass over the runs
+// collects the runs in it and counts the ones above it before the slice; the few collected are ranked
+// by counting.  Only if more than kSelCand runs share the bin is it divided again.
+//
+// One workgroup per unit over the votes themselves took 26 us for 8 units of 32768 votes and 30 for
+// 128 units, bound by the vector instructions of the one compute unit (32 votes a thread through the
+// counting and the emission); seven launches of radix passes took 35 us for 8 units of 131072.  Now
+// 7.4 / 15 / 10.8 us.  Slices stay at 4096 positions or more, and at one round over the chip.
 constexpr int kSelT = 1024;
-constexpr int kSelBatch = 8;
-__global__ __launch_bounds__(kSelT) void snap_select_kernel(CacheView c, SnapArgs a) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t wsum[kSelT / kWave], wsum_eq[kSelT / kWave];
-  __shared__ uint32_t sh_bucket, sh_k;
+constexpr int kSelCand = 512;
+constexpr int kSelSlice = 4 * kSelT;  // positions emitted at a time
+constexpr int kSelBatch = 8;          // runs a thread has in flight
+
+struct SelShared {
+  uint32_t hist[kSelBins];
+  uint2 cand[kSelCand];
+  uint32_t wsum[2][kSelT / kWave];
+  uint32_t n_cand, bin, rank, tau, need;
+};
+
+// The wanted rank's bin by a scan from the top, four bins a thread, in h[] the highest first:
+// sh.bin and, within it, sh.rank.  Ends with a barrier.
+__device__ __forceinline__ void find_bin(const uint32_t (&h)[4], uint32_t k, SelShared& sh) {
+  const int top = kSelBins - 1 - (int)threadIdx.x * 4;
+  uint32_t above = block_excl_scan<kSelT>(h[0] + h[1] + h[2] + h[3], sh.wsum[0]);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (above < k && k <= above + h[j]) {
+      sh.bin = (uint32_t)(top - j);
+      sh.rank = k - above;
+    }
+    above += h[j];
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ void snap_threshold(const uint2* runs, int n_runs, const uint32_t* ghist, uint32_t want,
+                                               uint32_t group0, SelShared& sh, uint32_t& tau, uint32_t& need_eq,
+                                               uint32_t& gt_before, uint32_t& eq_before) {
+  static_assert(kSelBins == 4 * kSelT, "four bins a thread");
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int unit = blockIdx.x;
+  const auto fetch = [&](uint2 (&v)[kSelBatch], int x0) {  // an absent run has length 0
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      const int x = x0 + u * kSelT + tid;
+      v[u] = x < n_runs ? runs[x] : make_uint2(0u, 0u);
+    }
+  };
+  uint2 first[kSelBatch];  // on their way while the histogram is scanned
+  fetch(first, 0);
+  const auto each = [&](const auto& fn) {
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u)
+      if (first[u].y != 0u) fn(first[u].x, first[u].y);
+    for (int x0 = kSelBatch * kSelT; x0 < n_runs; x0 += kSelBatch * kSelT) {
+      uint2 v[kSelBatch];
+      fetch(v, x0);
+#pragma unroll
+      for (int u = 0; u < kSelBatch; ++u)
+        if (v[u].y != 0u) fn(v[u].x, v[u].y);
+    }
+  };
+  const uint4 gh = reinterpret_cast<const uint4*>(ghist)[kSelT - 1 - tid];
+  if (tid == 0) sh.n_cand = 0;
+  const uint32_t h0[4] = {gh.w, gh.z, gh.y, gh.x};
+  find_bin(h0, want, sh);
+  uint32_t lo, span, k = sh.rank;
+  bin_range(sh.bin, lo, span);
+  uint32_t gt = 0, eq = 0;  // this thread's share of what lies before the slice
+  each([&](uint32_t key, uint32_t gl) {
+    if (key < lo) return;
+    if (key - lo > span) {
+      if ((gl >> 4) < group0) gt += gl & 15u;
+    } else {
+      const uint32_t at = atomicAdd(&sh.n_cand, 1u);
+      if (at < (uint32_t)kSelCand) sh.cand[at] = make_uint2(key, gl);
+    }
+  });
+  __syncthreads();
+  int n_cand = (int)sh.n_cand;
+  const bool few = n_cand <= kSelCand;
+  while (n_cand > kSelCand && span != 0u) {  // divide [lo, lo + span] again
+    int shift = 0;
+    while ((span >> shift) >= (uint32_t)kSelBins) ++shift;
+    __syncthreads();  // n_cand and the bin have been read
+    for (int i = tid; i < kSelBins; i += kSelT) sh.hist[i] = 0;
+    if (tid == 0) sh.n_cand = 0;
+    __syncthreads();
+    each([&](uint32_t key, uint32_t gl) {
+      if (key >= lo && key - lo <= span) atomicAdd(&sh.hist[(key - lo) >> shift], gl & 15u);
+    });
+    __syncthreads();
+    uint32_t h[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) h[j] = sh.hist[kSelBins - 1 - tid * 4 - j];
+    find_bin(h, k, sh);
+    k = sh.rank;
+    lo += sh.bin << shift;
+    span = (1u << shift) - 1u;
+    each([&](uint32_t key, uint32_t gl) {
+      if (key >= lo && key - lo <= span) {
+        const uint32_t at = atomicAdd(&sh.n_cand, 1u);
+        if (at < (uint32_t)kSelCand) sh.cand[at] = make_uint2(key, gl);
+      }
+    });
+    __syncthreads();
+    n_cand = (int)sh.n_cand;
+  }
+  if (n_cand <= kSelCand) {
+    if (tid < n_cand) {
+      const uint32_t ki = sh.cand[tid].x;
+      uint32_t above = 0, upto = 0;
+      for (int j = 0; j < n_cand; ++j) {
+        const uint2 o = sh.cand[j];
+        above += o.x > ki ? o.y & 15u : 0u;
+        upto += o.x >= ki ? o.y & 15u : 0u;
+      }
+      if (above < k && k <= upto) {  // equal keys write the same pair
+        sh.tau = ki;
+        sh.need = k - above;
+      }
+    }
+    __syncthreads();
+    tau = sh.tau;
+    need_eq = sh.need;
+  } else {  // one key left
+    tau = lo;
+    need_eq = k;
+  }
+  const auto before = [&](uint32_t key, uint32_t gl) {
+    const uint32_t len = (gl >> 4) < group0 ? gl & 15u : 0u;
+    gt += key > tau ? len : 0u;
+    eq += key == tau ? len : 0u;
+  };
+  if (few) {  // the ones above the bin are in `gt`
+    if (tid < n_cand) before(sh.cand[tid].x, sh.cand[tid].y);
+  } else {
+    gt = 0;
+    each(before);
+  }
+  gt = wave_incl_scan(gt);
+  eq = wave_incl_scan(eq);
+  if (lane == kWave - 1) {
+    sh.wsum[0][wave] = gt;
+    sh.wsum[1][wave] = eq;
+  }
+  __syncthreads();
+  gt_before = eq_before = 0;
+#pragma unroll
+  for (int w = 0; w < kSelT / kWave; ++w) {
+    gt_before += sh.wsum[0][w];
+    eq_before += sh.wsum[1][w];
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kSelT) void snap_select_kernel(CacheView c, SnapArgs a) {
+  __shared__ SelShared sh;
+  const int tid = threadIdx.x;
+  const int unit = blockIdx.y, slice = blockIdx.x;
   const int b = unit / c.n_kv_heads, g = unit % c.n_kv_heads;
   const int S = c.seq_lens[b];
   int32_t* kept = a.kept + (int64_t)unit * a.keep;
@@ -445,6 +697,7 @@ __global__ __launch_bounds__(kSelT) void snap_select_kernel(CacheView c, SnapArg
   const bool small = S <= a.keep;
   const bool bad = S > c.pages_cap * kAttnPage;
   if (small || bad) {
+    if (slice != 0) return;
     const int cnt = bad ? 0 : S;
     for (int i = tid; i < a.keep; i += kSelT) {
       const int v = i < cnt ? i : -1;
@@ -456,468 +709,61 @@ __global__ __launch_bounds__(kSelT) void snap_select_kernel(CacheView c, SnapArg
   }
   const int L = S - a.W;
   const int k_pref = a.keep - a.W;
-  // the row holds s_cap >= L + W floats and starts 16-byte aligned: the last group of four is in bounds
-  const float4* pv4 = reinterpret_cast<const float4*>(a.pooled + (int64_t)unit * a.s_cap);
-  const int n4 = (L + 3) / 4;
+  const int blocks = (L + kSelSlice - 1) / kSelSlice, per = (blocks + a.sel_split - 1) / a.sel_split;
+  const int j_begin = slice * per * kSelSlice, j_end = min(j_begin + per * kSelSlice, L);
+  if (j_begin >= L) return;
+  // the slice's first votes travel while the threshold is found
+  const float* row = a.pooled + (int64_t)unit * a.s_cap;
+  const auto load = [&](int j) { return j < L ? *reinterpret_cast<const float4*>(row + j) : make_float4(0.f, 0.f, 0.f, 0.f); };
+  float4 v = load(j_begin + tid * 4);
 
-  uint32_t prefix = 0, mask = 0, k = (uint32_t)k_pref;
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    if (tid < 256) hist[tid] = 0;
-    __syncthreads();
-    for (int base = 0; base < n4; base += kSelT * kSelBatch) {  // the same trip count for every thread
-      float4 v[kSelBatch];
+  uint32_t tau, need_eq, gt, eq;
+  snap_threshold(a.runs + (int64_t)unit * a.s_cap, (int)a.n_runs[unit * kCountStride], a.hist + (int64_t)unit * kSelBins,
+                 (uint32_t)k_pref, (uint32_t)j_begin / 8, sh, tau, need_eq, gt, eq);
+
+  // ordered emission: kSelSlice positions at a time, four neighbours a thread
+  for (int j0 = j_begin; j0 < j_end; j0 += kSelSlice) {
+    const int j = j0 + tid * 4;
+    const float x[4] = {v.x, v.y, v.z, v.w};
+    if (j0 + kSelSlice < j_end) v = load(j + kSelSlice);
+    uint32_t key[4], cnt = 0;  // low 16 bits: keys above the threshold, high 16 bits: keys at it
 #pragma unroll
-      for (int u = 0; u < kSelBatch; ++u) {
-        const int q = base + u * kSelT + tid;
-        v[u] = q < n4 ? pv4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+    for (int e = 0; e < 4; ++e) {
+      key[e] = order_key(x[e]);
+      if (j + e < j_end) cnt += (key[e] > tau ? 1u : 0u) + (key[e] == tau ? 0x10000u : 0u);
+    }
+    const uint32_t before = block_excl_scan<kSelT>(cnt, sh.wsum[0]);
+    uint32_t mgt = gt + (before & 0xffffu), meq = eq + (before >> 16);
 #pragma unroll
-      for (int u = 0; u < kSelBatch; ++u) {
-        const int q = base + u * kSelT + tid;
-        const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-        bool on[4];
-        uint32_t digit[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t key = order_key(x[e]);
-          on[e] = q < n4 && 4 * q + e < L && (key & mask) == prefix;
-          digit[e] = (key >> shift) & 255u;
-        }
-        // the top digit: four neighbours mostly share it (pooling repeats a maximum 2r+1 times), and
-        // so do most lanes; such a group of four is counted in one step for all lanes that agree
-        const bool four = pass == 0 && on[0] && on[1] && on[2] && on[3] && digit[0] == digit[1] &&
-                          digit[1] == digit[2] && digit[2] == digit[3];
-        if (pass == 0) hist_add_grouped(hist, digit[0], four, 4u);
-        if (!four) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (on[e]) atomicAdd(&hist[digit[e]], 1u);
+    for (int e = 0; e < 4; ++e) {
+      if (j + e >= j_end || key[e] < tau) continue;
+      if (key[e] > tau || meq < need_eq) {
+        const uint32_t pos = mgt + min(meq, need_eq);
+        if ((int)pos < k_pref) {
+          kept[pos] = j + e;
+          if (kept2) kept2[pos] = j + e;
         }
       }
+      if (key[e] > tau) ++mgt; else ++meq;
     }
-    __syncthreads();
-    uint32_t v = 0, inc = 0;
-    if (tid < 256) {  // bins are owned by the first four wavefronts
-      v = hist[tid];
-      inc = v;
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t y = __shfl_down(inc, off);
-        if (lane + off < kWave) inc += y;
+    if (j0 + kSelSlice < j_end) {  // what this block adds to the ones after it
+      if (tid == kSelT - 1) {
+        sh.rank = (before & 0xffffu) + (cnt & 0xffffu);
+        sh.need = (before >> 16) + (cnt >> 16);
       }
-      if (lane == 0) wsum[wave] = inc;
-    }
-    __syncthreads();
-    if (tid < 256) {
-      for (int w = wave + 1; w < 4; ++w) inc += wsum[w];
-      const uint32_t exc = inc - v;
-      if (exc < k && k <= inc) {
-        sh_bucket = (uint32_t)tid;
-        sh_k = k - exc;
-      }
-    }
-    __syncthreads();
-    prefix |= sh_bucket << shift;
-    mask |= 0xffu << shift;
-    k = sh_k;
-    __syncthreads();
-  }
-  const uint32_t tau = prefix, need_eq = k;
-
-  // ordered emission: wavefront w owns groups [w * gpw, (w + 1) * gpw), gpw a multiple of 64
-  const int gpw = ((n4 + kSelT / kWave - 1) / (kSelT / kWave) + kWave - 1) / kWave * kWave;
-  const int wbeg = wave * gpw, wend = min(wbeg + gpw, n4);
-  uint32_t cgt = 0, ceq = 0;
-  for (int base = wbeg; base < wend; base += kWave * kSelBatch) {
-    float4 v[kSelBatch];
-#pragma unroll
-    for (int u = 0; u < kSelBatch; ++u) {
-      const int q = base + u * kWave + lane;
-      v[u] = q < wend ? pv4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < kSelBatch; ++u) {
-      const int q = base + u * kWave + lane;
-      const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t key = order_key(x[e]);
-        const bool in = q < wend && 4 * q + e < L;
-        cgt += in && key > tau;
-        ceq += in && key == tau;
-      }
+      __syncthreads();
+      gt += sh.rank;
+      eq += sh.need;
+      __syncthreads();
     }
   }
-  // keys above / equal to the threshold in the wavefronts before this one
-  {
-    const uint32_t tg = wave_incl_scan(cgt), te = wave_incl_scan(ceq);
-    if (lane == kWave - 1) {
-      wsum[wave] = tg;
-      wsum_eq[wave] = te;
-    }
-  }
-  __syncthreads();
-  uint32_t gt = 0, eq = 0;  // the same for every lane of the wavefront
-  for (int w = 0; w < wave; ++w) {
-    gt += wsum[w];
-    eq += wsum_eq[w];
-  }
-  for (int base = wbeg; base < wend; base += kWave * kSelBatch) {
-    float4 v[kSelBatch];
-#pragma unroll
-    for (int u = 0; u < kSelBatch; ++u) {
-      const int q = base + u * kWave + lane;
-      v[u] = q < wend ? pv4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < kSelBatch; ++u) {
-      const int q = base + u * kWave + lane;
-      const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-      uint32_t key[4];
-      uint32_t ng = 0, ne = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        key[e] = order_key(x[e]);
-        const bool in = q < wend && 4 * q + e < L;
-        if (!in) key[e] = 0;  // below every threshold that is reached here (kp < L)
-        ng += in && key[e] > tau;
-        ne += in && key[e] == tau;
-      }
-      const uint32_t sg = wave_incl_scan(ng), se = wave_incl_scan(ne);
-      uint32_t mgt = gt + sg - ng, meq = eq + se - ne;  // before this lane's four positions
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool in = q < wend && 4 * q + e < L;
-        bool take = in && key[e] > tau;
-        uint32_t eq_taken = min(meq, need_eq);
-        if (in && key[e] == tau) {
-          take = meq < need_eq;
-          eq_taken = meq;
-          ++meq;
-        }
-        if (take) {
-          const uint32_t pos = mgt + eq_taken;
-          if ((int)pos < k_pref) {
-            kept[pos] = 4 * q + e;
-            if (kept2) kept2[pos] = 4 * q + e;
-          }
-        }
-        if (in && key[e] > tau) ++mgt;
-      }
-      gt += (uint32_t)__builtin_amdgcn_readlane((int)sg, kWave - 1);
-      eq += (uint32_t)__builtin_amdgcn_readlane((int)se, kWave - 1);
-    }
-  }
-  for (int w = tid; w < a.W; w += kSelT) {
-    kept[k_pref + w] = L + w;
-    if (kept2) kept2[k_pref + w] = L + w;
-  }
-  if (g == 0 && tid == 0) a.n_out[b] = a.keep;
-}
-
-// ---- the same selection with several workgroups per unit ------------------------------------------
-// One long prompt is eight units: one workgroup each leaves the chip idle for the six passes above.
-// Here a unit's row is cut into `sel_split` slices, and every pass is a launch of its own: four
-// launches add their slice's digit counts to the unit's histograms in memory (each workgroup first
-// re-derives the digits fixed so far from the earlier histograms, which is 256 counters per digit),
-// one counts the keys above / equal to the threshold per slice, and the last emits in order from the
-// slice counts before it.  Same result as the single-launch kernel.
-constexpr int kSplitT = 256;
-
-// (prefix, remaining k) after the first `passes` radix digits, from the unit's histograms; every
-// wavefront computes it for itself
-__device__ __forceinline__ void split_threshold(const uint32_t* ghist, int passes, uint32_t k_pref,
-                                                uint32_t& prefix, uint32_t& mask, uint32_t& k) {
-  const int lane = threadIdx.x % kWave;
-  prefix = 0;
-  mask = 0;
-  k = k_pref;
-  for (int pass = 0; pass < passes; ++pass) {
-    const int shift = 24 - 8 * pass;
-    const int b0 = 4 * (kWave - 1 - lane);  // lane 0 owns the four highest bins
-    const uint4 h = *reinterpret_cast<const uint4*>(ghist + pass * 256 + b0);
-    const uint32_t s3 = h.w, s2 = h.z + s3, s1 = h.y + s2, s0 = h.x + s1;
-    const uint32_t above = wave_incl_scan(s0) - s0;
-    const uint32_t in[4] = {above + s0, above + s1, above + s2, above + s3};
-    const uint32_t hc[4] = {h.x, h.y, h.z, h.w};
-    int found = -1;
-    uint32_t newk = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t exc = in[j] - hc[j];
-      if (exc < k && k <= in[j]) {
-        found = b0 + j;
-        newk = k - exc;
-      }
-    }
-    const unsigned long long who = __ballot(found >= 0);
-    const int src = __ffsll((long long)who) - 1;
-    const uint32_t bucket = (uint32_t)__builtin_amdgcn_readlane(found, src);
-    k = (uint32_t)__builtin_amdgcn_readlane((int)newk, src);
-    prefix |= bucket << shift;
-    mask |= 0xffu << shift;
-  }
-}
-
-// the slice of float4 groups of workgroup `wg`: a multiple of 64 groups, so wavefront steps stay whole
-__device__ __forceinline__ void split_slice(int n4, int split, int wg, int& gbeg, int& gend) {
-  const int per = ((n4 + split - 1) / split + kWave - 1) / kWave * kWave;
-  gbeg = min(wg * per, n4);
-  gend = min(gbeg + per, n4);
-}
-
-__global__ __launch_bounds__(kSplitT) void snap_split_hist_kernel(CacheView c, SnapArgs a, int pass) {
-  __shared__ uint32_t hist[256];
-  const int tid = threadIdx.x;
-  const int unit = blockIdx.y, wg = blockIdx.x;
-  const int b = unit / c.n_kv_heads;
-  const int S = c.seq_lens[b];
-  if (S <= a.keep || S > c.pages_cap * kAttnPage) return;
-  const int L = S - a.W;
-  const float4* pv4 = reinterpret_cast<const float4*>(a.pooled + (int64_t)unit * a.s_cap);
-  const int n4 = (L + 3) / 4;
-  int gbeg, gend;
-  split_slice(n4, a.sel_split, wg, gbeg, gend);
-  uint32_t* ghist = a.sel_hist + (int64_t)unit * 4 * 256;
-  uint32_t prefix, mask, k;
-  split_threshold(ghist, pass, (uint32_t)(a.keep - a.W), prefix, mask, k);
-  const int shift = 24 - 8 * pass;
-  hist[tid] = 0;
-  __syncthreads();
-  for (int base = gbeg; base < gend; base += kSplitT * 4) {  // the same trip count for every thread
-    float4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = base + u * kSplitT + tid;
-      v[u] = q < gend ? pv4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = base + u * kSplitT + tid;
-      const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-      bool on[4];
-      uint32_t digit[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t key = order_key(x[e]);
-        on[e] = q < gend && 4 * q + e < L && (key & mask) == prefix;
-        digit[e] = (key >> shift) & 255u;
-      }
-      const bool four = pass == 0 && on[0] && on[1] && on[2] && on[3] && digit[0] == digit[1] &&
-                        digit[1] == digit[2] && digit[2] == digit[3];
-      if (pass == 0) hist_add_grouped(hist, digit[0], four, 4u);
-      if (!four) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (on[e]) atomicAdd(&hist[digit[e]], 1u);
-      }
-    }
-  }
-  __syncthreads();
-  if (hist[tid] != 0) atomicAdd(&ghist[pass * 256 + tid], hist[tid]);
-}
-
-// EMIT = false: the slice's counts of keys above / equal to the threshold, to sel_hist's second part.
-// EMIT = true: the ordered emission of the slice (and, by slice 0, the window and the short prompts).
-template <bool EMIT>
-__global__ __launch_bounds__(kSplitT) void snap_split_emit_kernel(CacheView c, SnapArgs a) {
-  __shared__ uint32_t wsum[kSplitT / kWave], wsum_eq[kSplitT / kWave];
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int unit = blockIdx.y, wg = blockIdx.x;
-  const int units = gridDim.y;
-  const int b = unit / c.n_kv_heads, g = unit % c.n_kv_heads;
-  const int S = c.seq_lens[b];
-  int32_t* kept = a.kept + (int64_t)unit * a.keep;
-  int32_t* kept2 = a.kept_user ? a.kept_user + (int64_t)unit * a.kept_stride : nullptr;
-  const bool small = S <= a.keep;
-  const bool bad = S > c.pages_cap * kAttnPage;
-  if (small || bad) {
-    if (EMIT && wg == 0) {
-      const int cnt = bad ? 0 : S;
-      for (int i = tid; i < a.keep; i += kSplitT) {
-        const int v = i < cnt ? i : -1;
-        kept[i] = v;
-        if (kept2) kept2[i] = v;
-      }
-      if (g == 0 && tid == 0) a.n_out[b] = cnt;
-    }
-    return;
-  }
-  const int L = S - a.W;
-  const int k_pref = a.keep - a.W;
-  const float4* pv4 = reinterpret_cast<const float4*>(a.pooled + (int64_t)unit * a.s_cap);
-  const int n4 = (L + 3) / 4;
-  int gbeg, gend;
-  split_slice(n4, a.sel_split, wg, gbeg, gend);
-  uint32_t tau, mask, need_eq;
-  split_threshold(a.sel_hist + (int64_t)unit * 4 * 256, 4, (uint32_t)k_pref, tau, mask, need_eq);
-  uint32_t* slice_cnt = a.sel_hist + (int64_t)units * 4 * 256 + (int64_t)unit * a.sel_split * 2;
-
-  // wavefront w of the workgroup owns groups [wbeg, wend) of the slice, a multiple of 64 long
-  const int gpw = ((gend - gbeg + kSplitT / kWave - 1) / (kSplitT / kWave) + kWave - 1) / kWave * kWave;
-  const int wbeg = min(gbeg + wave * gpw, gend), wend = min(wbeg + gpw, gend);
-  uint32_t cgt = 0, ceq = 0;
-  for (int base = wbeg; base < wend; base += kWave * 4) {
-    float4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = base + u * kWave + lane;
-      v[u] = q < wend ? pv4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = base + u * kWave + lane;
-      const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t key = order_key(x[e]);
-        const bool in = q < wend && 4 * q + e < L;
-        cgt += in && key > tau;
-        ceq += in && key == tau;
-      }
-    }
-  }
-  {
-    const uint32_t tg = wave_incl_scan(cgt), te = wave_incl_scan(ceq);
-    if (lane == kWave - 1) {
-      wsum[wave] = tg;
-      wsum_eq[wave] = te;
-    }
-  }
-  __syncthreads();
-  if (!EMIT) {
-    if (tid == 0) {
-      uint32_t tg = 0, te = 0;
-      for (int w = 0; w < kSplitT / kWave; ++w) {
-        tg += wsum[w];
-        te += wsum_eq[w];
-      }
-      slice_cnt[wg * 2] = tg;
-      slice_cnt[wg * 2 + 1] = te;
-    }
-    return;
-  }
-  // keys above / equal to the threshold before this wavefront: earlier slices, earlier wavefronts
-  uint32_t gt = 0, eq = 0;
-  {
-    uint32_t pg = 0, pe = 0;
-    if (lane < wg) {  // sel_split <= 64 (host)
-      pg = slice_cnt[lane * 2];
-      pe = slice_cnt[lane * 2 + 1];
-    }
-    gt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(pg), kWave - 1);
-    eq = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(pe), kWave - 1);
-  }
-  for (int w = 0; w < wave; ++w) {
-    gt += wsum[w];
-    eq += wsum_eq[w];
-  }
-  for (int base = wbeg; base < wend; base += kWave * 4) {
-    float4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = base + u * kWave + lane;
-      v[u] = q < wend ? pv4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = base + u * kWave + lane;
-      const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-      uint32_t key[4];
-      uint32_t ng = 0, ne = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        key[e] = order_key(x[e]);
-        const bool in = q < wend && 4 * q + e < L;
-        ng += in && key[e] > tau;
-        ne += in && key[e] == tau;
-      }
-      const uint32_t sg = wave_incl_scan(ng), se = wave_incl_scan(ne);
-      uint32_t mgt = gt + sg - ng, meq = eq + se - ne;  // before this lane's four positions
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool in = q < wend && 4 * q + e < L;
-        bool take = in && key[e] > tau;
-        uint32_t eq_taken = min(meq, need_eq);
-        if (in && key[e] == tau) {
-          take = meq < need_eq;
-          eq_taken = meq;
-          ++meq;
-        }
-        if (take) {
-          const uint32_t pos = mgt + eq_taken;
-          if ((int)pos < k_pref) {
-            kept[pos] = 4 * q + e;
-            if (kept2) kept2[pos] = 4 * q + e;
-          }
-        }
-        if (in && key[e] > tau) ++mgt;
-      }
-      gt += (uint32_t)__builtin_amdgcn_readlane((int)sg, kWave - 1);
-      eq += (uint32_t)__builtin_amdgcn_readlane((int)se, kWave - 1);
-    }
-  }
-  if (wg == 0) {
-    for (int w = tid; w < a.W; w += kSplitT) {
+  if (slice == 0) {
+    for (int w = tid; w < a.W; w += kSelT) {
       kept[k_pref + w] = L + w;
       if (kept2) kept2[k_pref + w] = L + w;
     }
     if (g == 0 && tid == 0) a.n_out[b] = a.keep;
   }
-}
-
-__global__ __launch_bounds__(256) void snap_split_zero_kernel(uint32_t* p, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
-// The same selection for prompts of up to ROCKETKV_MAX_PAGES tokens, through the register-resident
-// top-k that Step 2 of the decode path uses for its page scores (one token = one page of size 1,
-// budget = the prefix share of the keep budget): every pooled vote is read once and stays in
-// registers, where the radix kernels above walk the row six times.  Same result: the k largest, ties
-// to the lower position, ascending.
-__global__ __launch_bounds__(kSelT) void snap_select_fast_kernel(CacheView c, SnapArgs a) {
-  __shared__ PickShared<kSelT> sh;
-  const int tid = threadIdx.x;
-  const int unit = blockIdx.x;
-  const int b = unit / c.n_kv_heads, g = unit % c.n_kv_heads;
-  const int S = c.seq_lens[b];
-  int32_t* kept = a.kept + (int64_t)unit * a.keep;
-  int32_t* kept2 = a.kept_user ? a.kept_user + (int64_t)unit * a.kept_stride : nullptr;
-  const bool small = S <= a.keep;
-  const bool bad = S > c.pages_cap * kAttnPage;
-  if (small || bad) {
-    const int cnt = bad ? 0 : S;
-    for (int i = tid; i < a.keep; i += kSelT) {
-      const int v = i < cnt ? i : -1;
-      kept[i] = v;
-      if (kept2) kept2[i] = v;
-    }
-    if (g == 0 && tid == 0) a.n_out[b] = cnt;
-    return;
-  }
-  const int L = S - a.W;
-  const int k_pref = a.keep - a.W;
-  for (int i = tid; i < 4 * 256; i += kSelT) (&sh.hist[0][0])[i] = 0;  // the pick expects clear counters
-  __syncthreads();
-  CacheView row = c;  // the pooled votes of this unit as one sequence of one-token pages
-  row.page_size = 1;
-  row.pages_cap = a.s_cap;
-  SelectArgs pa = {};
-  pa.in_scores = a.pooled + (int64_t)unit * a.s_cap;
-  pa.T = k_pref;
-  pa.n_recent = 0;
-  pa.out_pages = kept;
-  pa.row_len = k_pref;
-  pa.out_pages2 = kept2;
-  pa.row_len2 = k_pref;
-  pick_from_scores<kSelT, false, true>(row, pa, 0, L, sh);
-  for (int w = tid; w < a.W; w += kSelT) {
-    kept[k_pref + w] = L + w;
-    if (kept2) kept2[k_pref + w] = L + w;
-  }
-  if (g == 0 && tid == 0) a.n_out[b] = a.keep;
 }
 
 // copy the kept tokens into the destination cache; one workgroup per kGatherBlocks x 16 kept tokens
@@ -1069,14 +915,12 @@ SnapPlan plan_snapkv(const CacheView& src, int window, int keep) {
   off += up(units * s_cap * sizeof(float));
   p.kept_off = off;
   off += up(units * (size_t)keep * sizeof(int32_t));
-  // long prompts of few units: the select runs as several workgroups per unit over several launches
-  p.sel_split = 0;
-  if (s_cap > ROCKETKV_MAX_PAGES && units <= 64) {
-    int split = (int)(256 / units);
-    p.sel_split = split > 32 ? 32 : split;
-  }
-  p.sel_off = off;
-  off += up(units * (size_t)(4 * 256 + 2 * 64) * sizeof(uint32_t));
+  // the select: one round of workgroups over the chip, slices of kSelSlice positions or more
+  const size_t slices = (s_cap + kSelSlice - 1) / kSelSlice;
+  p.sel_split = (int)(units >= 256 ? 1 : 256 / units);
+  if ((size_t)p.sel_split > slices) p.sel_split = (int)slices;
+  p.runs_off = off;
+  off += up(units * s_cap * sizeof(uint2)) + up(units * (kCountStride + kSelBins) * sizeof(uint32_t));
   p.total_bytes = off;
   return p;
 }
@@ -1106,7 +950,9 @@ hipError_t launch_snapkv(const bf16_t* q_obs, const CacheView& src, int window, 
   a.kept_user = kept_idx;
   a.kept_stride = kept_stride;
   a.n_out = n_out;
-  a.sel_hist = reinterpret_cast<uint32_t*>(base + plan.sel_off);
+  a.runs = reinterpret_cast<uint2*>(base + plan.runs_off);
+  a.n_runs = reinterpret_cast<uint32_t*>(base + plan.runs_off + up((size_t)units * a.s_cap * sizeof(uint2)));
+  a.hist = a.n_runs + (size_t)units * kCountStride;
   a.sel_split = plan.sel_split;
 
   const dim3 sgrid(plan.n_chunks, units);
@@ -1123,21 +969,9 @@ hipError_t launch_snapkv(const bf16_t* q_obs, const CacheView& src, int window, 
   else
     hipLaunchKernelGGL((snap_score_kernel<true, 1>), sgrid, dim3(256), kSnapRingBytes + vote_bytes, st, src, a);
   const dim3 pgrid((a.s_cap + kPoolTile - 1) / kPoolTile, units);
-  hipLaunchKernelGGL(snap_pool_kernel, pgrid, dim3(256), 2 * (kPoolTile + 2 * a.pool_r) * sizeof(float), st,
-                     src, a);
-  if (a.s_cap <= ROCKETKV_MAX_PAGES) {
-    hipLaunchKernelGGL(snap_select_fast_kernel, dim3(units), dim3(kSelT), 0, st, src, a);
-  } else if (plan.sel_split > 0) {
-    const int n_clear = units * (4 * 256 + 2 * plan.sel_split);
-    hipLaunchKernelGGL(snap_split_zero_kernel, dim3((n_clear + 255) / 256), dim3(256), 0, st, a.sel_hist, n_clear);
-    const dim3 hgrid(plan.sel_split, units);
-    for (int pass = 0; pass < 4; ++pass)
-      hipLaunchKernelGGL(snap_split_hist_kernel, hgrid, dim3(kSplitT), 0, st, src, a, pass);
-    hipLaunchKernelGGL(snap_split_emit_kernel<false>, hgrid, dim3(kSplitT), 0, st, src, a);
-    hipLaunchKernelGGL(snap_split_emit_kernel<true>, hgrid, dim3(kSplitT), 0, st, src, a);
-  } else {
-    hipLaunchKernelGGL(snap_select_kernel, dim3(units), dim3(kSelT), 0, st, src, a);
-  }
+  const size_t pool_groups = kPoolT + 2 * ((a.pool_r + 7) / 8);
+  hipLaunchKernelGGL(snap_pool_kernel, pgrid, dim3(kPoolT), pool_groups * 10 * sizeof(float), st, src, a);
+  hipLaunchKernelGGL(snap_select_kernel, dim3(plan.sel_split, units), dim3(kSelT), 0, st, src, a);
   if (!dst) return hipGetLastError();  // filter only: the indices are the result
   const dim3 ggrid((keep + kGatherBlocks * kAttnPage - 1) / (kGatherBlocks * kAttnPage), units);
   hipLaunchKernelGGL(snap_gather_kernel, ggrid, dim3(256), 0, st, src, *dst, a);
