@@ -83,6 +83,15 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
          (uint32_t)__builtin_amdgcn_readlane((int)(v & 0xffffffff), l);
 }
 
+// 16 bytes per lane from `src` straight to LDS: lane l's land 16 l bytes behind the wavefront's `dst`
+template <int POLICY>
+__device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
+#ifdef __HIP_DEVICE_COMPILE__  // the builtin is unknown to the host pass
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, POLICY);
+#endif
+}
+
 constexpr int kSnapMaxIters = 2 * kWave;  // pages one wavefront walks in a chunk, at most
 constexpr int kSnapRing = 3;              // key tiles a wavefront keeps in flight (4 KiB of LDS each)
 constexpr size_t kSnapRingBytes = (size_t)4 * kSnapRing * 4 * kWave * 16;  // four wavefronts
@@ -106,7 +115,8 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
   const int p_begin = chunk * a.chunk_pages;
   const int p_limit = PASS2 ? (L + kAttnPage - 1) / kAttnPage : (S + kAttnPage - 1) / kAttnPage;
   const int p_end = min(p_begin + a.chunk_pages, p_limit);
-  const int n_it = p_end > p_begin ? (p_end - p_begin + npw - 1) / npw : 0;  // <= kSnapMaxIters (host)
+  if (p_begin >= p_end) return;  // a chunk beyond the prompt: its statistics are never read
+  const int n_it = (p_end - p_begin + npw - 1) / npw;  // <= kSnapMaxIters (host)
 
   // Where this wavefront's pages live: lane i looks up iterations i and i + 64 once, up front, and
   // the loop hands the tile offsets out by readlane, so it contains no table lookups and no waits
@@ -158,16 +168,18 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
   // belongs there: the chunks of a row are stored XOR-swizzled by the row number, so that the reads
   // below (16 rows at one chunk position) spread over all LDS banks.
   const int dma_row = lane >> 4;                 // + 4 j
-  const auto issue = [&](int it, int slot) {
-    const int64_t off = tile_off(it);
-    const bf16_t* kt = c.k_pool + (off >= 0 ? off : 0) + head_off;
+  const auto fetch = [&](const bf16_t* rows, ring_u32x4* dst, auto policy) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int row = 4 * j + dma_row;
       const int chunk = (lane & 15) ^ row;
-      __builtin_amdgcn_global_load_lds(reinterpret_cast<const ring_u32x4*>(kt + row * kHeadDim + chunk * 8),
-                                       ring + (slot * 4 + j) * kWave, 16, 0, PASS2 ? 0 : kPolicyStream);
+      load_to_lds<decltype(policy)::value>(rows + row * kHeadDim + chunk * 8, dst + j * kWave);
     }
+  };
+  const auto issue = [&](int it, int slot) {
+    const int64_t off = tile_off(it);
+    fetch(c.k_pool + (off >= 0 ? off : 0) + head_off, ring + slot * 4 * kWave,
+          std::integral_constant<int, PASS2 ? 0 : kPolicyStream>{});
   };
   const auto read_tile = [&](int slot, bf16x8* kf) {
     // everything but the kSnapRing - 1 younger tiles (four loads each) has landed
@@ -223,7 +235,7 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
       *reinterpret_cast<float4*>(s_votes + cgi * chunk_tokens + (tok0 - p_begin * kAttnPage)) =
           make_float4(v[0], v[1], v[2], v[3]);
   };
-  int slot = 0;
+  int slot = kSnapRing - 1;  // the first tile's; see below
   // One page: its tile out of the ring, then per group of four column blocks the products and the
   // update; the slot is refilled once the last products have read it.
   const auto page = [&](auto masked_tag, int it) {
@@ -267,32 +279,63 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
     if (p_last >= p_begin + pw) n_fast = (p_last - p_begin - pw) / npw + 1;
     n_fast = min(n_fast, n_it);
   }
+  // The queries: fetched once per workgroup, as whole cache lines, into two of every wavefront's three
+  // ring slots, laid out like the key tiles (16 softmax rows for 16 tokens) and read from there; the
+  // first key tile travels beside them into the third slot.  (Every wavefront fetching its fragments
+  // from memory by itself took 9 us per workgroup, as long as 30 tiles: 128 loads of 16 half lines each
+  // through one first-level cache.  A pass over one prompt of 32768 tokens, 512 workgroups: 24.8 ->
+  // 20.5 us; over 16 of them, 2048 workgroups: 204 -> 190 and 247 -> 232.)  The rows of a group's heads
+  // lie one after the other, so column `col` is simply row `col`; window and group x window are
+  // multiples of 16, so a block of 16 columns is real or not as a whole and its place in the window is
+  // a scalar.
+  static_assert(kSnapRing == 3 && kSnapColBlocks == 8, "eight blocks of queries fill two slots of four wavefronts");
+  const auto block_at = [&](int cb) {  // where block cb lies: slot cb / 4 of wavefront cb % 4
+    return reinterpret_cast<ring_u32x4*>(snap_dyn) + ((cb % 4) * kSnapRing + cb / 4) * 4 * kWave;
+  };
+  const bf16_t* q_rows = a.qobs + ((int64_t)b * c.n_q_heads + (int64_t)g * c.group) * a.W * kHeadDim;
+  for (int cg = 0; cg < a.CG; ++cg) {
+    if (cg > 0) __syncthreads();  // the blocks of the group before have been read
 #pragma unroll
-  for (int t = 0; t < kSnapRing; ++t) issue(t, t);
-  // the queries (and pass 2's row statistics) come in behind the first tiles rather than before them
-#pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) {
-    const int col = (cgi * kSnapColBlocks + cb) * 16 + hn;
-    if (col < a.NC) {
-      const int h = col / a.W, w = col % a.W;
-      const bf16_t* qp =
-          a.qobs + (((int64_t)b * c.n_q_heads + (int64_t)g * c.group + h) * a.W + w) * kHeadDim + kg * 8;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) qf[cb][j].u = *reinterpret_cast<const uint4*>(qp + j * 32);
-      limit[cb] = L + w;
-      if (PASS2) {
-        const float2 st2 = *reinterpret_cast<const float2*>(a.stats + ((int64_t)unit * a.NC + col) * 2);
-        M2[cb] = st2.x;
-        invZ[cb] = st2.y;
-      }
+    for (int h = 0; h < QD; ++h) {
+      const int cb = h * 4 + wave, block = cg * kSnapColBlocks + cb;
+      if (block * 16 < a.NC) fetch(q_rows + block * 16 * kHeadDim, block_at(cb), std::integral_constant<int, 0>{});
+    }
+    if (cg == 0) {
+      issue(0, slot);
+      asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // all but the first key tile
     } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    __syncthreads();
+    if (cg == cgi) {
+      int w0 = cg * kSnapColBlocks * 16 % a.W;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) qf[cb][j].u = make_uint4(0, 0, 0, 0);
-      limit[cb] = -1;
-      M2[cb] = 0.f;
-      invZ[cb] = 0.f;
+      for (int cb = 0; cb < NCB; ++cb) {
+        const bool real = (cg * kSnapColBlocks + cb) * 16 < a.NC;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const ring_u32x4 x = block_at(cb)[hn * 16 + ((4 * j + kg) ^ hn)];
+          qf[cb][j].u = real ? make_uint4(x.x, x.y, x.z, x.w) : make_uint4(0, 0, 0, 0);
+        }
+        limit[cb] = real ? L + w0 + hn : -1;
+        w0 = w0 + 16 == a.W ? 0 : w0 + 16;
+      }
     }
   }
+  if (PASS2) {
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      const int col = (cgi * kSnapColBlocks + cb) * 16 + hn;
+      const float2 st2 = col < a.NC ? *reinterpret_cast<const float2*>(a.stats + ((int64_t)unit * a.NC + col) * 2)
+                                    : make_float2(0.f, 0.f);
+      M2[cb] = st2.x;
+      invZ[cb] = st2.y;
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();  // the blocks have been read: their slots take key tiles now
+  issue(1, 0);
+  issue(2, 1);
   int it = 0;
   for (; it < n_fast; ++it) page(std::false_type{}, it);
   for (; it < n_it; ++it) page(std::true_type{}, it);
