@@ -213,6 +213,10 @@ __device__ __forceinline__ void attend_tokens_block(const CacheView& c, const At
     const unsigned long long fresh = PATCH ? __ballot(is_new) : 0ull;
     const int cnt = min(kWave, we - base);
     for (int i = 0; i * 32 < cnt; ++i) {
+      // None of the group holds a token (the end of a list shorter than its row): nothing to read, and with
+      // pages that do not divide the share a round trip less for its last wavefront.  (Only where the list
+      // comes from memory: in the fused kernels the test costs what it gains.)
+      if (!INDEXED && !PATCH && (uint32_t)(live >> (32 * i)) == 0u) continue;
       u32x4 kf[2][4], vr[2][4];
       const bf16_t* vt[2];
 #pragma unroll
