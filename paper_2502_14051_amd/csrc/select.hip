@@ -165,13 +165,23 @@ hipError_t launch_hsa_select(const CacheView& c, const SelectArgs& a, hipStream_
   return hipGetLastError();
 }
 
+// A unit's summary rows go to as many workgroups as leave one per compute unit, up to eight (their
+// reports queue up at the unit's counter: 16 are slower again) and 16 runs each: a compute unit draws
+// some 30 GB/s of cold rows, so with few units the rows are what the launch waits for.  9675 tokens in
+// pages of 3 at 81 channels, us per layer-step with two workgroups per unit and now: one sequence
+// 30.2 / 25.4 (four per unit 26.8, sixteen 25.9), two 31.1 / 27.0, eight 35.7 / 32.8.
+constexpr int kMaxScoreSplit = 8;
+constexpr int kMinScoreRuns = 16;
+
 hipError_t launch_hsa_select_split(const CacheView& c, const SelectArgs& a, const AppendArgs& ap,
                                    uint32_t* unit_counters, uint32_t* seq_counters, hipStream_t st) {
   const int units = c.batch * c.n_kv_heads;
   const int runs = (c.pages_cap + 7) / 8;
   if (unit_counters) {
     // with counters to meet at: scores and top-k in one launch
-    const dim3 grid((runs + kPickThreads / 4 - 1) / (kPickThreads / 4), units);
+    int per_unit = (runs + kPickThreads / 4 - 1) / (kPickThreads / 4);
+    while (per_unit < kMaxScoreSplit && 2 * per_unit * units <= 256 && runs >= 2 * per_unit * kMinScoreRuns) per_unit *= 2;
+    const dim3 grid(per_unit, units);
     if (ap.k_new)
       hipLaunchKernelGGL((hsa_score_kernel<kPickThreads, true, true>), grid, dim3(kPickThreads), 0, st, c, a, ap,
                          unit_counters, seq_counters);
