@@ -449,7 +449,9 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 // small probabilities under a few heavy tokens: equal-width bins would put nearly all into the lowest).
 // The select starts from those: about a sixth of the votes, and its first counting pass done.  The
 // counters of different units sit in lines of their own (adds to one line queue up: 128 units sharing
-// four lines took 27 us here and 8 units of 131072 votes sharing one 16.5; 17.8 and 10.2 apart).
+// four lines took 27 us here and 8 units of 131072 votes sharing one 16.5; 17.7 and 10.1 apart.
+// Clearing and reading the bins is the same work for a workgroup of any size: 14.5 and 8.1 with 512
+// threads instead of 256, no more with 1024.).
 constexpr uint32_t kBinBase = (127u + 8u - 64u) << 6;  // bins cover 2^-56 .. 2^8; the first and the last take the rest
 
 __device__ __forceinline__ uint32_t vote_bin(uint32_t key) {  // monotone in the ordered bits
@@ -464,7 +466,7 @@ __device__ __forceinline__ void bin_range(uint32_t bin, uint32_t& lo, uint32_t& 
   span = last - lo;
 }
 
-constexpr int kPoolT = 256;
+constexpr int kPoolT = 512;
 constexpr int kPoolTile = kPoolT * 8;
 __global__ __launch_bounds__(kPoolT) void snap_pool_kernel(CacheView c, SnapArgs a) {
   extern __shared__ float smem[];  // raw[], one float of padding per eight, then the groups' maxima
