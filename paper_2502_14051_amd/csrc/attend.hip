@@ -84,7 +84,13 @@ AttendPlan plan_attend(const CacheView& c, int row_len, bool gather) {
   // append at the benchmark shape, and is not used.
   p.n_csplit = 1;
   p.dense_aim = p.dense_limit = 0;
-  if (!gather && (int64_t)units * ((row_len + 2 * waves - 1) / (2 * waves)) > kComputeUnits) {
+  // Short rows and large batches keep the division by capacity as well: deriving the other one costs every
+  // workgroup its time, more than 64 sequences at a time several times over, and a row of a few dozen
+  // pages is one workgroup's work in any case (60 sequences of 300 tokens 15.6 against 16.8 us, 96 of 1000
+  // 61.5 against 67.9, 512 of 500 166 against 215; but 128 of 2000 178 against 163, 108 against 68.5
+  // with unequal lengths).
+  const bool divide = (c.batch <= kWave && row_len >= 48) || (c.batch <= 2 * kWave && row_len >= 100);
+  if (!gather && divide && (int64_t)units * ((row_len + 2 * waves - 1) / (2 * waves)) > kComputeUnits) {
     // The workgroups divide the pages that are there between them (dense_share), so the launch only
     // has to hold as many as that division can make: the aim, or two per sequence.  Below this size
     // every workgroup has the smallest share whatever the lengths are and all of them run at once:

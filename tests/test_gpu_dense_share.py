@@ -16,14 +16,15 @@ pytestmark = pytest.mark.gpu
     (4, 1, (1,), 16, 0),                                   # one page: one share
     (4, 1, (255, 256, 257), 16, 0),                        # around the smallest share of eight wavefronts
     (32, 8, (0, 5000, 17, 1), 16, 0),                      # an empty sequence among unequal ones
-    (15, 5, (3001, 150, 1600), 16, 0),                     # heads that do not divide the workgroups
-    (16, 16, tuple(5 + 37 * i for i in range(20)), 16, 0),  # more units than compute units
-    (2, 2, tuple((97 * i) % 700 for i in range(70)), 16, 0),  # a second block of 64 sequences
-    (16, 1, (2000, 31), 16, 0),                            # the largest group: four wavefronts
+    (15, 5, (3001, 150, 1600, 3100), 16, 0),                     # heads that do not divide the workgroups
+    (16, 16, tuple(5 + 47 * i for i in range(20)), 16, 0),  # more units than compute units
+    (2, 2, tuple((97 * i) % 1700 for i in range(70)), 16, 0),  # a second block of 64 sequences
+    (16, 1, (20000, 31, 9000), 16, 0),                            # the largest group: four wavefronts
     (8, 2, (40000, 700), 16, 0),
-    (8, 2, (4097, 0, 333), 3, 1),                          # token-major, pages that do not divide 16
-    (32, 8, (2500, 16, 1111), 16, 1),
-    (6, 6, tuple(3 + 11 * i for i in range(66)), 1, 1),
+    (8, 2, (30000, 0, 333), 3, 1),                          # token-major, pages that do not divide 16
+    (32, 8, (2700, 16, 1111), 16, 1),
+    (6, 6, tuple(5 + 60 * i for i in range(20)), 1, 1),
+    (4, 1, (300, 17), 16, 0),                              # below the line: divided by capacity,
 ])
 def test_unequal_lengths(oracle, hq, hkv, lens, ps, layout):
     import torch
