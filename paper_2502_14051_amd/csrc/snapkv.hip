@@ -16,7 +16,7 @@
 
 #include "common.h"
 #include "select_core.h"
-
+#include "vote_bins.h"
 
 namespace rkv {
 
@@ -32,7 +32,6 @@ union FragS {
   bf16x8 v;
 };
 
-constexpr int kSelBins = 4096;    // histogram of the pooled votes
 constexpr int kCountStride = 64;  // uint32 between the run counters of two units
 
 struct SnapArgs {
@@ -452,20 +451,6 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 // four lines took 27 us here and 8 units of 131072 votes sharing one 16.5; 17.7 and 10.1 apart.
 // Clearing and reading the bins is the same work for a workgroup of any size: 14.5 and 8.1 with 512
 // threads instead of 256, no more with 1024.).
-constexpr uint32_t kBinBase = (127u + 8u - 64u) << 6;  // bins cover 2^-56 .. 2^8; the first and the last take the rest
-
-__device__ __forceinline__ uint32_t vote_bin(uint32_t key) {  // monotone in the ordered bits
-  if (!(key & 0x80000000u)) return 0u;
-  const int x = (int)((key & 0x7fffffffu) >> 17) - (int)kBinBase;
-  return (uint32_t)min(max(x, 0), kSelBins - 1);
-}
-// the keys of a bin: [lo, lo + span]
-__device__ __forceinline__ void bin_range(uint32_t bin, uint32_t& lo, uint32_t& span) {
-  lo = bin == 0u ? 0u : (0x80000000u | ((bin + kBinBase) << 17));
-  const uint32_t last = bin == (uint32_t)kSelBins - 1u ? 0xffffffffu : (0x80000000u | ((bin + 1u + kBinBase) << 17)) - 1u;
-  span = last - lo;
-}
-
 constexpr int kPoolT = 512;
 constexpr int kPoolTile = kPoolT * 8;
 __global__ __launch_bounds__(kPoolT) void snap_pool_kernel(CacheView c, SnapArgs a) {
@@ -641,12 +626,12 @@ __device__ __forceinline__ void snap_threshold(const uint2* runs, int n_runs, co
   if (tid == 0) sh.n_cand = 0;
   const uint32_t h0[4] = {gh.w, gh.z, gh.y, gh.x};
   find_bin(h0, want, sh);
-  uint32_t lo, span, k = sh.rank;
-  bin_range(sh.bin, lo, span);
+  uint32_t k = sh.rank;
+  KeyRange in = bin_range(sh.bin);  // where the wanted key lies
   uint32_t gt = 0, eq = 0;  // this thread's share of what lies before the slice
   each([&](uint32_t key, uint32_t gl) {
-    if (key < lo) return;
-    if (key - lo > span) {
+    if (key < in.lo) return;
+    if (key - in.lo > in.span) {
       if ((gl >> 4) < group0) gt += gl & 15u;
     } else {
       const uint32_t at = atomicAdd(&sh.n_cand, 1u);
@@ -656,15 +641,14 @@ __device__ __forceinline__ void snap_threshold(const uint2* runs, int n_runs, co
   __syncthreads();
   int n_cand = (int)sh.n_cand;
   const bool few = n_cand <= kSelCand;
-  while (n_cand > kSelCand && span != 0u) {  // divide [lo, lo + span] again
-    int shift = 0;
-    while ((span >> shift) >= (uint32_t)kSelBins) ++shift;
+  while (n_cand > kSelCand && in.span != 0u) {
+    const int shift = part_shift(in);
     __syncthreads();  // n_cand and the bin have been read
     for (int i = tid; i < kSelBins; i += kSelT) sh.hist[i] = 0;
     if (tid == 0) sh.n_cand = 0;
     __syncthreads();
     each([&](uint32_t key, uint32_t gl) {
-      if (key >= lo && key - lo <= span) atomicAdd(&sh.hist[(key - lo) >> shift], gl & 15u);
+      if (key >= in.lo && key - in.lo <= in.span) atomicAdd(&sh.hist[(key - in.lo) >> shift], gl & 15u);
     });
     __syncthreads();
     uint32_t h[4];
@@ -672,10 +656,9 @@ __device__ __forceinline__ void snap_threshold(const uint2* runs, int n_runs, co
     for (int j = 0; j < 4; ++j) h[j] = sh.hist[kSelBins - 1 - tid * 4 - j];
     find_bin(h, k, sh);
     k = sh.rank;
-    lo += sh.bin << shift;
-    span = (1u << shift) - 1u;
+    in = part_range(in, sh.bin, shift);
     each([&](uint32_t key, uint32_t gl) {
-      if (key >= lo && key - lo <= span) {
+      if (key >= in.lo && key - in.lo <= in.span) {
         const uint32_t at = atomicAdd(&sh.n_cand, 1u);
         if (at < (uint32_t)kSelCand) sh.cand[at] = make_uint2(key, gl);
       }
@@ -701,7 +684,7 @@ __device__ __forceinline__ void snap_threshold(const uint2* runs, int n_runs, co
     tau = sh.tau;
     need_eq = sh.need;
   } else {  // one key left
-    tau = lo;
+    tau = in.lo;
     need_eq = k;
   }
   const auto before = [&](uint32_t key, uint32_t gl) {

@@ -1,6 +1,6 @@
 """Stage 1's max-pool and select at the edges of their tiles: pooling widths around the groups of eight,
-prompts that end inside a group, tile or slice, the three sizes of run list a workgroup handles, and votes
-with so many ties that one pass of bins cannot decide.
+prompts that end inside a group, tile or slice, the three sizes of run list a workgroup handles, votes
+with so many ties that one pass of bins cannot decide, and a wanted vote at the upper end of the lowest bin.
 
 Selections: exact outside a 1e-3 band around the threshold (the GPU sums votes in fp32, the oracle in fp64);
 where every vote is one of a few well separated values, exact with the tie rule."""
@@ -69,4 +69,39 @@ def test_ties(oracle, values, S, keep, ks):
     rng = np.random.default_rng(S + values)
     d["K"] = np.ascontiguousarray(d["K"][:, :, rng.integers(0, values, size=S)])
     got, ref = kept_of(oracle, d, 1, ks, keep)
+    assert got[0, 0].tolist() == ref["kept"][0, 0].tolist()
+
+
+@pytest.mark.parametrize("S,ks,share", [(5000, 1, 0.5), (5000, 1, 0.0), (20000, 1, 0.9), (5000, 3, 0.5)])
+def test_lowest_bin(oracle, S, ks, share):
+    """One token takes nearly all the weight; the other votes lie around 2^-56, where the lowest bin ends, in levels
+    1/64 octave apart or more.  The wanted one is the highest level of that bin, with more smaller votes in
+    the bin than are ranked at once and others just above it.  Votes in fp32 are off by 1e-5 or so, the levels
+    by 1e-2: exact."""
+    print("[case] lowest bin", S, ks, share, flush=True)
+    rng = np.random.default_rng(S + ks)
+    wanted = 1 + 1 / 128
+    levels = np.array([2.0**-5, 2.0**-3, 2.0**-2, 0.5, 0.75, wanted] + [wanted + i / 64 for i in range(1, 8)])
+    f = rng.choice(levels, size=S, p=[0.1] * 5 + [0.08] + [0.06] * 7)
+    f[S - W:] = levels[0]
+    # q . k / sqrt(128) = log(f) - 60 log 2: a vote is W of those probabilities
+    coarse, q0 = -58.75, 8.0
+    k1 = (np.log(f) - 60 * np.log(2.0)) * np.sqrt(128.0) - coarse * q0
+    K = np.zeros((1, 1, S, 128), dtype=np.float32)
+    K[0, 0, :, 0], K[0, 0, :, 1] = coarse, k1
+    heavy = 4321 % (S - W)
+    K[0, 0, heavy] = 0.0
+    qobs = np.zeros((1, 1, W, 128), dtype=np.float32)
+    qobs[..., 0], qobs[..., 1] = q0, 1.0
+    f[heavy] = 2.0**56
+    r = ks // 2
+    pooled = np.array([f[max(0, j - r):min(S - W, j + r + 1)].max() for j in range(S - W)])
+    above, at = int((pooled > wanted).sum()), int((pooled == wanted).sum())
+    assert (pooled <= wanted).sum() > 512 and at > 2
+    keep = W + above + max(1, int(share * at))
+    d = dict(qobs=wl.f32_to_bf16_bits(qobs), K=wl.f32_to_bf16_bits(K), V=wl.f32_to_bf16_bits(K),
+             q=wl.f32_to_bf16_bits(qobs[:, :, 0]), seq_lens=np.array([S], dtype=np.int32))
+    got, ref = kept_of(oracle, d, 1, ks, keep)
+    theta = np.sort(ref["pooled"][0, 0, :S - W])[::-1][keep - W - 1]
+    assert 2.0**-56 * (1 + 1e-3) < theta < 2.0**-56 * (1 + 1 / 64 - 1e-3)
     assert got[0, 0].tolist() == ref["kept"][0, 0].tolist()
