@@ -29,11 +29,11 @@ __global__ __launch_bounds__(WAVES* kWave) __attribute__((amdgpu_waves_per_eu(2)
 void dense_mfma_kernel(CacheView c, AttendArgs a, DenseGrid grid) {
   extern __shared__ float smem[];
   __shared__ int s_last;
-  const DenseShare s = dense_share(c, grid, 2 * WAVES, blockIdx.x);
+  const DenseShare s = dense_share(c, grid, 2 * WAVES, blockIdx.y);
   if (s.b < 0) return;
-  dense_args(a, c, grid, s, blockIdx.y, WAVES);
+  dense_args(a, c, grid, s, blockIdx.x, WAVES);
   const TailPatch none = {-1, 0, nullptr, nullptr};
-  attend_block<WAVES, 1, false, 8>(c, a, s.b * c.n_kv_heads + blockIdx.y, s.split, 0, s.tokens, nullptr, smem, &s_last, none);
+  attend_block<WAVES, 1, false, 8>(c, a, s.b * c.n_kv_heads + blockIdx.x, s.split, 0, s.tokens, nullptr, smem, &s_last, none);
 }
 
 __global__ void zero_u32_kernel(uint32_t* p, int n) {
@@ -83,28 +83,23 @@ AttendPlan plan_attend(const CacheView& c, int row_len, bool gather) {
   // softmax step of the unit), 22.1 against 22.3 us without and 24.6 against 23.8 us with the token
   // append at the benchmark shape, and is not used.
   p.n_csplit = 1;
-  p.dense_aim = p.dense_limit = 0;
-  // Short rows and large batches keep the division by capacity as well: deriving the other one costs every
-  // workgroup its time, more than 64 sequences at a time several times over, and a row of a few dozen
-  // pages is one workgroup's work in any case (60 sequences of 300 tokens 15.6 against 16.8 us, 96 of 1000
-  // 61.5 against 67.9, 512 of 500 166 against 215; but 128 of 2000 178 against 163, 108 against 68.5
-  // with unequal lengths).
-  const bool divide = (c.batch <= kWave && row_len >= 48) || (c.batch <= 2 * kWave && row_len >= 100);
+  p.dense = {0, 0, 0};
+  // Short rows keep the division by capacity as well: deriving the other one costs every workgroup its time, and
+  // a row of a few dozen pages is one workgroup's work in any case (60 sequences of 300 tokens 15.6 against
+  // 16.8 us, 96 of 1000 61.5 against 67.9; but 128 of 2000 178 against 163, 108 against 68.5 with unequal
+  // lengths).  So do batches beyond two sequences per lane, whose workgroups would read and add up all
+  // lengths block by block, several times over (512 of 500 166 against 215).  That is what 129 unequal
+  // ones of up to 8192 tokens pay: 443 us, where 128 take 226.
+  const bool divide = (c.batch <= kWave && row_len >= 48) || (c.batch <= kDenseMaxBatch && row_len >= 100);
   if (!gather && divide && (int64_t)units * ((row_len + 2 * waves - 1) / (2 * waves)) > kComputeUnits) {
-    // The workgroups divide the pages that are there between them (dense_share), so the launch only
-    // has to hold as many as that division can make: the aim, or two per sequence.  Below this size
+    // The workgroups divide the pages that are there between them (dense_share).  Below this size
     // every workgroup has the smallest share whatever the lengths are and all of them run at once:
     // nothing to balance, and the division would only cost its time (10.2 against 10.8 us for four
-    // sequences of 1000 tokens, 10.4 against 11.1 us for one of 2048 over token-major V).
-    const int64_t shares = (int64_t)c.batch * row_len / kDensePages;
-    const int64_t most = (int64_t)c.batch * (row_len / (2 * waves) + 2);  // a pair per wavefront is the least
+    // sequences of 1000 tokens, 10.4 against 11.1 us for one of 2048 over token-major V).  Just above it
+    // that holds for full sequences (10 of 1500 tokens 15.1 against 15.7), but not for unequal ones
+    // (12.8 against 10.6).
     const int slots = kComputeUnits * 8 / waves;  // the chip holds two wavefronts per SIMD of these kernels (registers)
-    p.dense_aim = slots / c.n_kv_heads > 1 ? slots / c.n_kv_heads : 1;
-    int64_t limit = p.dense_aim;
-    if (shares >= kDenseRounds * limit) limit = shares < kMaxWorkgroups / c.n_kv_heads ? shares : kMaxWorkgroups / c.n_kv_heads;
-    if (limit > most) limit = most;
-    if (limit < 2 * c.batch) limit = 2 * c.batch;
-    p.dense_limit = (int)limit;
+    p.dense = dense_grid(c.batch, c.n_kv_heads, row_len, slots, 2 * waves);
   }
   if (gather && !c.v_token_major && waves == 8 && (int64_t)units * n_wg * 2 <= kComputeUnits) p.n_csplit = 2;
   int chunk = (row_len + n_wg - 1) / n_wg;
@@ -127,7 +122,7 @@ AttendPlan plan_attend(const CacheView& c, int row_len, bool gather) {
   p.counter_off = off;  // always first: the part rocketkv_workspace_init clears
   off += ROCKETKV_WS_HEADER_BYTES;
   p.partial_off = off;
-  const size_t parts = p.dense_limit ? (size_t)p.dense_limit * c.n_kv_heads : (size_t)units * p.n_csplit * p.n_split;
+  const size_t parts = p.dense.limit ? (size_t)p.dense.limit * c.n_kv_heads : (size_t)units * p.n_csplit * p.n_split;
   off += (parts * c.group * kPartialStride * sizeof(float) + 255) / 256 * 256;
   p.total_bytes = off;
   return p;
@@ -166,13 +161,12 @@ hipError_t launch_attend(const CacheView& c, const bf16_t* q, const int32_t* pag
     return hipGetLastError();
   }
   const size_t smem = (size_t)plan.waves * c.group * (kHeadDim + 2) * sizeof(float);
-  if (plan.dense_limit) {
-    const DenseGrid dg = {plan.dense_aim, plan.dense_limit};
-    const dim3 dgrid(plan.dense_limit, c.n_kv_heads);
+  if (plan.dense.limit) {
+    const dim3 dgrid(c.n_kv_heads, plan.dense.limit);
     if (plan.waves == 8)
-      hipLaunchKernelGGL(dense_mfma_kernel<8>, dgrid, dim3(8 * kWave), smem, st, c, a, dg);
+      hipLaunchKernelGGL(dense_mfma_kernel<8>, dgrid, dim3(8 * kWave), smem, st, c, a, plan.dense);
     else
-      hipLaunchKernelGGL(dense_mfma_kernel<4>, dgrid, dim3(4 * kWave), smem, st, c, a, dg);
+      hipLaunchKernelGGL(dense_mfma_kernel<4>, dgrid, dim3(4 * kWave), smem, st, c, a, plan.dense);
     return hipGetLastError();
   }
   const dim3 grid(plan.n_split, units);

@@ -74,25 +74,14 @@ struct AttendArgs {
   int n_csplit;          // workgroups a unit's output channels are divided between (1 or 2)
 };
 
-// The Full-KV baseline divides the pages the sequences really hold, which only the device knows: every
-// workgroup derives the same division from the lengths.  Workgroups aim at equal shares of `c` pages;
-// a sequence of P pages gets max(1, ceil(P / c)) of them per KV head and divides its pages evenly
-// between those, so a workgroup works for one unit only and never meets another one's.  What bounds the
-// kernel is HBM, as long as every compute unit has a share of the stream to the end.  Dividing the
-// capacity instead left five conversations of 1500 to 30011 tokens on 415 unequal workgroups over 256
-// compute units, and as many again that had come only to merge nothing: 86 us a layer for 272 MB, 47.6
-// with the division by length (5.7 TB/s); sixteen of up to 30000 tokens 214 -> 91 us.
-// A launch of many rounds runs in shares of 256 pages: 16 x 32768 tokens take 316 us with them
-// (6.8 TB/s), 333 in shares of 128, 329 of 192, 326 of 384, and 325 in one round of equal shares.  One
-// round is the better form up to four (90.7 against 97.5 us for the sixteen conversations at three).
-constexpr int kDensePages = 256;  // pages per workgroup of a launch that takes several rounds over the chip
-constexpr int kDenseRounds = 4;   // ... which it does from that many on; below, one round of equal shares
-
-struct DenseGrid {  // per KV head
-  int aim;    // workgroups of one round over the chip
-  int limit;  // workgroups launched, at least 2 * batch
-};
-
+// The Full-KV baseline divides the pages the sequences really hold (dense_division.h), which only the
+// device knows: every workgroup derives the same division from the lengths.  Dividing the capacity
+// instead left five conversations of 1500 to 30011 tokens on 415 unequal workgroups over 256 compute
+// units, and as many again that had come only to merge nothing: 86 us a layer for 272 MB, 47.6 with the
+// division by length (5.7 TB/s); sixteen of up to 30000 tokens 214 -> 91 us.
+// The workgroups of all KV heads at one share of a sequence follow each other in the grid: a page's
+// heads are neighbours in memory, and successive workgroups go to different XCDs whatever the number of
+// shares is (head by head, 5 sequences of 6000 tokens over 40 KV heads took 164 us, now 98).
 struct DenseShare {
   int b;        // the sequence; < 0: nothing to do
   int split;    // which of its workgroups this is (per KV head) ...
@@ -111,81 +100,54 @@ __device__ __forceinline__ DenseShare dense_share(const CacheView& c, const Dens
     return n < 0 ? 0 : (n > cap ? cap : n);
   };
   const auto pages_in = [](int n) { return (n + kAttnPage - 1) / kAttnPage; };
-  if (B == 1) {  // nothing to weigh: in scalar arithmetic, no lane moves
+  const auto rcp = [](float x) { return __builtin_amdgcn_rcpf(x); };
+  const auto last_lane = [](int x) { return __builtin_amdgcn_readlane(x, kWave - 1); };
+  const auto scan = [](int x) { return (int)wave_incl_scan((uint32_t)x); };
+  const DenseShare none = {-1, 0, 1, 0, 0};
+  if (B == 1) {  // in scalar arithmetic, no lane moves
     const int n = tokens_of(0), P = pages_in(n);
-    int aim = P / kDensePages;
-    if (aim < kDenseRounds * grid.aim) aim = grid.aim;
-    const int n_split = max(1, min(min(aim, grid.limit), (P + least - 1) / least));
+    const int last = dense_last(grid, 1, P, least);
+    const auto own = [&](float rc) { return dense_shares(P, rc); };
+    const int n_split = own(dense_rate(grid, 1, P, last, [&] { return (float)P; }, least, rcp, own));
     return {wg < n_split ? 0 : -1, wg, n_split, 0, n};
   }
-  const auto last_lane = [](uint32_t x) { return __builtin_amdgcn_readlane((int)x, kWave - 1); };
-  // workgroups to aim at for T pages: one round, or as many as shares of kDensePages make
-  const auto aim_for = [&](int T) {
-    int aim = T / kDensePages;
-    if (aim < kDenseRounds * grid.aim) aim = grid.aim;
-    return max(min(aim, grid.limit), B);
-  };
-  // Workgroups of a sequence of P pages for shares of c = 1 / rc pages.  Whatever the rounding makes of
-  // the quotient, it is the same wherever it is formed, and any number of workgroups divides the pages.
-  const auto shares = [](int P, float rc) { return max(1, (int)ceilf((float)P * rc)); };
-  // just below 1 / c, so that shares(k c) is k: the sum over the batch is less than T / c + B
-  const auto rcp_of = [](float cc) { return __builtin_amdgcn_rcpf(cc) * 0.999998f; };
-  const auto c_for = [&](int T, int w) { return (float)T * __builtin_amdgcn_rcpf((float)w); };
-  // The smallest c whose count of workgroups fits the aim lies between T / aim and T / (aim - B); where
-  // the aim is B (more units than workgroups fit at once) c = T / B, which makes at most 2 B.
-  const auto narrow = [&](int T, int aim, float c_lo, const auto& count) {
-    float c_hi = c_for(T, aim - B);
-#pragma unroll 1
-    for (int i = 0; i < 4; ++i) {
-      const float mid = 0.5f * (c_lo + c_hi);
-      if (count(rcp_of(mid)) > aim) c_lo = mid; else c_hi = mid;
-    }
-    return rcp_of(c_hi);
-  };
-  const auto found = [&](int b0, int n, int w, int end, unsigned long long mine) -> DenseShare {
+  const auto found = [&](int b0, int n, int w, int end) -> DenseShare {
+    const unsigned long long mine = __ballot(wg < end);
+    if (mine == 0ull) return none;
     const int src = __ffsll(mine) - 1;
     const int n_split = __builtin_amdgcn_readlane(w, src);
     const int first = __builtin_amdgcn_readlane(end, src) - n_split;
     return {b0 + src, wg - first, n_split, first, __builtin_amdgcn_readlane(n, src)};
   };
+  const int n0 = tokens_of(lane), P0 = pages_in(n0);
+  const auto own = [&](int b, int P, float rc) { return b < B ? dense_shares(P, rc) : 0; };
   if (B <= kWave) {  // a sequence per lane
-    const int n = tokens_of(lane), P = pages_in(n);
-    const int T = last_lane(wave_incl_scan((uint32_t)P));
-    const int aim = aim_for(T);
-    const float c_lo = fmaxf(c_for(T, aim), (float)least);
-    const auto own = [&](float rc) { return lane < B ? shares(P, rc) : 0; };
-    int w = own(rcp_of(c_lo));
-    int end = (int)wave_incl_scan((uint32_t)w);
-    if (aim > B && last_lane((uint32_t)end) > aim) {
-      w = own(narrow(T, aim, c_lo, [&](float rc) { return last_lane(wave_incl_scan((uint32_t)own(rc))); }));
-      end = (int)wave_incl_scan((uint32_t)w);
-    }
-    const unsigned long long mine = __ballot(wg < end);
-    if (mine == 0ull) return {-1, 0, 1, 0, 0};
-    return found(0, n, w, end, mine);
+    const int T = last_lane(scan(P0)), last = dense_last(grid, B, T, least);
+    if (wg >= dense_most(grid, B, last)) return none;
+    int w = 0, end = 0;
+    float seen = -1.f;
+    const auto count = [&](float rc) {
+      seen = rc;
+      w = own(lane, P0, rc);
+      end = scan(w);
+      return last_lane(end);
+    };
+    const float rc = dense_rate(grid, B, T, last, [&] { return wave_max_f32((float)P0); }, least, rcp, count);
+    if (rc != seen) count(rc);
+    return found(0, n0, w, end);
   }
-  // 64 at a time
-  int T = 0;
-  for (int b0 = 0; b0 < B; b0 += kWave) T += last_lane(wave_incl_scan((uint32_t)pages_in(tokens_of(b0 + lane))));
-  const auto own = [&](int b0, float rc) { return b0 + lane < B ? shares(pages_in(tokens_of(b0 + lane)), rc) : 0; };
-  const auto count = [&](float rc) {
-    int w = 0;
-    for (int b0 = 0; b0 < B; b0 += kWave) w += last_lane(wave_incl_scan((uint32_t)own(b0, rc)));
-    return w;
-  };
-  const int aim = aim_for(T);
-  const float c_lo = fmaxf(c_for(T, aim), (float)least);
-  float rc = rcp_of(c_lo);
-  if (aim > B && count(rc) > aim) rc = narrow(T, aim, c_lo, count);
-  int base = 0;  // workgroups of the sequences before this block of 64
-  for (int b0 = 0; b0 < B; b0 += kWave) {
-    const int w = own(b0, rc);
-    const int end = base + (int)wave_incl_scan((uint32_t)w);
-    const unsigned long long mine = __ballot(wg < end);
-    if (mine != 0ull) return found(b0, tokens_of(b0 + lane), w, end, mine);
-    base = last_lane((uint32_t)end);
-  }
-  return {-1, 0, 1, 0, 0};
+  static_assert(kDenseMaxBatch == 2 * kWave, "two sequences per lane");
+  const int n1 = tokens_of(lane + kWave), P1 = pages_in(n1);
+  const int T = last_lane(scan(P0 + P1)), last = dense_last(grid, B, T, least);
+  if (wg >= dense_most(grid, B, last)) return none;
+  const float rc = dense_rate(grid, B, T, last, [&] { return wave_max_f32((float)max(P0, P1)); }, least, rcp, [&](float r) {
+    return last_lane(scan(own(lane, P0, r) + own(lane + kWave, P1, r)));
+  });
+  const int w0 = own(lane, P0, rc), end0 = scan(w0);
+  const DenseShare s = found(0, n0, w0, end0);
+  if (s.b >= 0) return s;
+  const int w1 = own(lane + kWave, P1, rc);
+  return found(kWave, n1, w1, last_lane(end0) + scan(w1));
 }
 
 // the arguments of the attention routine for that share of head `g`

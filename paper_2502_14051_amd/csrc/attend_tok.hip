@@ -25,14 +25,14 @@ __global__ __launch_bounds__(WAVES* kWave) __attribute__((amdgpu_waves_per_eu(2)
 void dense_tokens_kernel(CacheView c, AttendArgs a, TokenRun t, DenseGrid grid) {
   extern __shared__ float smem[];
   __shared__ int s_last;
-  const DenseShare s = dense_share(c, grid, 2 * WAVES, blockIdx.x);
+  const DenseShare s = dense_share(c, grid, 2 * WAVES, blockIdx.y);
   if (s.b < 0) return;
-  dense_args(a, c, grid, s, blockIdx.y, WAVES);
+  dense_args(a, c, grid, s, blockIdx.x, WAVES);
   t.tokens = a.row_len * kAttnPage;
   a.chunk *= kAttnPage;
   a.per_wave *= kAttnPage;
   const TokenPatch none = {-1, nullptr, nullptr};
-  attend_tokens_block<WAVES, false>(c, a, t, s.b * c.n_kv_heads + blockIdx.y, s.split, s.tokens, nullptr, smem, &s_last,
+  attend_tokens_block<WAVES, false>(c, a, t, s.b * c.n_kv_heads + blockIdx.x, s.split, s.tokens, nullptr, smem, &s_last,
                                     none);
 }
 
@@ -60,13 +60,12 @@ hipError_t launch_attend_tokens(const CacheView& c, const bf16_t* q, const int32
   t.n_logical = lv ? lv->n_indexed : nullptr;
   t.logical_pages_cap = lv ? lv->pages_cap : 0;
   const size_t smem = (size_t)plan.waves * c.group * (kHeadDim + 2) * sizeof(float);
-  if (plan.dense_limit) {
-    const DenseGrid dg = {plan.dense_aim, plan.dense_limit};
-    const dim3 dgrid(plan.dense_limit, c.n_kv_heads);
+  if (plan.dense.limit) {
+    const dim3 dgrid(c.n_kv_heads, plan.dense.limit);
     if (plan.waves == 8)
-      hipLaunchKernelGGL(dense_tokens_kernel<8>, dgrid, dim3(8 * kWave), smem, st, c, a, t, dg);
+      hipLaunchKernelGGL(dense_tokens_kernel<8>, dgrid, dim3(8 * kWave), smem, st, c, a, t, plan.dense);
     else
-      hipLaunchKernelGGL(dense_tokens_kernel<4>, dgrid, dim3(4 * kWave), smem, st, c, a, t, dg);
+      hipLaunchKernelGGL(dense_tokens_kernel<4>, dgrid, dim3(4 * kWave), smem, st, c, a, t, plan.dense);
     return hipGetLastError();
   }
   const dim3 grid(plan.n_split, units);

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dense_division.h"
 #include "rocketkv.h"
 
 namespace rkv {
@@ -216,8 +217,7 @@ struct AttendPlan {
   int n_split;        // workgroups a unit's page list is divided between (each of the n_csplit shares)
   int chunk;          // page-list entries per workgroup
   int per_wave;       // page-list entries per wavefront (even)
-  int dense_aim;      // the Full-KV baseline, workgroups per KV head: of one round over the chip ...
-  int dense_limit;    // ... and launched (0: a page list drives the launch)
+  DenseGrid dense;    // the Full-KV baseline (limit 0: a page list drives the launch, or the capacity is divided)
   size_t partial_off; // workspace offsets (bytes)
   size_t counter_off;
   size_t total_bytes;
