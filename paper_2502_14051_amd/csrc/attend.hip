@@ -3,6 +3,7 @@
 // page list in global memory (or the identity list), plus the launch geometry shared with the
 // fused decode kernel.
 #include "attend_core.h"
+#include "list_division.h"
 
 namespace rkv {
 
@@ -102,22 +103,12 @@ AttendPlan plan_attend(const CacheView& c, int row_len, bool gather) {
     p.dense = dense_grid(c.batch, c.n_kv_heads, row_len, slots, 2 * waves);
   }
   if (gather && !c.v_token_major && waves == 8 && (int64_t)units * n_wg * 2 <= kComputeUnits) p.n_csplit = 2;
-  int chunk = (row_len + n_wg - 1) / n_wg;
-  int per_wave = ((chunk + waves - 1) / waves + 1) / 2 * 2;  // whole pairs
-  chunk = per_wave * waves;
-  p.n_split = (row_len + chunk - 1) / chunk;
-  if (p.n_split < 1) p.n_split = 1;
-  // Where wavefronts walk more than one pair, the same workgroups take equal shares (48 entries: 24 and
-  // 24, not 32 and 16; 13 ragged sequences at a budget of 777: 21.9 -> 21.4 us a layer, 4 x 32 heads at
-  // 700: 22.2 -> 21.3).  With one pair each there is no round to save, and a short share that is done
-  // early costs nothing (19 entries as 16 and 3 rather than 10 and 9: 17.0 against 17.3 us).
-  if (per_wave > 2) {
-    chunk = ((row_len + p.n_split - 1) / p.n_split + 1) / 2 * 2;
-    per_wave = ((chunk + waves - 1) / waves + 1) / 2 * 2;
-    p.n_split = (row_len + chunk - 1) / chunk;
-  }
-  p.chunk = chunk;
-  p.per_wave = per_wave;
+  const ListShares shares = list_shares(row_len, n_wg, waves, [&](int n) {
+    return (int64_t)units * p.n_csplit * n <= kComputeUnits * 8 / waves;
+  });
+  p.n_split = shares.n_split;
+  p.chunk = shares.chunk;
+  p.per_wave = shares.per_wave;
   size_t off = 0;
   p.counter_off = off;  // always first: the part rocketkv_workspace_init clears
   off += ROCKETKV_WS_HEADER_BYTES;
