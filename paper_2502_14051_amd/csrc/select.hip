@@ -24,8 +24,8 @@ __global__ __launch_bounds__(kSelThreads) void hsa_select_kernel(CacheView c, Se
 // NT threads score NT/4 eight-page runs.  Two shapes are launched:
 //   <256, APPEND, false>  small workgroups for the score launch of rocketkv_hsa_select, which has no
 //                         workspace for counters and leaves the top-k to hsa_pick_kernel;
-//   <1024, APPEND, true>  the decode step: a (sequence, KV head) is covered by one to four workgroups of
-//                         a compute unit's worth of threads; the scores go out with device-scope stores,
+//   <1024, APPEND, true>  the decode step: a (sequence, KV head) is covered by one to sixteen workgroups of
+//                         a compute unit's worth of threads (launch_hsa_select_split); the scores go out with device-scope stores,
 //                         each workgroup reports to the unit's counter, and the last one to report
 //                         picks the top-k right there, a launch boundary and a round trip earlier.
 //
@@ -165,12 +165,14 @@ hipError_t launch_hsa_select(const CacheView& c, const SelectArgs& a, hipStream_
   return hipGetLastError();
 }
 
-// A unit's summary rows go to as many workgroups as leave one per compute unit, up to eight (their
-// reports queue up at the unit's counter: 16 are slower again) and 16 runs each: a compute unit draws
-// some 30 GB/s of cold rows, so with few units the rows are what the launch waits for.  9675 tokens in
-// pages of 3 at 81 channels, us per layer-step with two workgroups per unit and now: one sequence
-// 30.2 / 25.4 (four per unit 26.8, sixteen 25.9), two 31.1 / 27.0, eight 35.7 / 32.8.
-constexpr int kMaxScoreSplit = 8;
+// A unit's summary rows go to as many workgroups as leave one per compute unit with 16 runs each, doubling
+// from the fewest that can hold them until there are eight or more (their reports queue up at the unit's
+// counter): a compute unit draws some 30 GB/s of cold rows, so with few units the rows are what the launch
+// waits for.  9675 tokens in pages of 3 at 81 channels, us per layer-step with two workgroups per unit and
+// now: one sequence 30.2 / 25.4 (four per unit 26.8, sixteen 25.9), two 31.1 / 27.0, eight 35.7 / 32.8.  The
+// last doubling may go past eight: one sequence of 4200 pages at 128 channels takes 34.2 with three, 30.3
+// with six, 28.8 with twelve; of 10000 pages 40.5 with five, 38.9 with eight, 35.6 with ten.
+constexpr int kScoreSplit = 8;
 constexpr int kMinScoreRuns = 16;
 
 hipError_t launch_hsa_select_split(const CacheView& c, const SelectArgs& a, const AppendArgs& ap,
@@ -180,7 +182,7 @@ hipError_t launch_hsa_select_split(const CacheView& c, const SelectArgs& a, cons
   if (unit_counters) {
     // with counters to meet at: scores and top-k in one launch
     int per_unit = (runs + kPickThreads / 4 - 1) / (kPickThreads / 4);
-    while (per_unit < kMaxScoreSplit && 2 * per_unit * units <= 256 && runs >= 2 * per_unit * kMinScoreRuns) per_unit *= 2;
+    while (per_unit < kScoreSplit && 2 * per_unit * units <= 256 && runs >= 2 * per_unit * kMinScoreRuns) per_unit *= 2;
     const dim3 grid(per_unit, units);
     if (ap.k_new)
       hipLaunchKernelGGL((hsa_score_kernel<kPickThreads, true, true>), grid, dim3(kPickThreads), 0, st, c, a, ap,
