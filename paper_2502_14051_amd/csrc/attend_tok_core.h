@@ -143,7 +143,7 @@ __device__ __forceinline__ void attend_tokens_block(const CacheView& c, const At
   const int cap_pages = INDEXED ? t.logical_pages_cap : c.pages_cap;
   if (n > cap_pages * ps) n = cap_pages * ps;
 
-  // this wave's share of the token slots (chunk and per_wave are multiples of 32).  The plan is laid
+  // this wave's share of the token slots (chunk is a multiple of 16, per_wave of 32).  The plan is laid
   // out on whole 16-slot entries; the last wavefront of the last workgroup also takes the few slots
   // left over when pages do not fill the last entry, rather than a workgroup being launched for them.
   const int e_begin = split * a.chunk;
@@ -214,8 +214,9 @@ __device__ __forceinline__ void attend_tokens_block(const CacheView& c, const At
     const int cnt = min(kWave, we - base);
     for (int i = 0; i * 32 < cnt; ++i) {
       // None of the group holds a token (the end of a list shorter than its row): nothing to read, and with
-      // pages that do not divide the share a round trip less for its last wavefront.  (Only where the list
-      // comes from memory: in the fused kernels the test costs what it gains.)
+      // pages that do not divide the share a round trip less for its last wavefront (16 sequences of 4000
+      // tokens in pages of 3, budget 1024, without append: 32.2 -> 31.6 us).  Not through the index or with
+      // the append: there the test costs what it gains.
       if (!INDEXED && !PATCH && (uint32_t)(live >> (32 * i)) == 0u) continue;
       u32x4 kf[2][4], vr[2][4];
       const bf16_t* vt[2];

@@ -923,10 +923,12 @@ SnapPlan plan_snapkv(const CacheView& src, int window, int keep) {
   SnapPlan p;
   const size_t units = (size_t)src.batch * src.n_kv_heads;
   const int NC = src.group * window;
-  // Pages per workgroup in the score passes.  Every wavefront loads the whole observation-window
-  // query block before its first page, so long chunks amortise that; short ones keep the chip full
-  // when there are few (sequence, KV head) units.  Aim for 512 workgroups or more (two per compute
-  // unit): eight units of a 131072-token prompt ran a third slower in chunks of 32 pages than of 128.
+  // Pages per workgroup in the score passes.  A workgroup fetches its query block before its first page,
+  // which long chunks amortise; short ones keep the chip full when there are few (sequence, KV head)
+  // units.  Doubled while there are more than 512 workgroups, two per compute unit: the whole call over
+  // eight units of 65536 tokens takes 92 us so, 101 at a bound of 256 and 99 at 1024, 64 units of 8192 172,
+  // 171 and 181.  The shortest chunk dates from when every wavefront fetched the query block for itself; now
+  // chunks of 16 are faster where units are few (eight of 4096 tokens 45 against 52 us, of 16384 56 and 57).
   static_assert(kSnapMaxChunkPages / 2 <= kSnapMaxIters, "a wavefront's share of the longest chunk must fit its page-offset lanes");
   int chunk_pages = 32;
   while (chunk_pages < kSnapMaxChunkPages && units * ((src.pages_cap + chunk_pages - 1) / chunk_pages) > 512) chunk_pages *= 2;
