@@ -21,16 +21,10 @@
 namespace rkv {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kSnapColBlocks = 8;    // 16-column blocks per wavefront (128 softmax rows)
 constexpr float kLog2eS = 1.4426950408889634f;
 constexpr float kNegBigS = -1.0e30f;
-
-union FragS {
-  uint4 u;
-  bf16x8 v;
-};
 
 constexpr int kCountStride = 64;  // uint32 between the run counters of two units
 
@@ -53,33 +47,13 @@ struct SnapArgs {
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// sum over the 16 lanes of a DPP row (the lanes that hold the 16 columns of one token group); every
-// lane of the row ends up with the total
-__device__ __forceinline__ float row16_sum(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // quad_perm 2,3,0,1
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true));  // row_half_mirror
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, true));  // row_mirror
-  return v;
-}
-
 // max of three without the input canonicalisation fmaxf() brings along (three extra instructions
-// per call here); the inputs are matrix-core outputs and running maxima, never signalling NaNs
+// per call here); the inputs are matrix-core outputs and running maxima, never signalling NaNs.  A matrix-core output
+// must have been read by an instruction of the compiler's before (see the one use).
 __device__ __forceinline__ float max3_raw(float x, float y, float w) {
   float d;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(x), "v"(y), "v"(w));
   return d;
-}
-
-__device__ __forceinline__ float max2_raw(float x, float y) {
-  float d;
-  asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(x), "v"(y));
-  return d;
-}
-
-__device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
-  return ((int64_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
-         (uint32_t)__builtin_amdgcn_readlane((int)(v & 0xffffffff), l);
 }
 
 // 16 bytes per lane from `src` straight to LDS: lane l's land 16 l bytes behind the wavefront's `dst`
@@ -91,20 +65,71 @@ __device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
 #endif
 }
 
-constexpr int kSnapMaxIters = 2 * kWave;  // pages one wavefront walks in a chunk, at most
-constexpr int kSnapRing = 3;              // key tiles a wavefront keeps in flight (4 KiB of LDS each)
-constexpr size_t kSnapRingBytes = (size_t)4 * kSnapRing * 4 * kWave * 16;  // four wavefronts
-constexpr int kSnapMaxChunkPages = 128;  // pages per workgroup; pass 2 stages their votes in LDS (8 KiB per column group)
+constexpr int kSnapCols = 128;            // softmax rows (columns of the products) per wavefront, in blocks of 32
+constexpr int kSnapMaxPairs = kWave;      // page pairs one wavefront walks, at most: a lane each
+constexpr int kSnapSegPairs = 8;          // page pairs between two write-outs of the votes
+constexpr int kSnapMaxChunkPages = 512;   // pages per workgroup: four wavefronts' pairs
+constexpr int kRowsBytes = 4 * kHeadDim * (int)sizeof(bf16_t) + 16;  // four rows in LDS, and what shifts the next four's banks
+constexpr int kTileBytes = 4 * kRowsBytes, kSlotBytes = 2 * kTileBytes;
+constexpr int kRingBytes = 4 * 2 * kSlotBytes;
+constexpr int kSnapStatBytes = 2 * 4 * kSnapCols * (int)sizeof(float);
+constexpr int kSnapVoteBytes = 2 * kSnapSegPairs * 4 * 2 * kAttnPage * (int)sizeof(float);
 
-// QD: groups of four column blocks every wavefront works through (2 when some wavefront owns more
-// than four blocks with real softmax rows; blocks without any hold zero queries and are discarded).
-template <bool PASS2, int QD>
+// Four bytes to LDS, in assembly: in front of a store it can see the compiler waits for every load to LDS in flight,
+// which it cannot tell apart from the store's target.
+__device__ __forceinline__ void lds_store(float* dst, float x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)dst;
+  asm volatile("ds_write_b32 %0, %1" ::"v"(at), "v"(x) : "memory");
+#endif
+}
+
+// A lane's values x[0 .. 15], each to be summed over the 32 lanes of its half wavefront: lane l is left with the
+// total of x[8 (l / 16 % 2) + 4 (l / 8 % 2) + 2 (l / 4 % 2) + l / 2 % 2], which the lanes below and above it in a
+// pair share.  Every step halves the values a lane holds, so that 38 instructions do it; the order of the
+// additions is fixed.
+__device__ __forceinline__ float half_wave_sums(float (&x)[16], int lane) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {  // rows of 16 lanes: an even row keeps x[j], an odd one x[j + 8]
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[j]), __float_as_uint(x[j + 8]), false, false);
+    x[j] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+  const auto step = [&](auto ctrl, int bit, int n) {  // the lane `ctrl` names differs in `bit` (and covers the rest later)
+    const bool up = (lane & bit) != 0;
+#pragma unroll
+    for (int j = 0; j < n; ++j) {
+      const float keep = up ? x[j + n] : x[j], give = up ? x[j] : x[j + n];
+      x[j] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), decltype(ctrl)::value, 0xf, 0xf, true));
+    }
+  };
+  step(std::integral_constant<int, 0x128>{}, 8, 4);  // row_ror:8
+  step(std::integral_constant<int, 0x141>{}, 4, 2);  // row_half_mirror
+  step(std::integral_constant<int, 0x4E>{}, 2, 1);   // quad_perm 2,3,0,1
+  return x[0] + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x[0]), 0xB1, 0xf, 0xf, true));  // quad_perm 1,0,3,2
+}
+
+// NB: blocks of 32 softmax rows every wavefront works through (blocks without any hold zero queries and are
+// discarded).  A wavefront takes 32 tokens, a pair of neighbouring pages, at a time, against one block after the
+// other: a 32 x 32 product leaves a lane one softmax row and sixteen of the tokens.
+//
+// What bounds it: vector issue and HBM, nearly equally, and under sustained load the clock.  With 16 x 16 products
+// a lane held four tokens of a softmax row, so that a maximum, a rescale and their exponential were paid for every
+// four logits, and a product kept the vector port busy for half of its 16 cycles; with 32 x 32 ones it is sixteen
+// logits, and a product covers twice the work in the same issue time.  One workgroup per slot of the chip walks all of
+// its unit's pages it can (up to 512), so that the queries are fetched once and not in each of four rounds.
+// 16 x 32768 tokens over 8 KV heads, the two passes: 190 + 235 -> 170 + 182 us (bare stream of the same keys: 161
+// each; in a loop of layers, where the clock drops, 225 + 265 -> 209 + 222); 1 x 131072: 52 + 58 -> 49 + 48.
+template <bool PASS2, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void snap_score_kernel(CacheView c, SnapArgs a) {
-  __shared__ float sM[4][kSnapColBlocks * 16], sZ[4][kSnapColBlocks * 16];
+  typedef uint32_t ring_u32x4 __attribute__((ext_vector_type(4)));
+  // Two pairs of key tiles per wavefront, then in pass 1 maxima and sums by wavefront, in pass 2 the votes of two
+  // segments, [2][column groups][tokens].
+  extern __shared__ __align__(16) unsigned char s_ring[];
+  float* s_out = reinterpret_cast<float*>(s_ring + kRingBytes);
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // scalar: page indices stay in SGPRs
-  const int hn = lane % 16, kg = lane / 16;
+  const int hn = lane % 16, half = lane / 32;
   const int unit = blockIdx.y, chunk = blockIdx.x;
   const int b = unit / c.n_kv_heads, g = unit % c.n_kv_heads;
   const int S = c.seq_lens[b];
@@ -115,258 +140,273 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
   const int p_limit = PASS2 ? (L + kAttnPage - 1) / kAttnPage : (S + kAttnPage - 1) / kAttnPage;
   const int p_end = min(p_begin + a.chunk_pages, p_limit);
   if (p_begin >= p_end) return;  // a chunk beyond the prompt: its statistics are never read
-  const int n_it = (p_end - p_begin + npw - 1) / npw;  // <= kSnapMaxIters (host)
+  const int n_pairs = (p_end - p_begin + 2 * npw - 1) / (2 * npw);  // <= kSnapMaxPairs (host)
+  const auto first_page = [&](int it) { return p_begin + 2 * (it * npw + pw); };
 
-  // Where this wavefront's pages live: lane i looks up iterations i and i + 64 once, up front, and
-  // the loop hands the tile offsets out by readlane, so it contains no table lookups and no waits
-  // on them.  -1 marks an absent page.
-  int64_t off_lo = -1, off_hi = -1;
-  {
-    const int p0 = p_begin + lane * npw + pw, p1 = p0 + kWave * npw;
-    if (lane < n_it && p0 < p_end) {
-      const int64_t pp = phys_page(c, b, p0);
-      if (pp >= 0) off_lo = pp * c.stride_page;
-    }
-    if (lane + kWave < n_it && p1 < p_end) {
-      const int64_t pp = phys_page(c, b, p1);
-      if (pp >= 0) off_hi = pp * c.stride_page;
-    }
+  // Where this wavefront's pages live: lane i looks up pair i once, up front, and the loop hands the
+  // pages out by readlane, so it contains no table lookups and no waits on them.  -1: absent.
+  int pp0 = -1, pp1 = -1;
+  if (lane < n_pairs) {
+    const int p = first_page(lane);
+    if (p < p_end) pp0 = (int)phys_page(c, b, p);
+    if (p + 1 < p_end) pp1 = (int)phys_page(c, b, p + 1);
   }
 
-  constexpr int NCB = 4 * QD;
-  FragS qf[NCB][4];
-  int limit[NCB];
-  float M2[NCB], invZ[NCB];
-  float m[NCB], z[NCB];
+  bf16x8 qf[NB][8];
+  float M2[NB], invZ[NB];
+  float m[NB], z[NB];
 #pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) { m[cb] = kNegBigS; z[cb] = 0.f; }
+  for (int cb = 0; cb < NB; ++cb) { m[cb] = kNegBigS; z[cb] = 0.f; }
   const float sc = kLog2eS * 0.08838834764831845f;
-  const int64_t head_off = (int64_t)g * c.stride_head;
+  const char* k_head = reinterpret_cast<const char*>(c.k_pool + (int64_t)g * c.stride_head);
 
-  // Key tiles travel through a ring of kSnapRing slots of LDS per wavefront, filled by loads that
-  // write LDS directly (no registers are held for tiles in flight, so three of them fit where two
-  // register buffers used to): the tile for iteration it + kSnapRing is requested as soon as the
-  // products of iteration it have consumed the slot.  An absent or out-of-range page reads tile 0
-  // of the pool and is masked below; those loads are issued all the same, which keeps the number
-  // of loads younger than the tile being waited for constant.
-  typedef uint32_t ring_u32x4 __attribute__((ext_vector_type(4)));
-  extern __shared__ __align__(16) unsigned char snap_dyn[];
-  ring_u32x4* ring = reinterpret_cast<ring_u32x4*>(snap_dyn) + wave * (kSnapRing * 4 * kWave);
-  float* s_votes = reinterpret_cast<float*>(snap_dyn + kSnapRingBytes);  // pass 2: [column group][chunk_pages][16]
-  const auto tile_off = [&](int it) -> int64_t {  // `it` is wave-uniform; branch-free
-    const int l = it & (kWave - 1);
-    const int64_t lo = readlane64(off_lo, l), hi = readlane64(off_hi, l);
-    return it >= n_it ? -1 : (it < kWave ? lo : hi);
+  // Key tiles travel through two slots of LDS per wavefront, a pair of pages each, filled by loads that write LDS
+  // directly (no registers are held for tiles in flight): the pair for iteration it + 2 is requested as soon
+  // as iteration it has its own in registers.  An absent or out-of-range page reads tile 0 of the pool
+  // and is masked below; those loads are issued all the same, which keeps the number of loads younger
+  // than the pair being waited for constant.
+  unsigned char* ring = s_ring + wave * 2 * kSlotBytes;
+  const int row_at = hn / 4 * kRowsBytes + hn % 4 * kHeadDim * (int)sizeof(bf16_t) + half * 16;
+  const auto pages_at = [&](int it, int& a0, int& a1) {  // `it` is wave-uniform
+    a0 = __builtin_amdgcn_readlane(pp0, it & (kWave - 1));
+    a1 = __builtin_amdgcn_readlane(pp1, it & (kWave - 1));
+    if (it >= n_pairs) a0 = a1 = -1;
   };
-  // Pass 1 loads the keys with the streaming hint (a fifth faster here); pass 2 without, so that the
-  // part of the keys it reads last stays in the last-level cache for the gather that follows (which
-  // measures 20 us slower otherwise, more than the hint gains pass 2).
+  // Both passes load the keys with the streaming hint.  (Pass 2 used to do without, for the sake of the gather that
+  // follows and finds part of the keys in the last-level cache then: 222 + 98 us at 16 x 32768 tokens, 182 + 109 with
+  // the hint; 1 x 131072: 53 + 16, 48 + 15.)
   constexpr int kPolicyStream = 2;  // the "nt" bit of the load's cache policy
   // Load instruction j of a tile brings in token rows 4j .. 4j+3 (1 KiB, whole cache lines); lane l
-  // lands at 16 l bytes into the instruction's KiB of the slot, and fetches the 16-byte chunk that
-  // belongs there: the chunks of a row are stored XOR-swizzled by the row number, so that the reads
-  // below (16 rows at one chunk position) spread over all LDS banks.
-  const int dma_row = lane >> 4;                 // + 4 j
-  const auto fetch = [&](const bf16_t* rows, ring_u32x4* dst, auto policy) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = 4 * j + dma_row;
-      const int chunk = (lane & 15) ^ row;
-      load_to_lds<decltype(policy)::value>(rows + row * kHeadDim + chunk * 8, dst + j * kWave);
-    }
-  };
-  const auto issue = [&](int it, int slot) {
-    const int64_t off = tile_off(it);
-    fetch(c.k_pool + (off >= 0 ? off : 0) + head_off, ring + slot * 4 * kWave,
-          std::integral_constant<int, PASS2 ? 0 : kPolicyStream>{});
-  };
-  const auto read_tile = [&](int slot, bf16x8* kf) {
-    // everything but the kSnapRing - 1 younger tiles (four loads each) has landed
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kSnapRing - 1) * 4) : "memory");
-#pragma unroll
-    for (int j = 0; j < 4; ++j)  // token hn, channels 32 j + 8 kg ..: chunk 4 j + kg of row hn
-      kf[j] = __builtin_bit_cast(bf16x8, ring[slot * 4 * kWave + hn * 16 + ((4 * j + kg) ^ hn)]);
-  };
-  const auto products = [&](const bf16x8* kf, int qd, f32x4* acc) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  // lands 16 l bytes behind the instruction's place in the slot, and fetches the 16-byte chunk that
+  // belongs there: chunk x of row 4j + i stands at position x ^ 4i, and the instructions' places are 16 bytes
+  // more than a KiB apart, so that the reads below (16 rows at one chunk position) spread over all LDS banks.
+  const uint32_t dma_off = (uint32_t)((lane >> 4) * kHeadDim + ((lane & 15) ^ (lane >> 4) * 4) * 8) * sizeof(bf16_t);
+  const auto fetch = [&](const char* rows, unsigned char* dst, auto policy) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j], qf[qd * 4 + i][j].v, acc[i], 0, 0, 0);
+      load_to_lds<decltype(policy)::value>(rows + j * 4 * kHeadDim * (int)sizeof(bf16_t) + dma_off, dst + j * kRowsBytes);
   };
-  // MASKED = false is the hot case, a page that is present and lies wholly inside the prefix, so
-  // every window row sees all of it; it is written for the fewest vector instructions: the softmax
-  // scale goes into the exponent's multiply-add, and the page maximum is taken on the raw products
-  // (the scale is positive).
-  const auto update = [&](auto masked_tag, const f32x4* acc, int qd, bool present, int tok0, float* v) {
-    constexpr bool MASKED = decltype(masked_tag)::value;
+  const auto issue = [&](int it) {
+    int a0, a1;
+    pages_at(it, a0, a1);
+    unsigned char* dst = ring + (it & 1) * kSlotBytes;
+    constexpr std::integral_constant<int, kPolicyStream> policy{};
+    fetch(k_head + (int64_t)max(a0, 0) * c.stride_page * (int)sizeof(bf16_t), dst, policy);
+    fetch(k_head + (int64_t)max(a1, 0) * c.stride_page * (int)sizeof(bf16_t), dst + kTileBytes, policy);
+  };
+  // Row hn of a tile, channels 16 j + 8 half .., j = 0 .. 7: chunk 2 j + half
+  const auto read_row = [&](const unsigned char* tile, bf16x8 (&f)[8]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int cb = qd * 4 + i;
-      float s[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        s[r] = acc[i][r];
-        if (MASKED) s[r] = (present && tok0 + r <= limit[cb]) ? s[r] : -INFINITY;
+    for (int j = 0; j < 8; ++j)
+      f[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const ring_u32x4*>(tile + row_at + ((j / 2 ^ hn % 4) * 64 + j % 2 * 32)));
+  };
+  bf16x8 kf[8];
+  const auto read_pair = [&](int it) {  // this lane's row is token lane % 32 of the pair
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // everything but the younger pair has landed
+    read_row(ring + (it & 1) * kSlotBytes + lane % 32 / 16 * kTileBytes, kf);
+  };
+  const auto product = [&](int cb, int j, f32x16& acc) {
+    const f32x16 zero = {};
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j], qf[cb][j], j == 0 ? zero : acc, 0, 0, 0);
+  };
+  // The votes of a pair: staged in LDS, one copy per column group, and written out once per segment of
+  // kSnapSegPairs pairs (a global store per pair would sit among the tile loads the wait above counts, and
+  // make it wait for more of them than it needs).  Two buffers in turn, so one barrier per segment.
+  const int seg_tokens = kSnapSegPairs * 2 * npw * kAttnPage;
+  const int vote_at = pw * 2 * kAttnPage + lane / 16 % 2 * kAttnPage + lane / 8 % 2 * 8 + half * 4 + lane / 2 % 4;
+  const auto vote_slot = [&](int seg, int cg) { return s_out + ((seg & 1) * a.CG + cg) * seg_tokens; };
+  const auto emit_votes = [&](float (&v)[16], int it) {
+    // (element i of an accumulator is token 16 (i / 8) + 8 (i / 4 % 2) + 4 half + i % 4 of the pair)
+    const float total = half_wave_sums(v, lane);
+    lds_store(vote_slot(it / kSnapSegPairs, cgi) + it % kSnapSegPairs * (2 * npw * kAttnPage) + vote_at, total);
+  };
+  const auto write_out = [&](int it) {  // after iteration `it`, in every wavefront alike
+    if (!PASS2 || (it % kSnapSegPairs != kSnapSegPairs - 1 && it + 1 != n_pairs)) return;
+    // (not __syncthreads(), which would wait for the tiles in flight as well)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int seg = it / kSnapSegPairs, tok = p_begin * kAttnPage + seg * seg_tokens + tid * 4;
+    if (tid * 4 < seg_tokens && tok < min(p_end * kAttnPage, L)) {  // rows hold a multiple of four votes
+      float4 x = *reinterpret_cast<const float4*>(vote_slot(seg, 0) + tid * 4);
+      if (a.CG == 2) {
+        const float4 y = *reinterpret_cast<const float4*>(vote_slot(seg, 1) + tid * 4);
+        x = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
       }
-      if (!PASS2) {
-        // m[] is the running maximum in the log2 domain; an unchanged maximum rescales by exactly 1
-        const float mn = max2_raw(m[cb], max2_raw(max3_raw(s[0], s[1], s[2]), s[3]) * sc);
-        const float e01 = exp2_fast(fmaf(s[0], sc, -mn)) + exp2_fast(fmaf(s[1], sc, -mn));
-        const float e23 = exp2_fast(fmaf(s[2], sc, -mn)) + exp2_fast(fmaf(s[3], sc, -mn));
-        z[cb] = fmaf(z[cb], exp2_fast(m[cb] - mn), e01 + e23);
-        m[cb] = mn;
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = fmaf(exp2_fast(fmaf(s[r], sc, -M2[cb])), invZ[cb], v[r]);
-      }
+      *reinterpret_cast<float4*>(a.votes + (int64_t)unit * a.s_cap + tok) = x;
     }
   };
-  // votes of one page (already summed over the 16 columns a token group's lanes hold): staged in LDS,
-  // one copy per column group, and written out once per chunk (a global store per page would sit among
-  // the tile loads the wait above counts, and make it wait for more of them than it needs; adding the
-  // column groups per page would cost two workgroup barriers per page)
-  const int chunk_tokens = a.chunk_pages * kAttnPage;
-  const auto emit_votes = [&](float* v, bool live, int tok0) {
-    if (live && hn == 0)
-      *reinterpret_cast<float4*>(s_votes + cgi * chunk_tokens + (tok0 - p_begin * kAttnPage)) =
-          make_float4(v[0], v[1], v[2], v[3]);
-  };
-  int slot = kSnapRing - 1;  // the first tile's; see below
-  // One page: its tile out of the ring, then per group of four column blocks the products and the
-  // update; the slot is refilled once the last products have read it.
-  const auto page = [&](auto masked_tag, int it) {
-    constexpr bool MASKED = decltype(masked_tag)::value;
-    const int p = p_begin + it * npw + pw;
-    const bool present = MASKED ? tile_off(it) >= 0 : true;
-    const int tok0 = p * kAttnPage + kg * 4;
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    bf16x8 kf[4];
-    read_tile(slot, kf);
-#pragma unroll
-    for (int qd = 0; qd < QD; ++qd) {
-      f32x4 acc[4];
-      products(kf, qd, acc);
-      if (qd == QD - 1) {
-        // the tile is in registers (the products had to wait for the LDS reads): refill its slot
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        issue(it + kSnapRing, slot);
-      }
-      // keep the groups in program order: products of a later group hoisted above this group's
-      // update would need a second set of accumulators the register file has no room for
-      __builtin_amdgcn_sched_barrier(0);
-      update(masked_tag, acc, qd, present, tok0, v);
-    }
+
+  // Softmax update of block `cb` from its products `s`
+  float v[16];  // pass 2: this pair's votes
+  const auto update = [&](int cb, f32x16& s) {
     if (PASS2) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = row16_sum(v[r]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    slot = slot + 1 == kSnapRing ? 0 : slot + 1;
-    if (PASS2) emit_votes(v, p < p_end, tok0);
-  };
-  // The leading run of pages that need no mask takes the hot variant: none of the wavefront's pages
-  // absent, and the page's last token inside the prefix.
-  const bool any_absent =
-      __ballot((lane < n_it && off_lo < 0) || (lane + kWave < n_it && off_hi < 0)) != 0ull;
-  int n_fast = 0;
-  if (!any_absent) {
-    // pages p_begin + it * npw + pw with p * 16 + 15 <= L, i.e. p <= (L - 15) / 16, also below p_end
-    const int p_last = min(p_end - 1, (L - (kAttnPage - 1)) >= 0 ? (L - (kAttnPage - 1)) / kAttnPage : -1);
-    if (p_last >= p_begin + pw) n_fast = (p_last - p_begin - pw) / npw + 1;
-    n_fast = min(n_fast, n_it);
-  }
-  // The queries: fetched once per workgroup, as whole cache lines, into two of every wavefront's three
-  // ring slots, laid out like the key tiles (16 softmax rows for 16 tokens) and read from there; the
-  // first key tile travels beside them into the third slot.  (Every wavefront fetching its fragments
-  // from memory by itself took 9 us per workgroup, as long as 30 tiles: 128 loads of 16 half lines each
-  // through one first-level cache.  A pass over one prompt of 32768 tokens, 512 workgroups: 24.8 ->
-  // 20.5 us; over 16 of them, 2048 workgroups: 204 -> 190 and 247 -> 232.)  The rows of a group's heads
-  // lie one after the other, so column `col` is simply row `col`; window and group x window are
-  // multiples of 16, so a block of 16 columns is real or not as a whole and its place in the window is
-  // a scalar.
-  static_assert(kSnapRing == 3 && kSnapColBlocks == 8, "eight blocks of queries fill two slots of four wavefronts");
-  const auto block_at = [&](int cb) {  // where block cb lies: slot cb / 4 of wavefront cb % 4
-    return reinterpret_cast<ring_u32x4*>(snap_dyn) + ((cb % 4) * kSnapRing + cb / 4) * 4 * kWave;
-  };
-  const bf16_t* q_rows = a.qobs + ((int64_t)b * c.n_q_heads + (int64_t)g * c.group) * a.W * kHeadDim;
-  for (int cg = 0; cg < a.CG; ++cg) {
-    if (cg > 0) __syncthreads();  // the blocks of the group before have been read
-#pragma unroll
-    for (int h = 0; h < QD; ++h) {
-      const int cb = h * 4 + wave, block = cg * kSnapColBlocks + cb;
-      if (block * 16 < a.NC) fetch(q_rows + block * 16 * kHeadDim, block_at(cb), std::integral_constant<int, 0>{});
-    }
-    if (cg == 0) {
-      issue(0, slot);
-      asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // all but the first key tile
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
-    __syncthreads();
-    if (cg == cgi) {
-      int w0 = cg * kSnapColBlocks * 16 % a.W;
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        const bool real = (cg * kSnapColBlocks + cb) * 16 < a.NC;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const ring_u32x4 x = block_at(cb)[hn * 16 + ((4 * j + kg) ^ hn)];
-          qf[cb][j].u = real ? make_uint4(x.x, x.y, x.z, x.w) : make_uint4(0, 0, 0, 0);
-        }
-        limit[cb] = real ? L + w0 + hn : -1;
-        w0 = w0 + 16 == a.W ? 0 : w0 + 16;
+      for (int x = 0; x < 16; ++x) {
+        const float e = exp2_fast(fmaf(s[x], sc, -M2[cb]));
+        v[x] = cb == 0 ? e * invZ[cb] : fmaf(e, invZ[cb], v[x]);
       }
-    }
-  }
-  if (PASS2) {
+    } else {
+      // m[] is the running maximum in the log2 domain; an unchanged maximum rescales by exactly 1
+      // max3_raw() is assembly, in front of which the compiler leaves no time for the products to reach their
+      // registers.  It does in front of this multiplication, and the empty assembly puts the rest behind it.
+      const float last = s[15] * sc;
+      asm volatile("" : "+v"(s) : "v"(last));
+      const float x0 = max3_raw(s[0], s[1], s[2]), x1 = max3_raw(s[3], s[4], s[5]), x2 = max3_raw(s[6], s[7], s[8]);
+      const float x3 = max3_raw(s[9], s[10], s[11]), x4 = max3_raw(s[12], s[13], s[14]);
+      const float top = max3_raw(max3_raw(x0, x1, x2), x3, x4);
+      const float mn = max3_raw(m[cb], top * sc, last);
+      float sum = 0.f;
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-      const int col = (cgi * kSnapColBlocks + cb) * 16 + hn;
+      for (int x = 0; x < 16; x += 4) {
+        float e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = exp2_fast(fmaf(s[x + i], sc, -mn));
+        const float four = (e[0] + e[1]) + (e[2] + e[3]);
+        sum = x == 0 ? four : sum + four;
+      }
+      z[cb] = fmaf(z[cb], exp2_fast(m[cb] - mn), sum);
+      m[cb] = mn;
+    }
+  };
+
+  // The leading run of pairs that need no mask takes the hot variant: none of the wavefront's pages
+  // absent, and the pair's last token inside the prefix, so that every window row sees all of it.
+  int n_hot = 0;
+  // (A pair at or beyond the chunk's end is not an absent one: taken for one, it sent every pair of a wavefront down the
+  // masked path in the last chunk of most prompts: 25 us of pass 2 over 16 x 32768 tokens.)
+  const bool gone0 = first_page(lane) < p_end && pp0 < 0, gone1 = first_page(lane) + 1 < p_end && pp1 < 0;
+  if (__ballot(lane < n_pairs && (gone0 || gone1)) == 0ull) {
+    // pairs whose second page p has p * 16 + 15 <= L, i.e. p <= (L - 15) / 16, and lies below p_end
+    const int p_last = min(p_end - 1, (L - (kAttnPage - 1)) >= 0 ? (L - (kAttnPage - 1)) / kAttnPage : -1);
+    if (p_last >= p_begin + 2 * pw + 1) n_hot = (p_last - 1 - p_begin - 2 * pw) / (2 * npw) + 1;
+    n_hot = min(n_hot, n_pairs);
+  }
+  const auto hot_pairs = [&](int n) {
+    read_pair(0);
+    for (int it = 0; it < n; ++it) {
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        f32x16 acc;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) product(cb, j, acc);
+        if (cb == 0) {  // the keys are in registers (the products had to wait for the LDS reads): refill their slot
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          issue(it + 2);
+        }
+        if (cb == NB - 1) read_pair(it + 1);  // lands under the last update (behind the last pair, in vain)
+        // keep the blocks in program order: products of a later block hoisted above this one's update
+        // would need a second accumulator the register file has no room for
+        __builtin_amdgcn_sched_barrier(0);
+        update(cb, acc);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (PASS2) emit_votes(v, it);
+      write_out(it);
+    }
+  };
+  const int first_w = __builtin_amdgcn_readfirstlane(cgi * kSnapCols % a.W);
+  // A pair of any kind (pages absent, or at the end of the prefix, where rows differ in what they see).
+  const auto masked_pair = [&](int it) {
+    int a0, a1;
+    pages_at(it, a0, a1);
+    const int ln = (int)use_late((uint32_t)lane);  // nothing of this is worth a register across the hot pairs
+    const int tok0 = first_page(it) * kAttnPage + ln / 32 * 4;
+    read_pair(it);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    issue(it + 2);
+    int w0 = first_w;  // the place in the window of a block's first softmax row; window and blocks are multiples of 16
+    const auto next16 = [&](int w) { return w + 16 == a.W ? 0 : w + 16; };
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      f32x16 acc;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) product(cb, j, acc);
+      const int w1 = next16(w0);
+      int limit = L + ln % 16 + (ln & 16 ? w1 : w0);  // the last token this softmax row sees
+      if (cgi * kSnapCols + cb * 32 + ln % 32 >= a.NC) limit = -1;
+      w0 = next16(w1);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const bool sees = (i < 8 ? a0 : a1) >= 0 && tok0 + i / 4 * 8 + i % 4 <= limit;
+        acc[i] = sees ? acc[i] : -INFINITY;
+      }
+      update(cb, acc);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (PASS2) emit_votes(v, it);
+    write_out(it);
+  };
+
+  // The queries: fetched once per workgroup, as whole cache lines, into the second slot of every wavefront, laid
+  // out like the key tiles (16 softmax rows for 16 tokens) and read from there; the first pair of key
+  // tiles travels beside them into the first.  (Every wavefront fetching its fragments from memory by itself
+  // took 9 us per workgroup: 128 loads of 16 half lines each through one first-level cache.)  The rows of a
+  // group's heads lie one after the other, so column `col` is simply row `col`.
+  static_assert(kSnapCols == 8 * 16, "eight blocks of 16 queries fill one slot of four wavefronts");
+  const auto block_at = [&](int x) {  // where block x of 16 lies: tile x / 4 of the second slot of wavefront x % 4
+    return s_ring + (x % 4 * 2 + 1) * kSlotBytes + x / 4 * kTileBytes;
+  };
+  if (PASS2) {  // requested ahead of the queries: one round trip for both
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      const int col = cgi * kSnapCols + cb * 32 + lane % 32;
       const float2 st2 = col < a.NC ? *reinterpret_cast<const float2*>(a.stats + ((int64_t)unit * a.NC + col) * 2)
                                     : make_float2(0.f, 0.f);
       M2[cb] = st2.x;
       invZ[cb] = st2.y;
     }
   }
+  const char* q_rows = reinterpret_cast<const char*>(a.qobs + ((int64_t)b * c.n_q_heads + (int64_t)g * c.group) * a.W * kHeadDim);
+  for (int cg = 0; cg < a.CG; ++cg) {
+    if (cg > 0) __syncthreads();  // the blocks of the group before have been read
+#pragma unroll
+    for (int h = 0; h < (NB + 1) / 2; ++h) {
+      const int x = h * 4 + wave, block = cg * (kSnapCols / 16) + x;
+      if (block * 16 < a.NC) fetch(q_rows + (int64_t)block * 16 * kHeadDim * sizeof(bf16_t), block_at(x), std::integral_constant<int, 0>{});
+    }
+    if (cg == 0) {
+      issue(0);
+      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // all but the first pair of key tiles
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    __syncthreads();
+    if (cg == cgi) {
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        read_row(block_at(2 * cb + lane % 32 / 16), qf[cb]);
+        if (cg * kSnapCols + cb * 32 + lane % 32 >= a.NC) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) qf[cb][j] = __builtin_bit_cast(bf16x8, (ring_u32x4){0u, 0u, 0u, 0u});
+        }
+      }
+    }
+  }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __syncthreads();  // the blocks have been read: their slots take key tiles now
-  issue(1, 0);
-  issue(2, 1);
-  int it = 0;
-  for (; it < n_fast; ++it) page(std::false_type{}, it);
-  for (; it < n_it; ++it) page(std::true_type{}, it);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last refills (unused) land before LDS is reused
-  if (PASS2) {
-    __syncthreads();
-    const int tok_begin = p_begin * kAttnPage;
-    const int n_tok = min(p_end * kAttnPage, L) - tok_begin;
-    for (int i = tid; i < n_tok; i += 256)
-      a.votes[(int64_t)unit * a.s_cap + tok_begin + i] = a.CG == 2 ? s_votes[i] + s_votes[chunk_tokens + i] : s_votes[i];
-    return;
-  }
-  // ---- pass 1: merge statistics over token groups, waves, and hand the chunk's partial out -------
+  issue(1);
+  if (n_hot > 0) hot_pairs(n_hot);
+  for (int it = n_hot; it < n_pairs; ++it) masked_pair(it);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last refills (unused) land before the workgroup's LDS is given back
+  if (PASS2) return;
+  // ---- pass 1: merge statistics over the half wavefronts and the wavefronts, and hand the chunk's partial out
+  float (*sM)[kSnapCols] = reinterpret_cast<float (*)[kSnapCols]>(s_out);
+  float (*sZ)[kSnapCols] = sM + 4;
 #pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) {
-#pragma unroll
-    for (int off = 16; off <= 32; off <<= 1) {
-      const float mo = __shfl_xor(m[cb], off), zo = __shfl_xor(z[cb], off);
-      const float mn = fmaxf(m[cb], mo);
-      z[cb] = z[cb] * exp2_fast(m[cb] - mn) + zo * exp2_fast(mo - mn);
-      m[cb] = mn;
-    }
-    if (kg == 0) {
-      sM[wave][cb * 16 + hn] = m[cb];
-      sZ[wave][cb * 16 + hn] = z[cb];
+  for (int cb = 0; cb < NB; ++cb) {
+    const float mo = __shfl_xor(m[cb], 32), zo = __shfl_xor(z[cb], 32);
+    const float mn = fmaxf(m[cb], mo);
+    z[cb] = z[cb] * exp2_fast(m[cb] - mn) + zo * exp2_fast(mo - mn);
+    if (half == 0) {
+      sM[wave][cb * 32 + lane] = mn;
+      sZ[wave][cb * 32 + lane] = z[cb];
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < a.CG * kSnapColBlocks * 16; idx += 256) {
-    const int cg2 = idx / (kSnapColBlocks * 16), lc = idx % (kSnapColBlocks * 16);
-    const int col = cg2 * kSnapColBlocks * 16 + lc;
-    if (col >= a.NC) continue;
+  for (int idx = tid; idx < a.CG * kSnapCols; idx += 256) {
+    const int cg2 = idx / kSnapCols, lc = idx % kSnapCols;
+    if (idx >= a.NC) continue;
     float mm = kNegBigS, zz = 0.f;
     for (int w2 = cg2; w2 < 4; w2 += a.CG) {
       const float mo = sM[w2][lc], zo = sZ[w2][lc];
@@ -374,7 +414,7 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
       zz = zz * exp2_fast(mm - mn) + zo * exp2_fast(mo - mn);
       mm = mn;
     }
-    float* o = a.stats_part + (((int64_t)unit * a.n_chunks + chunk) * a.NC + col) * 2;
+    float* o = a.stats_part + (((int64_t)unit * a.n_chunks + chunk) * a.NC + idx) * 2;
     o[0] = mm;
     o[1] = zz;
   }
@@ -925,13 +965,13 @@ SnapPlan plan_snapkv(const CacheView& src, int window, int keep) {
   const int NC = src.group * window;
   // Pages per workgroup in the score passes.  A workgroup fetches its query block before its first page,
   // which long chunks amortise; short ones keep the chip full when there are few (sequence, KV head)
-  // units.  Doubled while there are more than 512 workgroups, two per compute unit: the whole call over
-  // eight units of 65536 tokens takes 92 us so, 101 at a bound of 256 and 99 at 1024, 64 units of 8192 172,
-  // 171 and 181.  The shortest chunk dates from when every wavefront fetched the query block for itself; now
-  // chunks of 16 are faster where units are few (eight of 4096 tokens 45 against 52 us, of 16384 56 and 57).
-  static_assert(kSnapMaxChunkPages / 2 <= kSnapMaxIters, "a wavefront's share of the longest chunk must fit its page-offset lanes");
+  // units.  Doubled while there are more than 512 workgroups, two per compute unit: 1 x 131072 takes 49 + 48 us so,
+  // 53 + 53 at a bound of 1024 and 61 + 57 at 2048; 16 x 32768 173, 180 and 187 for the first pass.
+  // A wavefront looks its pairs up in a lane each: with two column groups, two wavefronts share a chunk's pages.
+  const int max_chunk = NC > kSnapCols ? kSnapMaxChunkPages / 2 : kSnapMaxChunkPages;
+  static_assert(kSnapMaxChunkPages == 4 * 2 * kSnapMaxPairs, "a pair per lane");
   int chunk_pages = 32;
-  while (chunk_pages < kSnapMaxChunkPages && units * ((src.pages_cap + chunk_pages - 1) / chunk_pages) > 512) chunk_pages *= 2;
+  while (chunk_pages < max_chunk && units * ((src.pages_cap + chunk_pages - 1) / chunk_pages) > 512) chunk_pages *= 2;
   p.chunk_pages = chunk_pages;
   p.n_chunks = (src.pages_cap + chunk_pages - 1) / chunk_pages;
   const size_t s_cap = (size_t)src.pages_cap * kAttnPage;
@@ -965,7 +1005,7 @@ hipError_t launch_snapkv(const bf16_t* q_obs, const CacheView& src, int window, 
   a.qobs = q_obs;
   a.W = window;
   a.NC = src.group * window;
-  a.CG = a.NC > kSnapColBlocks * 16 ? 2 : 1;
+  a.CG = a.NC > kSnapCols ? 2 : 1;
   a.n_chunks = plan.n_chunks;
   a.chunk_pages = plan.chunk_pages;
   a.keep = keep;
@@ -986,18 +1026,16 @@ hipError_t launch_snapkv(const bf16_t* q_obs, const CacheView& src, int window, 
   a.sel_split = plan.sel_split;
 
   const dim3 sgrid(plan.n_chunks, units);
-  const size_t vote_bytes = (size_t)a.CG * a.chunk_pages * kAttnPage * sizeof(float);
-  const bool two_groups = a.NC > 4 * 16;  // some wavefront owns more than four blocks of real rows
-  if (two_groups)
-    hipLaunchKernelGGL((snap_score_kernel<false, 2>), sgrid, dim3(256), kSnapRingBytes, st, src, a);
+  const bool wide = a.NC > kSnapCols / 2;  // some wavefront owns more than two blocks of 32 softmax rows
+  if (wide)
+    hipLaunchKernelGGL((snap_score_kernel<false, 4>), sgrid, dim3(256), kRingBytes + kSnapStatBytes, st, src, a);
   else
-    hipLaunchKernelGGL((snap_score_kernel<false, 1>), sgrid, dim3(256), kSnapRingBytes, st, src, a);
+    hipLaunchKernelGGL((snap_score_kernel<false, 2>), sgrid, dim3(256), kRingBytes + kSnapStatBytes, st, src, a);
   hipLaunchKernelGGL(snap_stats_kernel, dim3(units), dim3(kStatsT), 0, st, src, a);
-
-  if (two_groups)
-    hipLaunchKernelGGL((snap_score_kernel<true, 2>), sgrid, dim3(256), kSnapRingBytes + vote_bytes, st, src, a);
+  if (wide)
+    hipLaunchKernelGGL((snap_score_kernel<true, 4>), sgrid, dim3(256), kRingBytes + kSnapVoteBytes, st, src, a);
   else
-    hipLaunchKernelGGL((snap_score_kernel<true, 1>), sgrid, dim3(256), kSnapRingBytes + vote_bytes, st, src, a);
+    hipLaunchKernelGGL((snap_score_kernel<true, 2>), sgrid, dim3(256), kRingBytes + kSnapVoteBytes, st, src, a);
   const dim3 pgrid((a.s_cap + kPoolTile - 1) / kPoolTile, units);
   const size_t pool_groups = kPoolT + 2 * ((a.pool_r + 7) / 8);
   hipLaunchKernelGGL(snap_pool_kernel, pgrid, dim3(kPoolT), pool_groups * 10 * sizeof(float), st, src, a);

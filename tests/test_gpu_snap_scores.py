@@ -1,0 +1,52 @@
+"""Stage 1's score passes at the edges of their tiles: blocks of 32 softmax rows that are real in part, one and two
+column groups, windows that do not divide a block, prompts that end inside a page, pair, segment and chunk, and the
+longest chunk (whose size follows from the capacity: the table is padded with absent pages).
+
+Kept positions against the oracle on unpooled votes, exact outside a 1e-3 band around the threshold (votes are sums of
+at most 256 probabilities, whose logits are summed in fp32: some 1e-6 relative)."""
+import numpy as np
+import pytest
+
+from paper_2502_14051_amd import workloads as wl
+from helpers import assert_topk_within_band, to_device_cache
+
+pytestmark = pytest.mark.gpu
+
+
+def check(oracle, hq, hkv, W, lens, cap, keep):
+    import torch
+    from paper_2502_14051_amd import rocketkv as rk
+    print("[case] scores", hq, hkv, W, lens, cap, keep, flush=True)
+    dev = torch.device("cuda:0")
+    w = wl.scaled(wl.CONFIGS["tiny"], batch=len(lens), n_q_heads=hq, n_kv_heads=hkv, context=max(lens), window=W, n_heavy=4,
+                  seed=hq * 100 + W)
+    d = wl.generate(w, with_obs=True)
+    d["seq_lens"] = np.asarray(lens, dtype=np.int32)
+    src, _ = to_device_cache(rk, torch, d, hq, 16, dev, shuffle_rng=np.random.default_rng(W))
+    held = src.block_table
+    src.pages_cap = max(cap, held.shape[1])
+    src.block_table = torch.full((len(lens), src.pages_cap), -1, dtype=torch.int32, device=dev)
+    src.block_table[:, :held.shape[1]] = held
+    dst = rk.alloc_cache(len(lens), hq, hkv, 128, 16, (keep + 15) // 16, dev, zero=True)
+    kept = torch.full((len(lens), hkv, keep), -9, dtype=torch.int32, device=dev)
+    rk.snapkv_compress(wl.from_bits(d["qobs"], dev), src, W, 1, keep, dst, kept, rk.alloc_workspace(rk.OP_SNAPKV, src, W, keep))
+    torch.cuda.synchronize()
+    got, ref = kept.cpu().numpy(), oracle.snapkv(d["qobs"], d["K"], d["seq_lens"], 1, keep, want_votes=True)
+    for b, S in enumerate(lens):
+        for g in range(hkv):
+            assert got[b, g, keep - W:].tolist() == list(range(S - W, S))
+            assert_topk_within_band(ref["gv"][b, g, :S - W], got[b, g, :keep - W], keep - W, f"b{b} g{g}")
+
+
+# softmax rows (group x window): 16, 32, 48, 64 | 80, 96, 128 | 144, 192, 256 in two column groups
+@pytest.mark.parametrize("hq,hkv,W", [(1, 1, 16), (2, 1, 16), (3, 1, 16), (8, 2, 16), (5, 1, 16), (2, 1, 48), (4, 1, 32),
+                                      (3, 1, 48), (4, 1, 48), (8, 1, 32), (2, 1, 128)])
+def test_rows(oracle, hq, hkv, W):
+    check(oracle, hq, hkv, W, (1500, 512 + W, 1024 + W + 16, 700 + W), 0, 200)
+
+
+@pytest.mark.parametrize("hq,hkv,W", [(4, 4, 16), (16, 4, 16), (64, 4, 16)])
+@pytest.mark.parametrize("last", [0, 1, 15, 16, 17, 32, 255, 1024, 1039])
+def test_chunk_ends(oracle, hq, hkv, W, last):
+    """A chunk of 512 pages (256 with two column groups) and what lies behind it."""
+    check(oracle, hq, hkv, W, (8192 + W + last, 4096 + W + last, 2000 + last, 8192 + last), 8448, 300)
