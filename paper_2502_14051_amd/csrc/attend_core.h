@@ -306,15 +306,23 @@ __device__ __forceinline__ void softmax_round(u32x4 (&kf)[NP][2][4], u32x2 (&vf)
   softmax_pv<NP, CB>(acc, vf, O, m, l, have_acc, sc);
 }
 
+struct NoHook {
+  __device__ __forceinline__ void operator()() const {}
+};
+
 // Merges of one workgroup's result: the wavefronts' (O, max, sum) through LDS, then, when the unit's
 // list is split over several workgroups, the hand-over of the partial and the last arriver's merge of
 // all of them.  `O`, `m`, `l` are the lane's online-softmax state with `l` already summed over the four
 // token groups; `smem` holds WAVES*G*(CB*16+2) floats, `s_last` one int.  The workgroup owns output
 // channels cs*CB*16 .. +CB*16-1 of the unit; workgroups with different `cs` never meet.
-template <int WAVES, int CB = 8>
+//
+// `unit_read` runs once in thread 0 of the workgroup that merges a split list, behind the loads of the first
+// partials: a place for a memory operation that must wait until every workgroup of the group has got this far, and whose
+// answer should travel with those loads.
+template <int WAVES, int CB = 8, typename Hook = NoHook>
 __device__ __forceinline__ void attend_merge(const CacheView& c, const AttendArgs& a, int unit, int split, int cs,
                                              const f32x4 (&O)[CB], float m, float l, float* smem,
-                                             int* s_last, int b, int g) {
+                                             int* s_last, int b, int g, const Hook& unit_read = Hook()) {
   constexpr int kThreads = WAVES * kWave;
   constexpr int CW = CB * 16;  // output channels of this workgroup
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
@@ -396,6 +404,7 @@ __device__ __forceinline__ void attend_merge(const CacheView& c, const AttendArg
         os[t] = ld_agent(ps + ch);
         if (!ok) { ms[t] = kNegBig; ls[t] = 0.f; os[t] = 0.f; }
       }
+      if (s0 == 0 && idx == 0) unit_read();
       float Mb = M;
 #pragma unroll
       for (int t = 0; t < 8; ++t) Mb = fmaxf(Mb, ms[t]);
@@ -421,10 +430,6 @@ __device__ __forceinline__ void attend_merge(const CacheView& c, const AttendArg
 // The attention of one workgroup: its share (`split`) of the page list of `unit`, then the merges.
 // `list` points at the unit's page ids (global memory or LDS; null = identity), `smem` at
 // WAVES*G*130 floats of LDS for the wave merge, `s_last` at one LDS int.
-struct NoHook {
-  __device__ __forceinline__ void operator()() const {}
-};
-
 // `after_stream` runs once per thread after the last K/V tile has been consumed and before the
 // merges: a place for stores whose latency should hide under the merge.
 //
@@ -437,12 +442,12 @@ struct NoHook {
 //
 // `last_round` runs once per thread right after the loads of its last round have been requested (or
 // before `after_stream` if it has no round at all): a place for a memory operation whose answer
-// should travel with those loads instead of being waited for on its own.
-template <int WAVES, int NP, bool STREAM_K, int CB = 8, typename Hook = NoHook, typename Hook2 = NoHook>
+// should travel with those loads instead of being waited for on its own.  `unit_read`: see attend_merge.
+template <int WAVES, int NP, bool STREAM_K, int CB = 8, typename Hook = NoHook, typename Hook2 = NoHook, typename Hook3 = NoHook>
 __device__ __forceinline__ void attend_block(const CacheView& c, const AttendArgs& a, int unit, int split, int cs,
                                              int n, const int32_t* list, float* smem, int* s_last,
                                              const TailPatch& tp, const Hook& after_stream = Hook(),
-                                             const Hook2& last_round = Hook2()) {
+                                             const Hook2& last_round = Hook2(), const Hook3& unit_read = Hook3()) {
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int hn = lane % 16, kg = lane / 16;
   const int b = unit / c.n_kv_heads, g = unit % c.n_kv_heads;
@@ -541,7 +546,7 @@ __device__ __forceinline__ void attend_block(const CacheView& c, const AttendArg
   RKV_STAMP(7);
   if (wb >= we) last_round();
   after_stream();
-  attend_merge<WAVES, CB>(c, a, unit, split, cs, O, m, l, smem, s_last, b, g);
+  attend_merge<WAVES, CB>(c, a, unit, split, cs, O, m, l, smem, s_last, b, g, unit_read);
 }
 
 }  // namespace rkv

@@ -129,12 +129,12 @@ __device__ __forceinline__ void token_round(u32x4 (&kf)[2][4], u32x4 (&vr)[2][4]
 // merges.  `n`: the unit's (logical) length, already counting a token being appended (which `tp`
 // describes; compiled in with PATCH); `list`: the unit's page ids (global memory or LDS; null = identity); `smem`:
 // WAVES*G*130 floats of LDS; `after_stream` runs once per thread after the last K/V row has been
-// consumed, before the merges.
-template <int WAVES, bool INDEXED, bool PATCH = false, typename Hook = NoHook>
+// consumed, before the merges, `unit_read` as in attend_merge.
+template <int WAVES, bool INDEXED, bool PATCH = false, typename Hook = NoHook, typename Hook2 = NoHook>
 __device__ __forceinline__ void attend_tokens_block(const CacheView& c, const AttendArgs& a, const TokenRun& t,
                                                     int unit, int split, int n, const int32_t* list,
                                                     float* smem, int* s_last, const TokenPatch& tp,
-                                                    const Hook& after_stream = Hook()) {
+                                                    const Hook& after_stream = Hook(), const Hook2& unit_read = Hook2()) {
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int hn = lane % 16, kg = lane / 16;
   const int b = unit / c.n_kv_heads, g = unit % c.n_kv_heads;
@@ -249,7 +249,7 @@ __device__ __forceinline__ void attend_tokens_block(const CacheView& c, const At
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
   after_stream();
-  attend_merge<WAVES, 8>(c, a, unit, split, 0, O, m, l, smem, s_last, b, g);
+  attend_merge<WAVES, 8>(c, a, unit, split, 0, O, m, l, smem, s_last, b, g, unit_read);
 }
 
 }  // namespace rkv

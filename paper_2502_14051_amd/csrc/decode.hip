@@ -10,8 +10,8 @@
 // summaries are updated each time a new key is generated): the first workgroup of each unit writes
 // the key row, the value column and the updated summary column for later steps, while every
 // workgroup patches the new key / value into what it reads from LDS copies, so nobody depends on
-// those writes having landed.  The sequence length is bumped by whichever workgroup of the sequence
-// is last to have read the old one (a per-sequence arrival counter in the workspace header).
+// those writes having landed.  The sequence length is bumped once every workgroup of the sequence has read the old
+// one (a per-sequence counter in the workspace header, see report_read).
 #include "attend_core.h"
 #include "select_core.h"
 
@@ -43,9 +43,8 @@ void hsa_decode_kernel(CacheView c, SelectArgs sa, AttendArgs aa, AppendArgs ap,
   uint32_t arrivals = 0;
   bf16_t kb = 0, vb = 0;
   if (APPEND && tid < kHeadDim) {
-    const int64_t src = ((int64_t)b * c.n_kv_heads + g) * kHeadDim + tid;
-    kb = ap.k_new[src];
-    vb = ap.v_new[src];
+    kb = ap.k_new[(int64_t)unit * kHeadDim + tid];
+    vb = ap.v_new[(int64_t)unit * kHeadDim + tid];
   }
 
   const int split = blockIdx.y / aa.n_csplit, cs = blockIdx.y % aa.n_csplit;
@@ -59,10 +58,6 @@ void hsa_decode_kernel(CacheView c, SelectArgs sa, AttendArgs aa, AppendArgs ap,
   TailPatch tp = {-1, 0, s_knew, s_vnew};
   for (int i = tid; i < sa.row_len; i += NT) list[i] = -1;
   if (APPEND && tid < kHeadDim) {
-    // Every thread has read the old length.  Behind its K/V stream the workgroup reports that read to
-    // the per-sequence counter, and the one that finds every other workgroup of the sequence has
-    // reported stores the new length at its very end: no thread anywhere sees the length change
-    // under it.
     s_knew[tid] = kb;
     s_vnew[tid] = vb;
   }
@@ -80,7 +75,7 @@ void hsa_decode_kernel(CacheView c, SelectArgs sa, AttendArgs aa, AppendArgs ap,
     }
   }
   // the summary column the new key goes into, and where the token's page lives: requested behind the
-  // thread's last K/V tiles (see `report`), looked at in the write-back
+  // thread's last K/V tiles, looked at in the write-back
   uint32_t old_max = 0, old_min = 0;  // bf16 bits
   const auto summary_slot = [&]() {
     return ((int64_t)unit * kHeadDim + (tid & (kHeadDim - 1))) * c.pages_cap + (room ? tp.page : 0);
@@ -145,17 +140,12 @@ void hsa_decode_kernel(CacheView c, SelectArgs sa, AttendArgs aa, AppendArgs ap,
   }
   __syncthreads();  // list complete; the selection scratch is dead and becomes the merge buffer
   RKV_STAMP(5);
-  // The token generated at this step goes to memory for later steps (the first workgroup of the unit
-  // writes the key row, the value column and the updated summary column), and the workgroup reports
-  // its read of the old length.  None of this is on the way of the result, so each piece sits where
-  // its memory latency hides:
-  //   request: the loads above;
-  //   report:  the add to the sequence's counter, behind the loads of thread 0's last K/V tiles, so
-  //            that its answer travels with them;
-  //   store:   the write-back itself.
-  // The stores follow the thread's last tile and drain under the merges.  Where the request has not
-  // gone out yet, it goes out with the report if the workgroup's registers allow (a share of the
-  // channels, CB < 8), otherwise in front of the stream, where its answers arrive with the first tiles.
+  // The token generated at this step goes to memory for later steps: the first workgroup of the unit
+  // writes the key row, the value column and the updated summary column.  None of this is on the way of the result, so
+  // each piece sits where its memory latency hides: the request above; the stores behind the thread's last tile,
+  // so that they drain under the merges.  Where the request has not gone out yet, it goes out behind the loads of the
+  // last tiles if the workgroup's registers allow (a share of the channels, CB < 8), otherwise in front of the stream,
+  // where its answers arrive with the first tiles.
   auto store = [&]() {
     if (APPEND && room && first && tid < kHeadDim) {
       const int64_t sum_off = summary_slot();
@@ -170,22 +160,27 @@ void hsa_decode_kernel(CacheView c, SelectArgs sa, AttendArgs aa, AppendArgs ap,
       if (tp.slot == 0 || x < bf16_to_f32((bf16_t)use_late(old_min))) ap.kmin[sum_off] = kb;
     }
   };
+  if (APPEND && tid == 0) report_read(seq_counters, read_slot(c, b));
+  auto check = [&]() {
+    if (APPEND) arrivals = reads_reported(seq_counters, read_slot(c, b));
+  };
   auto last_round = [&]() {
-    if (!APPEND) return;
-    if (tid == 0)
-      arrivals = __hip_atomic_fetch_add(&seq_counters[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (CB < 8) request();
+    if (APPEND && CB < 8) request();
+  };
+  auto behind = [&]() {
+    if (aa.n_split == 1 && tid == 0) check();
+    store();
   };
   if (CB == 8 && !kRequestEarly && !kBoundsFromRows) request();
   attend_block<WAVES, 1, STREAM_K, CB>(c, aa, unit, split, cs, n, list, reinterpret_cast<float*>(region), &s_last, tp,
-                                       store, last_round);
+                                       behind, last_round, check);
 
   RKV_STAMP(12);
   if (APPEND) {
-    // the last workgroup of the sequence to have read the old length stores the new one
-    if (tid == 0 && arrivals == (uint32_t)c.n_kv_heads * gridDim.y - 1u) {
+    // (a unit that finds the sequence's workgroups complete; at least the last one to look does)
+    if (tid == 0 && arrivals == (uint32_t)c.n_kv_heads * gridDim.y) {
       if (room) c.seq_lens[b] = n;
-      __hip_atomic_store(&seq_counters[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      clear_reads(seq_counters, read_slot(c, b));
     }
   }
 }

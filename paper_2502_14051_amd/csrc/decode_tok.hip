@@ -9,7 +9,7 @@
 // reader patches its key / value rows in from LDS copies; split 0 of the unit writes them to the cache,
 // updates the tail page's summary column and, under an index, records the token's cache position as
 // the next entry of the logical sequence.  The lengths (the cache's, and the logical one under an
-// index) are bumped by whichever workgroup of the sequence is last to have read the old ones.
+// index) are bumped once every workgroup of the sequence has read the old ones (see report_read).
 #include "attend_tok_core.h"
 #include "select_core.h"
 
@@ -41,12 +41,10 @@ void hsa_decode_tok_kernel(CacheView c, CacheView lc, SelectArgs sa, AttendArgs 
   uint32_t arrivals = 0;
   bf16_t kb = 0, vb = 0;
   if (APPEND) {
-    // every thread has read the old lengths (see the header comment for how the workgroup reports that)
     if (INDEXED) pos0 = c.seq_lens[b + opaque_zero()];
     if (tid < kHeadDim) {
-      const int64_t src = (int64_t)unit * kHeadDim + tid;
-      kb = ap.k_new[src];
-      vb = ap.v_new[src];
+      kb = ap.k_new[(int64_t)unit * kHeadDim + tid];
+      vb = ap.v_new[(int64_t)unit * kHeadDim + tid];
     }
   }
 
@@ -88,10 +86,13 @@ void hsa_decode_tok_kernel(CacheView c, CacheView lc, SelectArgs sa, AttendArgs 
   }
   select_pages<NT>(lc, sa, unit, n, sh, keys, list, split == 0, tp);
   __syncthreads();  // list complete; the selection scratch is dead and becomes the merge buffer
+  if (APPEND && tid == 0) report_read(seq_counters, read_slot(c, b));
+  auto check = [&]() {
+    if (APPEND) arrivals = reads_reported(seq_counters, read_slot(c, b));
+  };
   auto write_back = [&]() {
     if (!APPEND) return;
-    if (tid == 0)  // this workgroup's read of the old lengths, reported where the answer's latency hides under the merges
-      arrivals = __hip_atomic_fetch_add(&seq_counters[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (aa.n_split == 1 && tid == 0) check();
     if (room && split == 0 && tid < kHeadDim) {
       const int sp = pos0 / c.page_size, ss = pos0 % c.page_size;
       const int64_t pp = phys_page(c, b, sp);
@@ -108,15 +109,15 @@ void hsa_decode_tok_kernel(CacheView c, CacheView lc, SelectArgs sa, AttendArgs 
     }
   };
   attend_tokens_block<WAVES, INDEXED, APPEND>(c, aa, t, unit, split, n, list, reinterpret_cast<float*>(region),
-                                             &s_last, tokp, write_back);
+                                             &s_last, tokp, write_back, check);
   if (APPEND) {
-    // the last workgroup of the sequence to have read the old lengths stores the new ones
-    if (tid == 0 && arrivals == (uint32_t)c.n_kv_heads * gridDim.y - 1u) {
+    // (a unit that finds the sequence's workgroups complete; at least the last one to look does)
+    if (tid == 0 && arrivals == (uint32_t)c.n_kv_heads * gridDim.y) {
       if (room) {
         lc.seq_lens[b] = n;
         if (INDEXED) c.seq_lens[b] = pos0 + 1;
       }
-      __hip_atomic_store(&seq_counters[b], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      clear_reads(seq_counters, read_slot(c, b));
     }
   }
 }

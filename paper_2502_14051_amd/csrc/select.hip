@@ -15,8 +15,7 @@ __global__ __launch_bounds__(kSelThreads) void hsa_select_kernel(CacheView c, Se
   __shared__ SelectShared<kSelThreads> sh;
   const int unit = blockIdx.x;
   const int n = c.seq_lens[unit / c.n_kv_heads];
-  const TailPatch none = {-1, 0, nullptr, nullptr};
-  select_block<kSelThreads>(c, a, unit, n, sh, keys, nullptr, true, none);
+  select_block<kSelThreads>(c, a, unit, n, sh, keys);
 }
 
 // ---- large summaries: scores by several workgroups per (sequence, KV head), then the top-k ---------
