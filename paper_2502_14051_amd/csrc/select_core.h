@@ -39,14 +39,17 @@ struct SelectShared {
 
 // exclusive prefix sum of one uint32 per thread over the NT-thread workgroup.  REUSE = false leaves
 // out the trailing barrier, for a caller that does not touch `wsum` again before its next barrier.
+// The wavefronts' totals are summed by a scan of their own, a lane each: walking the ones in front took a sixteen-wavefront
+// workgroup up to fifteen LDS reads one after the other.
 template <int NT, bool REUSE = true>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum) {
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  constexpr int kWaves = NT / kWave;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t inc = wave_incl_scan(v);
   if (lane == kWave - 1) wsum[wave] = inc;
   __syncthreads();
-  uint32_t base = 0;
-  for (int w = 0; w < wave; ++w) base += wsum[w];
+  const uint32_t upto = wave_incl_scan(lane < kWaves ? wsum[lane] : 0u);
+  const uint32_t base = wave > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, wave - 1) : 0u;
   if (REUSE) __syncthreads();
   return base + inc - v;
 }
@@ -774,7 +777,7 @@ template <int NT>
 struct PickShared {
   __align__(16) uint32_t hist[4][256];  // 1024 value bins, or the four radix histograms of the fallback
   uint32_t cand[1024];
-  float wmin[NT / kWave], wmax[NT / kWave];
+  uint32_t wmin[NT / kWave], wmax[NT / kWave];
   uint32_t wsum[NT / kWave];
   int found[6];
   uint32_t cnt0;
@@ -824,7 +827,7 @@ __device__ __forceinline__ void pick_from_scores_n(const CacheView& c, const Sel
   if (P == 0) return;
   const int n_rec = min(a.n_recent, kp);  // no more forced pages than pages picked: the newest ones win
   uint32_t key[kVec * 4];
-  float lo = INFINITY, hi = -INFINITY;
+  uint32_t klo = 0xffffffffu, khi = 0u;  // the range of the finite scores, as order keys
 #pragma unroll
   for (int i = 0; i < kVec; ++i) {
     const float x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
@@ -837,8 +840,8 @@ __device__ __forceinline__ void pick_from_scores_n(const CacheView& c, const Sel
       key[i * 4 + e] = f32_order_key(sc);
       if (live) {
         if (fabsf(sc) < INFINITY) {
-          lo = fminf(lo, sc);
-          hi = fmaxf(hi, sc);
+          klo = min(klo, key[i * 4 + e]);
+          khi = max(khi, key[i * 4 + e]);
         }
       }
     }
@@ -850,23 +853,20 @@ __device__ __forceinline__ void pick_from_scores_n(const CacheView& c, const Sel
   if (kp < P) {
     uint32_t* hist = &sh.hist[0][0];
     uint32_t* cand = sh.cand;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, off));
-      hi = fmaxf(hi, __shfl_xor(hi, off));
-    }
+    klo = wave_min_u32(klo);
+    khi = wave_max_u32(khi);
     if (lane == 0) {
-      sh.wmin[wave] = lo;
-      sh.wmax[wave] = hi;
+      sh.wmin[wave] = klo;
+      sh.wmax[wave] = khi;
     }
     if (tid == 0) sh.cnt0 = 0;
     __syncthreads();
-#pragma unroll
-    for (int w = 0; w < NT / kWave; ++w) {
-      lo = fminf(lo, sh.wmin[w]);
-      hi = fmaxf(hi, sh.wmax[w]);
-    }
-    const float scale = (float)(NB - 1) / (hi - lo);
+    constexpr int kWaves = NT / kWave;
+    klo = wave_min_u32(lane < kWaves ? sh.wmin[lane] : 0xffffffffu);
+    khi = wave_max_u32(lane < kWaves ? sh.wmax[lane] : 0u);
+    const float lo = f32_from_order_key(klo), hi = f32_from_order_key(khi);  // (no finite score: lo is a NaN)
+    // (any positive factor makes monotone bins, so the hardware's reciprocal will do)
+    const float scale = (float)(NB - 1) * __builtin_amdgcn_rcpf(hi - lo);
     bool decided = (hi > lo) && (scale < 3.0e38f);  // same for every thread
     if (decided) {
       const auto bin_of = [&](uint32_t k) -> int {

@@ -745,12 +745,12 @@ __device__ __forceinline__ void snap_threshold(const uint2* runs, int n_runs, co
     sh.wsum[1][wave] = eq;
   }
   __syncthreads();
-  gt_before = eq_before = 0;
-#pragma unroll
-  for (int w = 0; w < kSelT / kWave; ++w) {
-    gt_before += sh.wsum[0][w];
-    eq_before += sh.wsum[1][w];
-  }
+  constexpr int kWaves = kSelT / kWave;
+  const auto total = [&](const uint32_t* w) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(lane < kWaves ? w[lane] : 0u), kWaves - 1);
+  };
+  gt_before = total(sh.wsum[0]);
+  eq_before = total(sh.wsum[1]);
   __syncthreads();
 }
 
