@@ -193,8 +193,7 @@ __device__ __forceinline__ void softmax_pv(f32x4 (&acc)[NP][2], u32x2 (&vf)[NP][
 #pragma unroll
     for (int x = 0; x < 2; ++x)
       mx = fmaxf(fmaxf(mx, fmaxf(acc[u][x][0], acc[u][x][1])), fmaxf(acc[u][x][2], acc[u][x][3]));
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  mx = rows_max_f32(mx);
   const float m_new = fmaxf(m, mx * sc);  // running max in the scaled log2 domain
   if (have_acc) {
     const float alpha = fast_exp2(m - m_new);
@@ -541,8 +540,7 @@ __device__ __forceinline__ void attend_block(const CacheView& c, const AttendArg
       have_acc = true;
     }
   }
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
+  l = rows_sum_f32(l);
   RKV_STAMP(7);
   if (wb >= we) last_round();
   after_stream();

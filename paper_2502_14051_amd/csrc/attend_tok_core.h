@@ -85,8 +85,7 @@ __device__ __forceinline__ void token_round(u32x4 (&kf)[2][4], u32x4 (&vr)[2][4]
   // online softmax of the 32 tokens (the one-pair case of softmax_pv)
   float mx = fmaxf(fmaxf(fmaxf(acc[0][0][0], acc[0][0][1]), fmaxf(acc[0][0][2], acc[0][0][3])),
                    fmaxf(fmaxf(acc[0][1][0], acc[0][1][1]), fmaxf(acc[0][1][2], acc[0][1][3])));
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  mx = rows_max_f32(mx);
   const float m_new = fmaxf(m, mx * sc);  // running max in the scaled log2 domain
   if (have_acc) {
     const float alpha = fast_exp2(m - m_new);
@@ -220,11 +219,12 @@ __device__ __forceinline__ void attend_tokens_block(const CacheView& c, const At
       if (!INDEXED && !PATCH && (uint32_t)(live >> (32 * i)) == 0u) continue;
       u32x4 kf[2][4], vr[2][4];
       const bf16_t* vt[2];
+      // tile x of the step takes its row offsets from row 2 i + x of the lanes: first from the half, then from its rows
+      const SwapPair hi32 = swap_rows32((uint32_t)(off >> 32)), lo32 = swap_rows32((uint32_t)off);
+      const SwapPair hi = swap_rows16(i == 0 ? hi32.a : hi32.b), lo = swap_rows16(i == 0 ? lo32.a : lo32.b);
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
-        const int src = 32 * i + 16 * x + hn;
-        const int64_t ofx = ((int64_t)__shfl((int)(off >> 32), src) << 32) |
-                            (uint32_t)__shfl((int)(off & 0xffffffff), src);
+        const int64_t ofx = ((int64_t)(x == 0 ? hi.a : hi.b) << 32) | (x == 0 ? lo.a : lo.b);
         const bf16_t* kt = c.k_pool + lane_off + ofx;
         vt[x] = c.v_pool + lane_off + ofx;
 #pragma unroll
@@ -246,8 +246,7 @@ __device__ __forceinline__ void attend_tokens_block(const CacheView& c, const At
       have_acc = true;
     }
   }
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
+  l = rows_sum_f32(l);
   after_stream();
   attend_merge<WAVES, 8>(c, a, unit, split, 0, O, m, l, smem, s_last, b, g, unit_read);
 }
