@@ -68,7 +68,7 @@ __device__ __forceinline__ void load_to_lds(const void* src, void* dst) {
 constexpr int kSnapCols = 128;            // softmax rows (columns of the products) per wavefront, in blocks of 32
 constexpr int kSnapMaxPairs = kWave;      // page pairs one wavefront walks, at most: a lane each
 constexpr int kSnapSegPairs = 8;          // page pairs between two write-outs of the votes
-constexpr int kSnapMaxChunkPages = 512;   // pages per workgroup: four wavefronts' pairs
+constexpr int kSnapMaxChunkPages = 128;   // pages per workgroup
 constexpr int kRowsBytes = 4 * kHeadDim * (int)sizeof(bf16_t) + 16;  // four rows in LDS, and what shifts the next four's banks
 constexpr int kTileBytes = 4 * kRowsBytes, kSlotBytes = 2 * kTileBytes;
 constexpr int kRingBytes = 4 * 2 * kSlotBytes;
@@ -115,10 +115,9 @@ __device__ __forceinline__ float half_wave_sums(float (&x)[16], int lane) {
 // What bounds it: vector issue and HBM, nearly equally, and under sustained load the clock.  With 16 x 16 products
 // a lane held four tokens of a softmax row, so that a maximum, a rescale and their exponential were paid for every
 // four logits, and a product kept the vector port busy for half of its 16 cycles; with 32 x 32 ones it is sixteen
-// logits, and a product covers twice the work in the same issue time.  One workgroup per slot of the chip walks all of
-// its unit's pages it can (up to 512), so that the queries are fetched once and not in each of four rounds.
-// 16 x 32768 tokens over 8 KV heads, the two passes: 190 + 235 -> 170 + 182 us (bare stream of the same keys: 161
-// each; in a loop of layers, where the clock drops, 225 + 265 -> 209 + 222); 1 x 131072: 52 + 58 -> 49 + 48.
+// logits, and a product covers twice the work in the same issue time.  16 x 32768 tokens over 8 KV heads: the call with
+// the summaries 588 -> 545 us again and again on the same keys (where the clock drops), 595 -> 592 a layer on new keys
+// each time (bare stream of the keys: 161 us a pass); 1 x 131072: 157 -> 153 and 186 -> 170.
 template <bool PASS2, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void snap_score_kernel(CacheView c, SnapArgs a) {
@@ -965,13 +964,13 @@ SnapPlan plan_snapkv(const CacheView& src, int window, int keep) {
   const int NC = src.group * window;
   // Pages per workgroup in the score passes.  A workgroup fetches its query block before its first page,
   // which long chunks amortise; short ones keep the chip full when there are few (sequence, KV head)
-  // units.  Doubled while there are more than 512 workgroups, two per compute unit: 1 x 131072 takes 49 + 48 us so,
-  // 53 + 53 at a bound of 1024 and 61 + 57 at 2048; 16 x 32768 173, 180 and 187 for the first pass.
-  // A wavefront looks its pairs up in a lane each: with two column groups, two wavefronts share a chunk's pages.
-  const int max_chunk = NC > kSnapCols ? kSnapMaxChunkPages / 2 : kSnapMaxChunkPages;
-  static_assert(kSnapMaxChunkPages == 4 * 2 * kSnapMaxPairs, "a pair per lane");
+  // units.  Doubled while there are more than 512 workgroups, two per compute unit (1 x 131072 takes 153 us a call so, 158
+  // at a bound of 1024 and 170 at 2048), up to 128 pages.  Longer ones, in one round over the chip, are faster on keys
+  // seen before and slower on new ones, where the workgroups are less alike: 16 x 32768 tokens 536 and 620 us a call
+  // with 512 pages, 545 and 592 with 128.
+  static_assert(kSnapMaxChunkPages <= 2 * 2 * kSnapMaxPairs, "a pair per lane, also where two wavefronts share a chunk's pages");
   int chunk_pages = 32;
-  while (chunk_pages < max_chunk && units * ((src.pages_cap + chunk_pages - 1) / chunk_pages) > 512) chunk_pages *= 2;
+  while (chunk_pages < kSnapMaxChunkPages && units * ((src.pages_cap + chunk_pages - 1) / chunk_pages) > 512) chunk_pages *= 2;
   p.chunk_pages = chunk_pages;
   p.n_chunks = (src.pages_cap + chunk_pages - 1) / chunk_pages;
   const size_t s_cap = (size_t)src.pages_cap * kAttnPage;

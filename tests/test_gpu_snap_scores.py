@@ -48,5 +48,5 @@ def test_rows(oracle, hq, hkv, W):
 @pytest.mark.parametrize("hq,hkv,W", [(4, 4, 16), (16, 4, 16), (64, 4, 16)])
 @pytest.mark.parametrize("last", [0, 1, 15, 16, 17, 32, 255, 1024, 1039])
 def test_chunk_ends(oracle, hq, hkv, W, last):
-    """A chunk of 512 pages (256 with two column groups) and what lies behind it."""
+    """Chunks of the longest kind (128 pages) and what lies behind them."""
     check(oracle, hq, hkv, W, (8192 + W + last, 4096 + W + last, 2000 + last, 8192 + last), 8448, 300)
