@@ -184,19 +184,6 @@ __device__ __forceinline__ float rows_sum_f32(float x) {
   return __uint_as_float(s.a) + __uint_as_float(s.b);
 }
 
-// Sum over the 64 lanes of a wavefront, in a fixed order; the last lane gets it.
-__device__ __forceinline__ float wave_sum_last_f32(float x) {
-#define RKV_DPP_SUM(ctrl, rows) x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, rows, 0xf, false))
-  RKV_DPP_SUM(0x111, 0xf);
-  RKV_DPP_SUM(0x112, 0xf);
-  RKV_DPP_SUM(0x114, 0xf);
-  RKV_DPP_SUM(0x118, 0xf);
-  RKV_DPP_SUM(0x142, 0xa);
-  RKV_DPP_SUM(0x143, 0xc);
-#undef RKV_DPP_SUM
-  return x;
-}
-
 // Device view of a cache (copied by value into kernel arguments).
 struct CacheView {
   int32_t batch, n_q_heads, n_kv_heads, group;

@@ -475,17 +475,31 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
   // The page that is receiving a token is always the sequence's last.  What the rows hold for it is stale: the last
   // wavefront, which has the fewest pages of its own, sums its score up from the page's old bounds folded with the new
   // key, or from the new key alone when the token opens the page (what memory holds for that column is then not
-  // looked at), one or two picked channels a lane, and the workgroup's last thread takes the page in its last round:
-  // still the last page in (round, thread) order.  The old bounds travel with the rows.  (Summed up by the wavefront
-  // whose run holds the page, on top of its rows, it kept the others waiting 0.5 of 23.7 us a layer at 16 x 4122 tokens.)
+  // looked at), and the workgroup's last thread takes the page in its last round: still the last page in
+  // (round, thread) order.  The sum is formed like every other page's, rows r, r + 8, ... by lane r and then the eight
+  // lanes, so that it equals what a later launch makes of the stored bounds, to the bit: pages that tie then are
+  // ranked alike.  The old bounds travel with the rows.
   const bool tail_wave = tp.page >= 0 && o_wave == (kWaves - 1) * (kWave / 8);
   const bool has_tail = tp.page >= 0 && tid == NT - 1;
+  // Lane l fetches rows l and 64 + l; rows beyond k1 count as below.  (The weight is read and then dropped: read under the
+  // condition, it has the compiler fetch the base pointer per lane from the kernel arguments, a round trip: 0.4 us a layer.)
+  const auto tail_row = [&](int j, float& w) {
+    const int jj = min(j, a.k1 - 1);
+    w = sh.s_wgt[jj];
+    if (j >= a.k1) w = 0.f;
+    return sh.s_chan[jj];
+  };
+  const int tail_rows = (a.k1 + 7) / 8 * 8;
   uint32_t tail_old[2] = {0u, 0u};
   if (tail_wave && tp.slot != 0) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int j = h * kWave + lane;
-      if (j < a.k1) tail_old[h] = ((sh.s_wgt[j] >= 0.f) ? a.kmax : a.kmin)[(rows + sh.s_chan[j]) * c.pages_cap + tp.page];
+      float w;
+      if (j < tail_rows) {
+        const int ch = tail_row(j, w);
+        tail_old[h] = (w >= 0.f ? a.kmax : a.kmin)[(rows + ch) * c.pages_cap + tp.page];
+      }
     }
   }
   // ---- s1: page scores.  Thread (o, r) = (tid / 8, tid % 8) takes the rows r, r + 8, ... of the picked
@@ -557,24 +571,36 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
         score[i] = mine;
       }
     }
-  }
-  if (tail_wave) {
-    float sum = 0.f;
+    if (tail_wave) {
+      float sum = 0.f;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int j = h * kWave + lane;
-      if (j < a.k1) {
-        const float w = sh.s_wgt[j];
-        float f = bf16_to_f32(tp.knew[sh.s_chan[j]]);
-        if (tp.slot != 0) {
-          const float fo = bf16_to_f32((bf16_t)use_late(tail_old[h]));
-          f = w >= 0.f ? fmaxf(fo, f) : fminf(fo, f);
+      for (int h = 0; h < 2; ++h) {
+        if (h * kWave >= a.k1) break;  // (the same for the whole launch, as the next one)
+        const int j = h * kWave + lane;
+        float w = 0.f, f = 0.f;
+        if (j < tail_rows) {
+          f = bf16_to_f32(tp.knew[tail_row(j, w)]);
+          if (tp.slot != 0) {
+            const float fo = bf16_to_f32((bf16_t)use_late(tail_old[h]));
+            f = w >= 0.f ? fmaxf(fo, f) : fminf(fo, f);
+          }
         }
-        sum = fmaf(w, f, sum);
+#pragma unroll
+        for (int t0 = 0; t0 < 8; t0 += 4) {
+          if (h * kWave + t0 * 8 >= a.k1) break;
+          float wt[4], ft[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            wt[t] = __shfl(w, r + (t0 + t) * 8);
+            ft[t] = __shfl(f, r + (t0 + t) * 8);
+          }
+#pragma unroll
+          for (int t = 0; t < 4; ++t) sum = fmaf(wt[t], ft[t], sum);
+        }
       }
+      sum = lanes8(sum);
+      if (has_tail) score[kRounds - 1] = sum;
     }
-    sum = wave_sum_last_f32(sum);
-    if (has_tail) score[kRounds - 1] = sum;
   }
   // the page of round i, and whether it is this thread's
   const auto page_of = [&](int i) { return has_tail && i == kRounds - 1 ? tp.page : i * NT + tid; };
