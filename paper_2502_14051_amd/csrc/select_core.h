@@ -95,41 +95,77 @@ __device__ __forceinline__ void score_rows8(const SelectArgs& a, const int* s_ch
   }
 }
 
-// The score of the page that is receiving a token (tp.page) is computed on its own by the first two
-// wavefronts from the page's old bounds and the new key, one picked channel per thread: the bound of
-// a channel is the old one folded with the new key's value, or the new value alone when the token
-// opens the page (whatever memory holds for that column is then not looked at).  Cheaper than
-// patching the packed rows in every wavefront that scores them.  In two parts, so that the lookup of
-// the old bound goes out before the caller's row loads and is used after them (one memory round trip
-// for both): tail_page_load returns the old bound's bits, tail_page_finish leaves the two wavefronts'
-// partial sums in out2[0..1]; the caller adds them (fixed order) after a barrier.
+// What the rows hold for a page that is receiving a token (tp.page) is stale.  Its score is computed on its own by the last
+// wavefront from the page's old bounds and the new key, one or two picked channels a lane: the bound of a channel is the
+// old one folded with the new key's value, or the new value alone when the token opens the page (whatever memory holds
+// for that column is then not looked at).  Cheaper than patching the rows in the wavefronts that read the page's run
+// (1.6 of 30.3 us a layer at 65536 tokens, 3 of 39.2 at 50000 with 120 channels).  In two parts, so that the lookup of the
+// old bounds goes out before the caller's row loads and is used after them (one memory round trip for both).
+//
+// tail_page_finish leaves sums to be added up in order behind a barrier, min(R, 128) of them in sh.s_abs.  Every other page is
+// summed up in R row groups, rows r, r + R, ... each in order, and then over the groups; these are the groups' sums, so
+// that the score equals what a later launch makes of the stored bounds, to the bit: pages that tie then are ranked alike.
+// ONE_GROUP: R is 1.
+struct TailRows {
+  uint32_t old[2], key[2];    // bf16 bits: the bounds of rows `lane` and 64 + `lane`, the new key at their channels
+  uint32_t old_pad, key_pad;  // of the row the padding reads: the last one, upper bound
+};
 template <int NT>
-__device__ __forceinline__ uint32_t tail_page_load(const SelectArgs& a, const int* s_chan, const float* s_wgt,
-                                                 int64_t rows, int pages_cap, const TailPatch& tp) {
-  const int tid = threadIdx.x;
-  uint32_t old = 0;
-  if (tp.page >= 0 && tp.slot != 0 && tid < a.k1)
-    old = ((s_wgt[tid] >= 0.f) ? a.kmax : a.kmin)[(rows + s_chan[tid]) * pages_cap + tp.page];
-  return old;
-}
-template <int NT>
-__device__ __forceinline__ void tail_page_finish(const SelectArgs& a, const int* s_chan, const float* s_wgt,
-                                                 const TailPatch& tp, uint32_t old, float* out2) {
-  const int tid = threadIdx.x;
-  if (tp.page < 0 || tid >= 2 * kWave) return;
-  float contrib = 0.f;
-  if (tid < a.k1) {
-    const float w = s_wgt[tid];
-    float f = bf16_to_f32(tp.knew[s_chan[tid]]);
-    if (tp.slot != 0) {
-      const float fo = bf16_to_f32((bf16_t)use_late(old));
-      f = (w >= 0.f) ? fmaxf(fo, f) : fminf(fo, f);
-    }
-    contrib = w * f;
-  }
+__device__ __forceinline__ TailRows tail_page_load(const SelectArgs& a, const SelectShared<NT>& sh, int64_t rows, int pages_cap,
+                                                   const TailPatch& tp) {
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  TailRows t = {{0u, 0u}, {0u, 0u}, 0u, 0u};
+  if (tp.page < 0 || wave != NT / kWave - 1) return t;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) contrib += __shfl_xor(contrib, off);
-  if (tid % kWave == 0) out2[tid / kWave] = contrib;
+  for (int h = 0; h < 2; ++h) {
+    const int j = h * kWave + lane;
+    if (j < a.k1) {
+      const int ch = sh.s_chan[j];
+      if (tp.slot != 0) t.old[h] = (sh.s_wgt[j] >= 0.f ? a.kmax : a.kmin)[(rows + ch) * pages_cap + tp.page];
+      t.key[h] = tp.knew[ch];
+    }
+  }
+  const int ch = sh.s_chan[a.k1 - 1];
+  if (tp.slot != 0) t.old_pad = a.kmax[(rows + ch) * pages_cap + tp.page];
+  t.key_pad = tp.knew[ch];
+  return t;
+}
+template <int NT, bool ONE_GROUP = false>
+__device__ __forceinline__ void tail_page_finish(const SelectArgs& a, SelectShared<NT>& sh, const TailPatch& tp,
+                                                 const TailRows& rows, int R) {
+  constexpr int kUnroll = ONE_GROUP ? 32 : 8;  // rows of a group whose operands are read together
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (tp.page < 0 || wave != NT / kWave - 1) return;
+  const auto fold = [&](uint32_t old, uint32_t key, bool upper) {
+    const float f = bf16_to_f32((bf16_t)key), fo = bf16_to_f32((bf16_t)use_late(old));
+    return tp.slot == 0 ? f : upper ? fmaxf(fo, f) : fminf(fo, f);
+  };
+  float* value = sh.s_abs;  // free since the channel pick ended
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int j = h * kWave + lane;
+    if (j < a.k1) value[j] = fold(rows.old[h], rows.key[h], sh.s_wgt[j] >= 0.f);
+  }
+  // (the exchange stays within the wavefront, whose LDS accesses keep their order)
+  __builtin_amdgcn_wave_barrier();
+  float sum[2] = {0.f, 0.f};  // row groups `lane` and 64 + `lane`
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h * kWave >= min(R, a.k1)) break;  // (the same for every lane)
+    for (int i = 0; i * R < a.k1; i += kUnroll) {
+#pragma unroll
+      for (int t = 0; t < kUnroll; ++t) {
+        const int j = ONE_GROUP ? i + t : h * kWave + lane + (i + t) * R, jj = ONE_GROUP ? j : min(j, kHeadDim - 1);
+        const float w = sh.s_wgt[jj], f = value[jj];
+        sum[h] = fmaf(j < a.k1 ? w : 0.f, j < a.k1 ? f : 0.f, sum[h]);
+      }
+    }
+  }
+  // groups of unequal length are filled up with the last row's upper bound, weight zero
+  if (a.k1 % R != 0) sum[0] = fmaf(0.f, fold(rows.old_pad, rows.key_pad, true), sum[0]);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) value[h * kWave + lane] = sum[h];
 }
 
 // lanes below this one whose bit is set
@@ -322,9 +358,7 @@ __device__ __forceinline__ int select_pages(const CacheView& c, const SelectArgs
   const int n_oct = (P + 7) / 8;
   const int64_t rows = (int64_t)unit * kHeadDim;
   float* out_scores = write_global ? a.out_scores : nullptr;
-  float* tail2 = sh.s_abs;  // free since the channel pick ended; [0..1]: the two halves of tp.page's score
-  // the old bounds of tp.page: requested ahead of the row loads, used after them
-  const uint32_t tail_old = tail_page_load<NT>(a, sh.s_chan, sh.s_wgt, rows, c.pages_cap, tp);
+  const TailRows tail = tail_page_load<NT>(a, sh, rows, c.pages_cap, tp);
   if (n_oct < NT) {
     int npow = 1;
     while (npow < n_oct) npow <<= 1;
@@ -336,15 +370,17 @@ __device__ __forceinline__ int select_pages(const CacheView& c, const SelectArgs
     if (o < n_oct)
       for (int jb = 0; jb < a.k1; jb += 8 * R)
         score_rows8(a, sh.s_chan, sh.s_wgt, rows, c.pages_cap, o, jb + r, jb, R, acc);
-    tail_page_finish<NT>(a, sh.s_chan, sh.s_wgt, tp, tail_old, tail2);
+    tail_page_finish<NT>(a, sh, tp, tail, R);
     RKV_STAMP(2);
 #pragma unroll
     for (int i = 0; i < 8; ++i) sh.partial[(r * npow + o) * 8 + i] = acc[i];
     __syncthreads();
     for (int p = tid; p < npow * 8; p += NT) {
+      const bool is_tail = p == tp.page;
+      const float* part = is_tail ? sh.s_abs : sh.partial + p;
+      const int step = is_tail ? 1 : npow * 8, n_part = is_tail ? min(R, kHeadDim) : R;
       float s = 0.f;
-      for (int rr = 0; rr < R; ++rr) s += sh.partial[rr * npow * 8 + p];
-      if (p == tp.page) s = tail2[0] + tail2[1];
+      for (int rr = 0; rr < n_part; ++rr) s += part[rr * step];
       if (p < n_oct * 8) {
         if (p < P && out_scores) out_scores[(int64_t)unit * c.pages_cap + p] = s;
         if (p >= P) s = -INFINITY;
@@ -355,8 +391,14 @@ __device__ __forceinline__ int select_pages(const CacheView& c, const SelectArgs
       }
     }
   } else {
-    tail_page_finish<NT>(a, sh.s_chan, sh.s_wgt, tp, tail_old, tail2);
-    __syncthreads();  // tail2 is read below
+    const auto keep = [&](int p, float s) {
+      if (p < P && out_scores) out_scores[(int64_t)unit * c.pages_cap + p] = s;
+      if (p >= P) s = -INFINITY;
+      else if (p >= P - n_rec) s = INFINITY;
+      const uint32_t key = f32_order_key(s);
+      keys[p] = key;
+      if (p < P) atomicAdd(&sh.hist[0][key >> 24], 1u);  // the first radix pass, counted on the way
+    };
     for (int o = tid; o < n_oct; o += NT) {
       float acc[8];
 #pragma unroll
@@ -364,18 +406,11 @@ __device__ __forceinline__ int select_pages(const CacheView& c, const SelectArgs
       for (int j0 = 0; j0 < a.k1; j0 += 8)
         score_rows8(a, sh.s_chan, sh.s_wgt, rows, c.pages_cap, o, j0, j0, 1, acc);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int p = o * 8 + i;
-        float s = acc[i];
-        if (p == tp.page) s = tail2[0] + tail2[1];
-        if (p < P && out_scores) out_scores[(int64_t)unit * c.pages_cap + p] = s;
-        if (p >= P) s = -INFINITY;
-        else if (p >= P - n_rec) s = INFINITY;
-        const uint32_t key = f32_order_key(s);
-        keys[p] = key;
-        if (p < P) atomicAdd(&sh.hist[0][key >> 24], 1u);  // the first radix pass, counted on the way
-      }
+      for (int i = 0; i < 8; ++i)
+        if (o * 8 + i != tp.page) keep(o * 8 + i, acc[i]);
     }
+    tail_page_finish<NT, true>(a, sh, tp, tail, 1);
+    if (tp.page >= 0 && tid == NT - kWave) keep(tp.page, sh.s_abs[0]);  // the thread that left it there
   }
   __syncthreads();
 
@@ -1060,23 +1095,24 @@ __device__ __forceinline__ void score_chunk(const CacheView& c, const SelectArgs
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
   // the page that is receiving a token, if it lies in this slice: scored on its own (see tail_page_load)
-  float* tail2 = sh.s_abs;  // free since the channel pick ended
   const int tail_local = tp.page >= 0 ? tp.page - o_begin * 8 : -1;
   const bool owns_tail = tail_local >= 0 && tail_local < n_runs * 8;  // same for the whole workgroup
   TailPatch mine = tp;
   if (!owns_tail) mine.page = -1;
-  const uint32_t tail_old = tail_page_load<NT>(a, sh.s_chan, sh.s_wgt, rows, c.pages_cap, mine);
+  const TailRows tail = tail_page_load<NT>(a, sh, rows, c.pages_cap, mine);
   if (o < n_runs)
     for (int jb = 0; jb < a.k1; jb += 8 * R)  // each slice of the rows has this one reader: streamed
       score_rows8<true>(a, sh.s_chan, sh.s_wgt, rows, c.pages_cap, o_begin + o, jb + r, jb, R, acc);
-  tail_page_finish<NT>(a, sh.s_chan, sh.s_wgt, mine, tail_old, tail2);
+  tail_page_finish<NT>(a, sh, mine, tail, R);
 #pragma unroll
   for (int i = 0; i < 8; ++i) sh.partial[(r * npow + o) * 8 + i] = acc[i];
   __syncthreads();
   for (int p = tid; p < n_runs * 8; p += NT) {
+    const bool is_tail = owns_tail && p == tail_local;
+    const float* part = is_tail ? sh.s_abs : sh.partial + p;
+    const int step = is_tail ? 1 : npow * 8, n_part = is_tail ? min(R, kHeadDim) : R;
     float s = 0.f;
-    for (int rr = 0; rr < R; ++rr) s += sh.partial[rr * npow * 8 + p];
-    if (owns_tail && p == tail_local) s = tail2[0] + tail2[1];
+    for (int rr = 0; rr < n_part; ++rr) s += part[rr * step];
     const int page = o_begin * 8 + p;
     if (page < P) {
       if (COHERENT)  // read back by another workgroup of this launch: write through, device scope

@@ -96,3 +96,19 @@ def test_places_and_channels(cap, tail, ps, k1, layout, slot0):
 @pytest.mark.parametrize("batch,hkv,layout", [(128, 1, CM), (129, 1, CM), (131, 3, CM), (500, 2, CM), (131, 1, TM)])
 def test_many_sequences(batch, hkv, layout):
     run(batch, hkv, 40, 39, 16, 32, layout, 0)
+
+
+# more pages than the register selection holds: scores through LDS, with eight-page runs for some of the threads, for all
+# of them, and more than one each
+@pytest.mark.parametrize("batch,hkv,cap,tail", [(4, 4, 2568, 2567), (4, 4, 2568, 300), (4, 4, 4088, 4087), (4, 4, 4104, 4103),
+                                                (257, 1, 1288, 1287), (257, 1, 2056, 2055)])
+@pytest.mark.parametrize("k1", [32, 81])
+def test_more_pages(batch, hkv, cap, tail, k1):
+    run(batch, hkv, cap, tail, 16, k1, CM, 0)
+
+
+# large summaries, scored by several workgroups: the receiving page in the last slot, and at either side of a share's edge
+@pytest.mark.parametrize("cap,tail,ps,k1", [(3232, 3231, 3, 81), (3232, 1616, 3, 81), (3232, 1615, 3, 81), (808, 807, 3, 128),
+                                            (4200, 4199, 2, 19), (8200, 8199, 1, 8), (8200, 20, 1, 9)])
+def test_score_launch(cap, tail, ps, k1):
+    run(4, 4, cap, tail, ps, k1, TM, 0)
