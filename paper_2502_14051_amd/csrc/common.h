@@ -105,20 +105,8 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
   return x;
 }
 
-// Minimum / maximum over the 64 lanes of a wavefront with the same lane moves (a lane that has no
-// source keeps its own value); every lane gets the result.
-__device__ __forceinline__ float wave_min_f32(float x) {
-#define RKV_DPP_MIN(ctrl, rows) \
-  x = fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), ctrl, rows, 0xf, false)))
-  RKV_DPP_MIN(0x111, 0xf);
-  RKV_DPP_MIN(0x112, 0xf);
-  RKV_DPP_MIN(0x114, 0xf);
-  RKV_DPP_MIN(0x118, 0xf);
-  RKV_DPP_MIN(0x142, 0xa);
-  RKV_DPP_MIN(0x143, 0xc);
-#undef RKV_DPP_MIN
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), kWave - 1));
-}
+// Maximum over the 64 lanes of a wavefront with the same lane moves (a lane that has no source keeps its own value);
+// every lane gets the result.
 __device__ __forceinline__ float wave_max_f32(float x) {
 #define RKV_DPP_MAX(ctrl, rows) \
   x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), ctrl, rows, 0xf, false)))
@@ -132,7 +120,7 @@ __device__ __forceinline__ float wave_max_f32(float x) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), kWave - 1));
 }
 
-// The same for unsigned words.
+// Minimum / maximum of unsigned words likewise.
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
 #define RKV_DPP_MIN(ctrl, rows) x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, ctrl, rows, 0xf, false))
   RKV_DPP_MIN(0x111, 0xf);
@@ -156,9 +144,10 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
 }
 
-// Exchanges between the four rows of 16 lanes, as register swaps (a lane permutation through LDS takes its round trip
-// every time: one sequence of 32768 tokens 229.3 -> 227.6 us for twelve layers, ragged ones 136.9 -> 136.0 for six).  After swap_rows16 of x with itself, .a holds the even row's value in both rows of a pair and .b the odd
-// row's; after swap_rows32, .a the lower half's in both halves and .b the upper half's.
+// Exchanges between the four rows of 16 lanes, as register swaps (a lane permutation through LDS takes its round
+// trip every time: one sequence of 32768 tokens 229.3 -> 227.6 us for twelve layers; batches stay within 0.5 %).
+// After swap_rows16 of x with itself, .a holds the even row's value in both rows of a pair and .b the odd row's;
+// after swap_rows32, .a the lower half's in both halves and .b the upper half's.
 struct SwapPair {
   uint32_t a, b;
 };
@@ -208,7 +197,8 @@ struct CacheView {
 // (Adding and looking with one atomic behind the stream, the last one to arrive storing, made 256 adds to neighbouring
 // words wait for each other in front of the merges: 0.8 of 23.8 us a layer at 16 sequences of 4122 tokens.)
 // read_slot: where the sequence's counter lies in the header's second half, in a line of its own for up to 128
-// sequences (adds to one line queue up: all in one line, the same launch took 25.2 us, so 22.2).
+// sequences (adds to one line queue up: all in one line, the same launch took 25.2 us, so 22.2).  More sequences lie
+// closer together, down to a word each; there are at most 8192, the words of that half (check_cache).
 __device__ __forceinline__ int read_slot(const CacheView& c, int b) {
   return b * (ROCKETKV_WS_HEADER_BYTES / 2 / (int)sizeof(uint32_t) / max(c.batch, 128));
 }

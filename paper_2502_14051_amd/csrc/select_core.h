@@ -37,10 +37,10 @@ struct SelectShared {
   uint32_t cnt0;
 };
 
-// exclusive prefix sum of one uint32 per thread over the NT-thread workgroup.  REUSE = false leaves
-// out the trailing barrier, for a caller that does not touch `wsum` again before its next barrier.
-// The wavefronts' totals are summed by a scan of their own, a lane each: walking the ones in front took a sixteen-wavefront
-// workgroup up to fifteen LDS reads one after the other.
+// exclusive prefix sum of one uint32 per thread over the NT-thread workgroup.  REUSE = false leaves out the
+// trailing barrier, for a caller that does not touch `wsum` again before its next barrier.  The wavefronts' totals
+// are summed by a scan of their own, a lane each: walking the ones in front took a sixteen-wavefront workgroup up
+// to fifteen LDS reads one after the other.
 template <int NT, bool REUSE = true>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum) {
   constexpr int kWaves = NT / kWave;
@@ -95,24 +95,25 @@ __device__ __forceinline__ void score_rows8(const SelectArgs& a, const int* s_ch
   }
 }
 
-// What the rows hold for a page that is receiving a token (tp.page) is stale.  Its score is computed on its own by the last
-// wavefront from the page's old bounds and the new key, one or two picked channels a lane: the bound of a channel is the
-// old one folded with the new key's value, or the new value alone when the token opens the page (whatever memory holds
-// for that column is then not looked at).  Cheaper than patching the rows in the wavefronts that read the page's run
-// (1.6 of 30.3 us a layer at 65536 tokens, 3 of 39.2 at 50000 with 120 channels).  In two parts, so that the lookup of the
-// old bounds goes out before the caller's row loads and is used after them (one memory round trip for both).
+// What the rows hold for a page that is receiving a token (tp.page) is stale.  Its score is computed on its own by
+// the last wavefront from the page's old bounds and the new key, one or two picked channels a lane: the bound of a
+// channel is the old one folded with the new key's value, or the new value alone when the token opens the page
+// (whatever memory holds for that column is then not looked at).  Cheaper than patching the rows in the wavefronts
+// that read the page's run (1.6 of 30.3 us a layer at 65536 tokens, 3 of 39.2 at 50000 with 120 channels).  In two
+// parts, so that the lookup of the old bounds goes out before the caller's row loads and is used after them (one
+// memory round trip for both).
 //
-// tail_page_finish leaves sums to be added up in order behind a barrier, min(R, 128) of them in sh.s_abs.  Every other page is
-// summed up in R row groups, rows r, r + R, ... each in order, and then over the groups; these are the groups' sums, so
-// that the score equals what a later launch makes of the stored bounds, to the bit: pages that tie then are ranked alike.
-// ONE_GROUP: R is 1.
+// tail_page_finish leaves sums to be added up in order behind a barrier, min(R, 128) of them in sh.s_abs.  Every
+// other page is summed up in R row groups, rows r, r + R, ... each in order, and then over the groups; these are
+// the groups' sums, so that the score equals what a later launch makes of the stored bounds, to the bit: pages that
+// tie then are ranked alike.  ONE_GROUP: R is 1.
 struct TailRows {
   uint32_t old[2], key[2];    // bf16 bits: the bounds of rows `lane` and 64 + `lane`, the new key at their channels
   uint32_t old_pad, key_pad;  // of the row the padding reads: the last one, upper bound
 };
 template <int NT>
-__device__ __forceinline__ TailRows tail_page_load(const SelectArgs& a, const SelectShared<NT>& sh, int64_t rows, int pages_cap,
-                                                   const TailPatch& tp) {
+__device__ __forceinline__ TailRows tail_page_load(const SelectArgs& a, const SelectShared<NT>& sh, int64_t rows,
+                                                   int pages_cap, const TailPatch& tp) {
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   TailRows t = {{0u, 0u}, {0u, 0u}, 0u, 0u};
   if (tp.page < 0 || wave != NT / kWave - 1) return t;
@@ -508,16 +509,17 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
   uint32_t* wcnt = whi + kWaves;                    // [kRounds][kWaves]
 
   // The page that is receiving a token is always the sequence's last.  What the rows hold for it is stale: the last
-  // wavefront, which has the fewest pages of its own, sums its score up from the page's old bounds folded with the new
-  // key, or from the new key alone when the token opens the page (what memory holds for that column is then not
-  // looked at), and the workgroup's last thread takes the page in its last round: still the last page in
-  // (round, thread) order.  The sum is formed like every other page's, rows r, r + 8, ... by lane r and then the eight
+  // wavefront, which has the fewest pages of its own, sums its score up from the page's old bounds folded with the
+  // new key, or from the new key alone when the token opens the page (what memory holds for that column is then not
+  // looked at), and the workgroup's last thread takes the page in its last round: still the last page in (round,
+  // thread) order.  The sum is formed like every other page's, rows r, r + 8, ... by lane r and then the eight
   // lanes, so that it equals what a later launch makes of the stored bounds, to the bit: pages that tie then are
   // ranked alike.  The old bounds travel with the rows.
   const bool tail_wave = tp.page >= 0 && o_wave == (kWaves - 1) * (kWave / 8);
   const bool has_tail = tp.page >= 0 && tid == NT - 1;
-  // Lane l fetches rows l and 64 + l; rows beyond k1 count as below.  (The weight is read and then dropped: read under the
-  // condition, it has the compiler fetch the base pointer per lane from the kernel arguments, a round trip: 0.4 us a layer.)
+  // Lane l fetches rows l and 64 + l; rows beyond k1 count as below.  (The weight is read and then dropped: read
+  // under the condition, it has the compiler fetch the base pointer per lane from the kernel arguments, a round
+  // trip: 0.4 us a layer.)
   const auto tail_row = [&](int j, float& w) {
     const int jj = min(j, a.k1 - 1);
     w = sh.s_wgt[jj];
@@ -684,10 +686,10 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
       khi = max(max(max(khi, h.x), max(h.y, h.z)), h.w);
     }
     const float lo = f32_from_order_key(klo), hi = f32_from_order_key(khi);  // (no finite score: lo is a NaN)
-    // bins, and bins per lane of a scanning wavefront.  Every wavefront walks its lanes' bins one after
-    // the other, so fewer bins make a shorter scan and more pages per bin a longer exact rank; with at
-    // most two pages per thread 256 bins measured 0.4 us ahead of 1024 at the benchmark shape, with five (one sequence
-    // of 32768 tokens) 512 are 0.4 us ahead of 1024.
+    // bins, and bins per lane of a scanning wavefront.  Every wavefront walks its lanes' bins one after the other,
+    // so fewer bins make a shorter scan and more pages per bin a longer exact rank; with at most two pages per
+    // thread 256 bins measured 0.4 us ahead of 1024 at the benchmark shape, with five (one sequence of 32768
+    // tokens) 512 are 0.4 us ahead of 1024.
     constexpr int NB = ROUNDS <= 2 ? 256 : 512, BPL = NB / kWave;
     // (any positive factor makes monotone bins, so the hardware's reciprocal will do)
     const float scale = (float)(NB - 2) * __builtin_amdgcn_rcpf(hi - lo);

@@ -86,8 +86,8 @@ __device__ __forceinline__ void lds_store(float* dst, float x) {
 
 // A lane's values x[0 .. 15], each to be summed over the 32 lanes of its half wavefront: lane l is left with the
 // total of x[8 (l / 16 % 2) + 4 (l / 8 % 2) + 2 (l / 4 % 2) + l / 2 % 2], which the lanes below and above it in a
-// pair share.  Every step halves the values a lane holds, so that 38 instructions do it; the order of the
-// additions is fixed.
+// pair share.  Every step halves the values a lane holds, so that 38 instructions do it; the order of the additions
+// is fixed.
 __device__ __forceinline__ float half_wave_sums(float (&x)[16], int lane) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) {  // rows of 16 lanes: an even row keeps x[j], an odd one x[j + 8]
@@ -115,9 +115,11 @@ __device__ __forceinline__ float half_wave_sums(float (&x)[16], int lane) {
 // What bounds it: vector issue and HBM, nearly equally, and under sustained load the clock.  With 16 x 16 products
 // a lane held four tokens of a softmax row, so that a maximum, a rescale and their exponential were paid for every
 // four logits, and a product kept the vector port busy for half of its 16 cycles; with 32 x 32 ones it is sixteen
-// logits, and a product covers twice the work in the same issue time.  16 x 32768 tokens over 8 KV heads: the call with
-// the summaries 588 -> 545 us again and again on the same keys (where the clock drops), 595 -> 592 a layer on new keys
-// each time (bare stream of the keys: 161 us a pass); 1 x 131072: 157 -> 153 and 186 -> 170.
+// logits, and a product covers twice the work in the same issue time.  The call with the summaries, 8 KV heads, us
+// on keys that are in no cache / again and again on the same keys: 16 x 32768 tokens 582 -> 548 / 579 -> 547, 4 x
+// 32768 175 -> 168 / 171 -> 162, 1 x 131072 164 -> 154 / 156 -> 152, 1 x 32768 81.5 -> 78 / 74.2 -> 74.3, 1 x 8192
+// 56 -> 51 / 53.5 -> 48.8.  Under the long set-up loop of the benchmark, where the clock drops, 16 x 32768 stays at
+// 580-595 a layer.  (Bare stream of 16 x 32768 keys: 161 us a pass.)
 template <bool PASS2, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void snap_score_kernel(CacheView c, SnapArgs a) {
@@ -171,14 +173,16 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
     a1 = __builtin_amdgcn_readlane(pp1, it & (kWave - 1));
     if (it >= n_pairs) a0 = a1 = -1;
   };
-  // Both passes load the keys with the streaming hint.  (Pass 2 used to do without, for the sake of the gather that
-  // follows and finds part of the keys in the last-level cache then: 222 + 98 us at 16 x 32768 tokens, 182 + 109 with
-  // the hint; 1 x 131072: 53 + 16, 48 + 15.)
+  // Both passes load the keys with the streaming hint.  Without it in pass 2 the gather that follows finds part of
+  // the keys in the last-level cache, which gives less than the hint gives the pass: pass + gather on keys not scored
+  // before, 16 x 32768 tokens 239 + 100 us without, 215 + 117 with; 1 x 32768 22.5 + 11.4 and 20.1 + 12.3.  The call
+  // with the summaries, without / with: 16 x 32768 570 / 548, 4 x 32768 176 / 168, 1 x 131072 160 / 154, 1 x 32768
+  // 80.3 / 78, 1 x 8192 51.1 / 50.7; only one prompt of 32768 scored over and over is ahead without (73.8 / 74.3).
   constexpr int kPolicyStream = 2;  // the "nt" bit of the load's cache policy
-  // Load instruction j of a tile brings in token rows 4j .. 4j+3 (1 KiB, whole cache lines); lane l
-  // lands 16 l bytes behind the instruction's place in the slot, and fetches the 16-byte chunk that
-  // belongs there: chunk x of row 4j + i stands at position x ^ 4i, and the instructions' places are 16 bytes
-  // more than a KiB apart, so that the reads below (16 rows at one chunk position) spread over all LDS banks.
+  // Load instruction j of a tile brings in token rows 4j .. 4j+3 (1 KiB, whole cache lines); lane l lands 16 l
+  // bytes behind the instruction's place in the slot, and fetches the 16-byte chunk that belongs there: chunk x of
+  // row 4j + i stands at position x ^ 4i, and the instructions' places are 16 bytes more than a KiB apart, so that
+  // the reads below (16 rows at one chunk position) spread over all LDS banks.
   const uint32_t dma_off = (uint32_t)((lane >> 4) * kHeadDim + ((lane & 15) ^ (lane >> 4) * 4) * 8) * sizeof(bf16_t);
   const auto fetch = [&](const char* rows, unsigned char* dst, auto policy) {
 #pragma unroll
@@ -272,8 +276,8 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
   // The leading run of pairs that need no mask takes the hot variant: none of the wavefront's pages
   // absent, and the pair's last token inside the prefix, so that every window row sees all of it.
   int n_hot = 0;
-  // (A pair at or beyond the chunk's end is not an absent one: taken for one, it sent every pair of a wavefront down the
-  // masked path in the last chunk of most prompts: 25 us of pass 2 over 16 x 32768 tokens.)
+  // (A pair at or beyond the chunk's end is not an absent one: taken for one, it sent every pair of a wavefront down
+  // the masked path in the last chunk of most prompts: 25 us of pass 2 over 16 x 32768 tokens.)
   const bool gone0 = first_page(lane) < p_end && pp0 < 0, gone1 = first_page(lane) + 1 < p_end && pp1 < 0;
   if (__ballot(lane < n_pairs && (gone0 || gone1)) == 0ull) {
     // pairs whose second page p has p * 16 + 15 <= L, i.e. p <= (L - 15) / 16, and lies below p_end
@@ -356,13 +360,15 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
       invZ[cb] = st2.y;
     }
   }
-  const char* q_rows = reinterpret_cast<const char*>(a.qobs + ((int64_t)b * c.n_q_heads + (int64_t)g * c.group) * a.W * kHeadDim);
+  const char* q_rows =
+      reinterpret_cast<const char*>(a.qobs + ((int64_t)b * c.n_q_heads + (int64_t)g * c.group) * a.W * kHeadDim);
   for (int cg = 0; cg < a.CG; ++cg) {
     if (cg > 0) __syncthreads();  // the blocks of the group before have been read
 #pragma unroll
     for (int h = 0; h < (NB + 1) / 2; ++h) {
       const int x = h * 4 + wave, block = cg * (kSnapCols / 16) + x;
-      if (block * 16 < a.NC) fetch(q_rows + (int64_t)block * 16 * kHeadDim * sizeof(bf16_t), block_at(x), std::integral_constant<int, 0>{});
+      if (block * 16 < a.NC)
+        fetch(q_rows + (int64_t)block * 16 * kHeadDim * sizeof(bf16_t), block_at(x), std::integral_constant<int, 0>{});
     }
     if (cg == 0) {
       issue(0);
@@ -387,7 +393,8 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
   issue(1);
   if (n_hot > 0) hot_pairs(n_hot);
   for (int it = n_hot; it < n_pairs; ++it) masked_pair(it);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last refills (unused) land before the workgroup's LDS is given back
+  // the last refills (unused) land before the workgroup's LDS is given back
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (PASS2) return;
   // ---- pass 1: merge statistics over the half wavefronts and the wavefronts, and hand the chunk's partial out
   float (*sM)[kSnapCols] = reinterpret_cast<float (*)[kSnapCols]>(s_out);
@@ -962,12 +969,12 @@ SnapPlan plan_snapkv(const CacheView& src, int window, int keep) {
   SnapPlan p;
   const size_t units = (size_t)src.batch * src.n_kv_heads;
   const int NC = src.group * window;
-  // Pages per workgroup in the score passes.  A workgroup fetches its query block before its first page,
-  // which long chunks amortise; short ones keep the chip full when there are few (sequence, KV head)
-  // units.  Doubled while there are more than 512 workgroups, two per compute unit (1 x 131072 takes 153 us a call so, 158
-  // at a bound of 1024 and 170 at 2048), up to 128 pages.  Longer ones, in one round over the chip, are faster on keys
-  // seen before and slower on new ones, where the workgroups are less alike: 16 x 32768 tokens 536 and 620 us a call
-  // with 512 pages, 545 and 592 with 128.
+  // Pages per workgroup in the score passes.  A workgroup fetches its query block before its first page, which long
+  // chunks amortise; short ones keep the chip full when there are few (sequence, KV head) units.  Doubled while
+  // there are more than 512 workgroups, two per compute unit (1 x 131072 takes 153 us a call so, 158 at a bound of
+  // 1024 and 170 at 2048), up to 128 pages.  Longer ones, in one round over the chip, are faster on keys seen
+  // before and slower on new ones, where the workgroups are less alike: 16 x 32768 tokens 536 us a call on the same
+  // keys and 620 a layer in the benchmark's set-up loop with 512 pages, 545 and 592 with 128.
   static_assert(kSnapMaxChunkPages <= 2 * 2 * kSnapMaxPairs, "a pair per lane, also where two wavefronts share a chunk's pages");
   int chunk_pages = 32;
   while (chunk_pages < kSnapMaxChunkPages && units * ((src.pages_cap + chunk_pages - 1) / chunk_pages) > 512) chunk_pages *= 2;

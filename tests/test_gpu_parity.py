@@ -328,16 +328,20 @@ DECODE_CASES = [
     ("tiny", dict(n_q_heads=2, n_kv_heads=1, context=32768 * 16 - 5, token_budget=4096, n_heavy=32), None, 1, False),
     # more (sequence, KV head) units than compute units: the four-wavefront launch geometry
     ("tiny", dict(batch=40, n_q_heads=32, n_kv_heads=8, context=1100, token_budget=512, n_heavy=4), None, 0, True),
-    # the page counts at which the selection changes its form, on either side of each step: two and five
-    # pages per thread in registers, then scores through LDS (512-thread workgroups: 1024 / 2560 pages) ...
+    # the page counts at which the selection changes its form, on either side of each step: one, two and five pages per
+    # thread in registers, then scores through LDS (512-thread workgroups: 512 / 1024 / 2560 pages) ...
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=512 * 16, token_budget=1024, n_heavy=16), None, 0, False),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=513 * 16 - 3, token_budget=1024, n_heavy=16), None, 1, True),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=1024 * 16, token_budget=1024, n_heavy=16), None, 0, False),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=1025 * 16 - 3, token_budget=1024, n_heavy=16), None, 1, True),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=2560 * 16, token_budget=1024, n_heavy=16), None, 0, True),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=2561 * 16 - 9, token_budget=1024, n_heavy=16), None, 2, False),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=8192 * 16, token_budget=2048, n_heavy=16), None, 0, False),
     # ... and the same steps for the 256-thread workgroups of launches with more than 256 units
-    # (512 / 1280 pages; `tile`: the host generator draws a third of the batch and the rest are copies,
+    # (256 / 512 / 1280 pages; `tile`: the host generator draws a third of the batch and the rest are copies,
     # which keeps it to seconds at 264 units)
+    ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=256 * 16, token_budget=512, n_heavy=4), None, 0, False),
+    ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=257 * 16 - 1, token_budget=512, n_heavy=4), None, 1, False),
     ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=512 * 16, token_budget=512, n_heavy=4), None, 0, False),
     ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=513 * 16 - 1, token_budget=512, n_heavy=4), None, 1, False),
     ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=1280 * 16, token_budget=512, n_heavy=4), None, 0, False),
