@@ -970,14 +970,21 @@ SnapPlan plan_snapkv(const CacheView& src, int window, int keep) {
   const size_t units = (size_t)src.batch * src.n_kv_heads;
   const int NC = src.group * window;
   // Pages per workgroup in the score passes.  A workgroup fetches its query block before its first page, which long
-  // chunks amortise; short ones keep the chip full when there are few (sequence, KV head) units.  Doubled while
-  // there are more than 512 workgroups, two per compute unit (1 x 131072 takes 153 us a call so, 158 at a bound of
+  // chunks amortise; short ones keep the chip full when there are few (sequence, KV head) units.
+  // Up to 32 pages: doubled while there are more than 256 workgroups, one per compute unit.  With 32 pages from the
+  // start a short prompt left most of the chip idle.  us a call with the summaries, 32 pages / by this rule, 8 KV
+  // heads: 1 x 2048 tokens 43.9 / 37.0, 1 x 4100 46.7 / 41.2, 1 x 8192 51.4 / 48.8, 2 x 4096 47.4 / 43.3; with 64
+  // query heads 1 x 5000 56.5 / 47.4.  Why one and not two per compute unit: 1 x 12000 takes 51.5 with 188 workgroups of
+  // 32 pages, 53.4 with 376 of 16; 4 heads 1 x 18000 45.1 with 141, 46.4 with 282.
+  // Beyond: doubled while there are more than 512 (1 x 131072 takes 153 us a call so, 158 at a bound of
   // 1024 and 170 at 2048), up to 128 pages.  Longer ones, in one round over the chip, are faster on keys seen
   // before and slower on new ones, where the workgroups are less alike: 16 x 32768 tokens 536 us a call on the same
   // keys and 620 a layer in the benchmark's set-up loop with 512 pages, 545 and 592 with 128.
   static_assert(kSnapMaxChunkPages <= 2 * 2 * kSnapMaxPairs, "a pair per lane, also where two wavefronts share a chunk's pages");
-  int chunk_pages = 32;
-  while (chunk_pages < kSnapMaxChunkPages && units * ((src.pages_cap + chunk_pages - 1) / chunk_pages) > 512) chunk_pages *= 2;
+  const auto workgroups = [&](int pages) { return units * ((src.pages_cap + pages - 1) / pages); };
+  int chunk_pages = 8;  // a pair for each of four wavefronts
+  while (chunk_pages < 32 && workgroups(chunk_pages) > 256) chunk_pages *= 2;
+  while (chunk_pages < kSnapMaxChunkPages && workgroups(chunk_pages) > 512) chunk_pages *= 2;
   p.chunk_pages = chunk_pages;
   p.n_chunks = (src.pages_cap + chunk_pages - 1) / chunk_pages;
   const size_t s_cap = (size_t)src.pages_cap * kAttnPage;

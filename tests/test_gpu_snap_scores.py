@@ -50,3 +50,11 @@ def test_rows(oracle, hq, hkv, W):
 def test_chunk_ends(oracle, hq, hkv, W, last):
     """Chunks of the longest kind (128 pages) and what lies behind them."""
     check(oracle, hq, hkv, W, (8192 + W + last, 4096 + W + last, 2000 + last, 8192 + last), 8448, 300)
+
+
+@pytest.mark.parametrize("hq,hkv,W", [(2, 2, 16), (16, 2, 16), (4, 1, 32)])
+@pytest.mark.parametrize("cap,chunk", [(512, 8), (520, 16), (1024, 16), (1032, 32)])
+def test_short_chunks(oracle, hq, hkv, W, cap, chunk):
+    """Capacities at which four units' workgroups are just as many as compute units, and the next longer ones."""
+    t = 16 * chunk  # tokens a workgroup scores
+    check(oracle, hq, hkv, W, tuple(x + W for x in (3 * t, 3 * t + 1, 5 * t - 1, 4 * t + 17))[:4 // hkv], cap, 200)
