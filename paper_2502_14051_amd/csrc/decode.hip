@@ -22,8 +22,9 @@ constexpr size_t kStageBytes = 2 * kHeadDim * sizeof(bf16_t);  // staged new key
 constexpr size_t kSeqCounterOff = ROCKETKV_WS_HEADER_BYTES / 2;  // per-sequence arrival counters
 
 // CB: channel blocks of the output a workgroup computes (8: all; 4: the unit's channels are divided
-// between two workgroups, see attend_block); blockIdx.y counts (list split, channel share) pairs.
-template <int WAVES, bool APPEND, bool STREAM_K, int CB>
+// between two workgroups, see attend_block); blockIdx.y counts (list split, channel share) pairs.  ROUNDS: the
+// selection's form (select_rounds).
+template <int WAVES, bool APPEND, bool STREAM_K, int CB, int ROUNDS>
 __global__ __launch_bounds__(WAVES* kWave) __attribute__((amdgpu_waves_per_eu(2)))
 void hsa_decode_kernel(CacheView c, SelectArgs sa, AttendArgs aa, AppendArgs ap, uint32_t* seq_counters) {
   constexpr int NT = WAVES * kWave;
@@ -126,7 +127,7 @@ void hsa_decode_kernel(CacheView c, SelectArgs sa, AttendArgs aa, AppendArgs ap,
       }
     }
   }
-  select_pages<NT>(c, sa, unit, n, sh, keys, list, first, tp);
+  select_pages<NT, ROUNDS>(c, sa, unit, n, sh, keys, list, first, tp);
   if (kBoundsFromRows && from_rows) {
     float mx = -INFINITY, mn = INFINITY;
 #pragma unroll
@@ -227,21 +228,30 @@ hipError_t launch_hsa_decode_fused(const CacheView& c, const SelectArgs& sa, con
   const dim3 grid(c.batch * c.n_kv_heads, plan.n_split * plan.n_csplit);
   const bool append = ap.k_new != nullptr;
   const bool stream_k = wants_stream_k(c, sa.row_len);
-#define RKV_LAUNCH_DECODE(W, A, S, CB) \
-  hipLaunchKernelGGL((hsa_decode_kernel<W, A, S, CB>), grid, dim3(W * kWave), smem, st, c, sa, a, ap, seq_counters)
-#define RKV_LAUNCH_DECODE_S(W, A) \
-  do { if (stream_k) RKV_LAUNCH_DECODE(W, A, true, 8); else RKV_LAUNCH_DECODE(W, A, false, 8); } while (0)
-  if (plan.n_csplit == 2) {
-    // (eight wavefronts by the plan.  K tiles are read by both workgroups of a pair: plain loads, so that
-    // the second reader finds them in L2; with the streaming hint it does not, measured 2.7 us slower.)
-    if (append) RKV_LAUNCH_DECODE(8, true, false, 4); else RKV_LAUNCH_DECODE(8, false, false, 4);
-  } else if (plan.waves == 8) {
-    if (append) RKV_LAUNCH_DECODE_S(8, true); else RKV_LAUNCH_DECODE_S(8, false);
-  } else {
-    if (append) RKV_LAUNCH_DECODE_S(4, true); else RKV_LAUNCH_DECODE_S(4, false);
-  }
-#undef RKV_LAUNCH_DECODE_S
-#undef RKV_LAUNCH_DECODE
+  const auto launch = [&](auto waves, auto with_append, auto streamed, auto blocks) {
+    constexpr int W = decltype(waves)::value, CB = decltype(blocks)::value;
+    constexpr bool A = decltype(with_append)::value, S = decltype(streamed)::value;
+    with_select_rounds(c.pages_cap, W * kWave, [&](auto rounds) {
+      hipLaunchKernelGGL((hsa_decode_kernel<W, A, S, CB, decltype(rounds)::value>), grid, dim3(W * kWave), smem, st, c, sa, a,
+                         ap, seq_counters);
+    });
+  };
+  const auto form = [&](auto with_append) {
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr std::integral_constant<int, 8> eight{};
+    constexpr std::integral_constant<int, 4> four{};
+    if (plan.n_csplit == 2) {
+      // (eight wavefronts by the plan.  K tiles are read by both workgroups of a pair: plain loads, so that
+      // the second reader finds them in L2; with the streaming hint it does not, measured 2.7 us slower.)
+      launch(eight, with_append, no, four);
+    } else if (plan.waves == 8) {
+      if (stream_k) launch(eight, with_append, yes, eight); else launch(eight, with_append, no, eight);
+    } else {
+      if (stream_k) launch(four, with_append, yes, eight); else launch(four, with_append, no, eight);
+    }
+  };
+  if (append) form(std::true_type{}); else form(std::false_type{});
   return hipGetLastError();
 }
 

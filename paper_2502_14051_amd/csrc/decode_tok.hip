@@ -21,8 +21,9 @@ constexpr size_t kTokStageBytes = 2 * kHeadDim * sizeof(bf16_t);  // staged new 
 }  // namespace
 
 // `c`: the cache (pools, its own paging, its lengths).  `lc`: what Step 2 works on, i.e. lengths, page
-// size and page capacity of the logical sequence (equal to `c` without an index).
-template <int WAVES, bool APPEND, bool INDEXED>
+// size and page capacity of the logical sequence (equal to `c` without an index).  ROUNDS: the selection's form
+// (select_rounds).
+template <int WAVES, bool APPEND, bool INDEXED, int ROUNDS>
 __global__ __launch_bounds__(WAVES* kWave) __attribute__((amdgpu_waves_per_eu(2)))
 void hsa_decode_tok_kernel(CacheView c, CacheView lc, SelectArgs sa, AttendArgs aa, TokenRun t, AppendArgs ap,
                            uint32_t* seq_counters) {
@@ -84,7 +85,7 @@ void hsa_decode_tok_kernel(CacheView c, CacheView lc, SelectArgs sa, AttendArgs 
     old_max = ap.kmax[sum_off];
     old_min = ap.kmin[sum_off];
   }
-  select_pages<NT>(lc, sa, unit, n, sh, keys, list, split == 0, tp);
+  select_pages<NT, ROUNDS>(lc, sa, unit, n, sh, keys, list, split == 0, tp);
   __syncthreads();  // list complete; the selection scratch is dead and becomes the merge buffer
   if (APPEND && tid == 0) report_read(seq_counters, read_slot(c, b));
   auto check = [&]() {
@@ -161,17 +162,21 @@ hipError_t launch_hsa_decode_tok_fused(const CacheView& c, const LogicalView* lv
   const size_t smem = fused_decode_tok_lds_bytes(lc, sa.row_len, plan);
   const dim3 grid(c.batch * c.n_kv_heads, plan.n_split);
   const bool append = ap.k_new != nullptr;
-#define RKV_LAUNCH_TOK(W, A, I)                                                                              \
-  hipLaunchKernelGGL((hsa_decode_tok_kernel<W, A, I>), grid, dim3(W * kWave), smem, st, c, lc, sa, a, t, ap, \
-                     seq_counters)
-  if (plan.waves == 8) {
-    if (append) { if (lv) RKV_LAUNCH_TOK(8, true, true); else RKV_LAUNCH_TOK(8, true, false); }
-    else        { if (lv) RKV_LAUNCH_TOK(8, false, true); else RKV_LAUNCH_TOK(8, false, false); }
-  } else {
-    if (append) { if (lv) RKV_LAUNCH_TOK(4, true, true); else RKV_LAUNCH_TOK(4, true, false); }
-    else        { if (lv) RKV_LAUNCH_TOK(4, false, true); else RKV_LAUNCH_TOK(4, false, false); }
-  }
-#undef RKV_LAUNCH_TOK
+  const auto launch = [&](auto waves, auto with_append, auto indexed) {
+    constexpr int W = decltype(waves)::value;
+    constexpr bool A = decltype(with_append)::value, I = decltype(indexed)::value;
+    with_select_rounds(lc.pages_cap, W * kWave, [&](auto rounds) {
+      hipLaunchKernelGGL((hsa_decode_tok_kernel<W, A, I, decltype(rounds)::value>), grid, dim3(W * kWave), smem, st, c, lc, sa,
+                         a, t, ap, seq_counters);
+    });
+  };
+  const auto form = [&](auto waves, auto with_append) {
+    if (lv) launch(waves, with_append, std::true_type{}); else launch(waves, with_append, std::false_type{});
+  };
+  constexpr std::integral_constant<int, 8> eight{};
+  constexpr std::integral_constant<int, 4> four{};
+  if (plan.waves == 8) { if (append) form(eight, std::true_type{}); else form(eight, std::false_type{}); }
+  else                 { if (append) form(four, std::true_type{}); else form(four, std::false_type{}); }
   return hipGetLastError();
 }
 

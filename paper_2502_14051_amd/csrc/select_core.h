@@ -11,6 +11,8 @@
 // the one-barrier radix passes and the lane-shift scans.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace rkv {
@@ -320,24 +322,15 @@ __device__ __forceinline__ void radix_threshold(const uint32_t* keys, int P, int
   need_eq = k;
 }
 
-template <int NT, int ROUNDS>
-__device__ __forceinline__ int select_pages_small(const CacheView& c, const SelectArgs& a, int unit, int n,
-                                                  SelectShared<NT>& sh, uint32_t* keys, int32_t* list_lds,
-                                                  bool write_global, const TailPatch& tp);
-
 // Step 2, second half for a sequence of n tokens: page scores from the picked summary rows, exact
 // top-kp pages.  `keys` is LDS scratch of ceil8(pages_cap) words.  The ascending list goes to
 // `list_lds` (if not null, kp entries) and, when `write_global`, to a.out_pages / a.out_pages2 (-1
 // padded) and the optional score output.  Returns kp.  Ends WITHOUT a final barrier: the caller
 // synchronises before reading `list_lds`.
 template <int NT>
-__device__ __forceinline__ int select_pages(const CacheView& c, const SelectArgs& a, int unit, int n,
-                                            SelectShared<NT>& sh, uint32_t* keys, int32_t* list_lds,
-                                            bool write_global, const TailPatch& tp) {
-  // (the same for the whole launch)
-  if (c.pages_cap <= NT) return select_pages_small<NT, 1>(c, a, unit, n, sh, keys, list_lds, write_global, tp);
-  if (c.pages_cap <= 2 * NT) return select_pages_small<NT, 2>(c, a, unit, n, sh, keys, list_lds, write_global, tp);
-  if (c.pages_cap <= 5 * NT) return select_pages_small<NT, 5>(c, a, unit, n, sh, keys, list_lds, write_global, tp);
+__device__ __forceinline__ int select_pages_any(const CacheView& c, const SelectArgs& a, int unit, int n,
+                                                SelectShared<NT>& sh, uint32_t* keys, int32_t* list_lds,
+                                                bool write_global, const TailPatch& tp) {
   const int tid = threadIdx.x;
   const int ps = c.page_size;
   int P = (n + ps - 1) / ps;
@@ -456,7 +449,7 @@ __device__ __forceinline__ int select_pages(const CacheView& c, const SelectArgs
 }
 
 // Step 2, second half, for caches of at most ROUNDS * NT pages (every fused decode launch of the usual
-// shapes): the same result as select_pages, arranged for latency.  The routine sits in front of the
+// shapes): the same result as select_pages_any, arranged for latency.  The routine sits in front of the
 // K/V stream with HBM idle, so what counts is the number of dependent steps, not the work:
 //   - eight neighbouring lanes share an eight-page run and split the picked rows between them; the
 //     row sums meet in three lane-exchange steps (no LDS, no barrier) and lane r keeps page r of the
@@ -470,7 +463,7 @@ __device__ __forceinline__ int select_pages(const CacheView& c, const SelectArgs
 //     LDS atomics on one address), value bins spread them;
 //   - scores without a finite range, or more than 64 pages in the threshold's bin, go through the
 //     radix passes of the general routine instead.
-// Ends WITHOUT a final barrier, like select_pages.
+// Ends WITHOUT a final barrier, like select_pages_any.
 template <int NT, int ROUNDS>
 __device__ __forceinline__ int select_pages_small(const CacheView& c, const SelectArgs& a, int unit, int n,
                                                   SelectShared<NT>& sh, uint32_t* keys, int32_t* list_lds,
@@ -824,6 +817,37 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
   return kp;
 }
 
+// Step 2, second half, with the form chosen by the cache's capacity: ROUNDS of select_rounds().  The fused kernels have
+// it as a template parameter and are instantiated per form.  With all forms behind branches in one kernel the longest
+// one set the registers of them all, and adding the forms of three and four rounds cost the others 4 %.  us a layer,
+// branches over 1, 2, 5 rounds / a kernel per form over 1, 2, 3, 4, 5: one sequence of 4096 tokens (one round) 15.1 /
+// 14.7, of 16000 (two) 16.8 / 16.5, of 24000 (three) 19.2 / 18.0, of 32000 (four) 19.9 / 19.2, four of 24000 20.2 / 19.0,
+// 16 of 4122 22.9 / 22.9.
+__host__ __device__ constexpr int select_rounds(int pages_cap, int nt) {
+  return pages_cap <= 5 * nt ? (pages_cap + nt - 1) / nt : 0;
+}
+
+template <int NT, int ROUNDS>
+__device__ __forceinline__ int select_pages(const CacheView& c, const SelectArgs& a, int unit, int n,
+                                            SelectShared<NT>& sh, uint32_t* keys, int32_t* list_lds,
+                                            bool write_global, const TailPatch& tp) {
+  if constexpr (ROUNDS == 0) return select_pages_any<NT>(c, a, unit, n, sh, keys, list_lds, write_global, tp);
+  else return select_pages_small<NT, ROUNDS>(c, a, unit, n, sh, keys, list_lds, write_global, tp);
+}
+
+// A kernel instance per form: runs fn(std::integral_constant<int, ROUNDS>) with the form of this capacity.
+template <class Fn>
+inline void with_select_rounds(int pages_cap, int nt, const Fn& fn) {
+  switch (select_rounds(pages_cap, nt)) {
+    case 1: fn(std::integral_constant<int, 1>{}); break;
+    case 2: fn(std::integral_constant<int, 2>{}); break;
+    case 3: fn(std::integral_constant<int, 3>{}); break;
+    case 4: fn(std::integral_constant<int, 4>{}); break;
+    case 5: fn(std::integral_constant<int, 5>{}); break;
+    default: fn(std::integral_constant<int, 0>{});
+  }
+}
+
 // Step 2's top-k (Algorithm 1, i2) on page scores that an earlier launch left in a.in_scores: the
 // pick of the large-summary path.  A thread keeps its contiguous run of a few scores in registers
 // from the one batch of loads to the ordered emission, so no pass waits on LDS reads.
@@ -1135,7 +1159,14 @@ __device__ __forceinline__ void select_block(const CacheView& c, const SelectArg
   uint32_t qv[kMaxGroup];
   load_q_column(c, a, unit, qv);
   select_channels<NT>(c, a, unit, sh, true, qv);
-  select_pages<NT>(c, a, unit, n, sh, keys, nullptr, true, none);
+  switch (select_rounds(c.pages_cap, NT)) {  // (the same for the whole launch)
+    case 1: select_pages<NT, 1>(c, a, unit, n, sh, keys, nullptr, true, none); break;
+    case 2: select_pages<NT, 2>(c, a, unit, n, sh, keys, nullptr, true, none); break;
+    case 3:
+    case 4:
+    case 5: select_pages<NT, 5>(c, a, unit, n, sh, keys, nullptr, true, none); break;
+    default: select_pages<NT, 0>(c, a, unit, n, sh, keys, nullptr, true, none);
+  }
 }
 
 }  // namespace rkv

@@ -83,6 +83,15 @@ def test_last_slot(batch, hkv, cap, k1):
     run(batch, hkv, cap, cap - 1, 16, k1, CM, 0)
 
 
+# three and four pages per thread, and the first cache of the next form
+@pytest.mark.parametrize("batch,hkv,cap,layout", [(4, 4, 1032, CM), (4, 4, 1536, CM), (4, 4, 1544, TM), (4, 4, 2048, CM),
+                                                  (4, 4, 2048, TM), (4, 4, 2056, CM), (257, 1, 520, CM), (257, 1, 768, CM),
+                                                  (257, 1, 776, TM), (257, 1, 1024, CM), (257, 1, 1032, TM)])
+@pytest.mark.parametrize("k1", [32, 40])
+def test_three_and_four_rounds(batch, hkv, cap, layout, k1):
+    run(batch, hkv, cap, cap - 1, 16, k1, layout, 0)
+
+
 # the receiving page in other rounds and runs, one to 128 channels, pages already begun; token-major caches
 @pytest.mark.parametrize("cap,tail,ps,k1,layout,slot0", [
     (512, 300, 16, 1, CM, 3), (512, 511, 16, 5, CM, 9), (512, 448, 16, 31, CM, 0), (512, 447, 16, 33, CM, 1),
