@@ -342,8 +342,7 @@ int decode_impl(const char* who, const rocketkv_cache_t* cache, const void* q, c
     e = launch_hsa_decode_fused(v, a, ap, static_cast<bf16_t*>(out), out_lse, ws + d.attend_off, d.attend, st);
     return e == hipSuccess ? ROCKETKV_OK : hip_fail(e, who);
   }
-  if (v.v_token_major && !select_wants_split(v, a.k1) &&
-      fused_decode_tok_lds_bytes(v, d.row_len, d.attend) + 64 <= kMaxLdsBytes) {
+  if (v.v_token_major && decode_tok_one_launch(v, false, a.k1, d.row_len, d.attend)) {
     a.out_pages = out_pages;
     a.out_pages2 = nullptr;
     a.row_len2 = 0;
@@ -632,7 +631,7 @@ int mt_decode_impl(const char* who, const rocketkv_cache_t* cache, const rocketk
   a.n_recent = n_recent_pages;
   a.row_len = d.row_len;
   a.out_channels = out_channels;
-  if (!select_wants_split(lcv, a.k1) && fused_decode_tok_lds_bytes(lcv, d.row_len, d.attend) + 64 <= kMaxLdsBytes) {
+  if (decode_tok_one_launch(lcv, true, a.k1, d.row_len, d.attend)) {
     // one launch: selection on the logical sequence, attention through the index, append folded in
     const AppendArgs ap = {static_cast<const bf16_t*>(k_new), static_cast<const bf16_t*>(v_new),
                            static_cast<bf16_t*>(kmax), static_cast<bf16_t*>(kmin)};

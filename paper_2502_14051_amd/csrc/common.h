@@ -276,6 +276,7 @@ struct AppendArgs {      // all null: plain decode
 // One launch when the picked summary rows are small enough for a workgroup per (sequence, KV head);
 // otherwise, and only if a.out_scores gives it somewhere to put the scores, a score launch split over
 // the pages followed by the top-k launch.
+constexpr int64_t kSplitSummaryBytes = 128 * 1024;
 bool select_wants_split(const CacheView& c, int k1);
 hipError_t launch_hsa_select(const CacheView& c, const SelectArgs& a, hipStream_t st);
 
@@ -309,8 +310,8 @@ hipError_t launch_attend_tokens(const CacheView& c, const bf16_t* q, const int32
                                 bf16_t* out, float* out_lse, void* ws, const AttendPlan& plan,
                                 const LogicalView* lv, hipStream_t st);
 // Step 2 + Step 3 (+ the token append) in one launch for token-major caches; `lv` (optional): over the
-// logical sequence of RocketKV-MT.  Usable when fused_decode_tok_lds_bytes() fits kMaxLdsBytes and the
-// summaries are not large enough to want the split selection.
+// logical sequence of RocketKV-MT.  For the caches that decode_tok_one_launch names (`lc`: the cache Step 2 works on).
+bool decode_tok_one_launch(const CacheView& lc, bool indexed, int k1, int row_len, const AttendPlan& plan);
 size_t fused_decode_tok_lds_bytes(const CacheView& lc, int row_len, const AttendPlan& plan);
 hipError_t launch_hsa_decode_tok_fused(const CacheView& c, const LogicalView* lv, const SelectArgs& sa,
                                        const AppendArgs& ap, bf16_t* out, float* out_lse, void* ws,

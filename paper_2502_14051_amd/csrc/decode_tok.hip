@@ -2,8 +2,8 @@
 // RocketKV-MT (Algorithm 1 of arXiv 2502.14051 end to end; Section 3.5 for the indexed variant).
 // Same structure as the channel-major fused kernel: every workgroup of a (sequence, KV head) unit runs
 // Step 2 for itself, keeps the page list in LDS and goes on to Step 3 over its share of the token
-// slots.  Used when the picked summary rows are small enough to be read twice per unit; larger ones
-// (small pages, many channels) take the score / pick / attention launches.
+// slots.  Used when the picked summary rows are small enough to be read by every workgroup of the unit
+// (decode_tok_one_launch); larger ones (small pages, many channels) take the score / pick / attention launches.
 //
 // APPEND also takes in the token generated at this step (Section 3.4 Step 1, last sentence): every
 // reader patches its key / value rows in from LDS copies; split 0 of the unit writes them to the cache,
@@ -121,6 +121,30 @@ void hsa_decode_tok_kernel(CacheView c, CacheView lc, SelectArgs sa, AttendArgs 
       clear_reads(seq_counters, read_slot(c, b));
     }
   }
+}
+
+// Whether a decode step over token-major caches is this one launch, or selects in launches of its own.  Here every workgroup
+// of a unit streams all of its picked summary rows for itself; there they are divided between workgroups, for a launch
+// boundary and the hand-over of the scores.  The line lies where the rows of a unit take as long as that, us a layer in
+// one launch / in two (8 KV heads a sequence, pages of 2 to 4 tokens, rows of a unit in KiB):
+//   1 sequence    179 20.9 / 24.9, 242 22.4 / 25.1, 240 23.6 / 24.7, 320 25.9 / 25.0, 503 29.2 / 25.4
+//   4 sequences   242 23.6 / 26.8, 320 26.5 / 26.6, 352 29.6 / 26.3
+//   8             240 25.2 / 27.3, 320 27.3 / 28.2, 400 30.3 / 29.4
+//   16            189 26.1 / 30.1, 241 27.2 / 31.2, 300 32.1 / 33.1, 352 33.6 / 33.0, 400 34.8 / 34.5
+//   64 (four wavefronts)  146 56.9 / 68.1, 241 69.7 / 76.4
+// so 256 KiB for up to eight sequences of eight heads, 320 KiB from there on.  Past five pages a thread the scores go through
+// LDS and radix passes, and two launches are ahead from fewer bytes on (one sequence, 4032 pages: 28.7 / 24.7 at 258); with
+// four wavefronts they are not.
+// Through an index the alternative is an append, two selection launches and the attention: 2088 pages of one sequence at 32
+// channels 23.6 / 28.6, of 16 at 128 channels 43.1 / 56.0; 4160 pages of four sequences at 32 32.1 / 36.8, of one at 64
+// (520 KiB) 37.9 / 31.8.
+bool decode_tok_one_launch(const CacheView& lc, bool indexed, int k1, int row_len, const AttendPlan& plan) {
+  if (lc.pages_cap > kSingleSelectPages || fused_decode_tok_lds_bytes(lc, row_len, plan) + 64 > kMaxLdsBytes) return false;
+  const int64_t rows = (int64_t)k1 * lc.pages_cap * (int64_t)sizeof(bf16_t);
+  const int64_t line = ((int64_t)lc.batch * lc.n_kv_heads > 64 ? 320 : 256) * 1024;
+  const bool in_registers = select_rounds(lc.pages_cap, plan.waves * kWave) != 0;
+  if (indexed) return in_registers || rows <= line;
+  return rows <= (in_registers || plan.waves == 4 ? line : kSplitSummaryBytes - 1);
 }
 
 size_t fused_decode_tok_lds_bytes(const CacheView& lc, int row_len, const AttendPlan& plan) {

@@ -144,10 +144,9 @@ __global__ __launch_bounds__(kPickThreads) void hsa_pick_kernel(CacheView c, Sel
   pick_from_scores<kPickThreads>(c, a, unit, n, sh);
 }
 
-// Picked summary rows of this size or more per (sequence, KV head) are streamed by several workgroups:
-// one workgroup reads them at about 11 GB/s, i.e. 128 KiB already costs it some 12 us.
-constexpr int64_t kSplitSummaryBytes = 128 * 1024;
-
+// Picked summary rows of kSplitSummaryBytes or more per (sequence, KV head) are streamed by several workgroups: one of 256
+// threads reads them at about 11 GB/s, i.e. 128 KiB already costs it some 12 us.  (The decode step over token-major caches
+// has its own line, decode_tok_one_launch.)
 bool select_wants_split(const CacheView& c, int k1) {
   return c.pages_cap > kSingleSelectPages ||
          (int64_t)k1 * c.pages_cap * (int64_t)sizeof(bf16_t) >= kSplitSummaryBytes;

@@ -121,3 +121,12 @@ def test_more_pages(batch, hkv, cap, tail, k1):
                                             (4200, 4199, 2, 19), (8200, 8199, 1, 8), (8200, 20, 1, 9)])
 def test_score_launch(cap, tail, ps, k1):
     run(4, 4, cap, tail, ps, k1, TM, 0)
+
+
+# either side of the lines between one launch and several: 256 KiB of picked rows up to 64 (sequence, KV head) units, 320
+# KiB beyond; more pages than the register selection holds, where it is 128 KiB, and with four wavefronts 320 again
+@pytest.mark.parametrize("batch,hkv,cap,k1", [(4, 4, 1024, 128), (4, 4, 1088, 128), (4, 4, 2560, 51), (4, 4, 2560, 52), (17, 4, 1280, 128),
+                                              (17, 4, 1288, 128), (4, 4, 2568, 25), (4, 4, 2568, 26), (257, 1, 1288, 127),
+                                              (257, 1, 1288, 128)])
+def test_one_launch_or_several(batch, hkv, cap, k1):
+    run(batch, hkv, cap, cap - 1, 2, k1, TM, 0)

@@ -261,3 +261,46 @@ def test_empty_and_full_logical_sequences(env, oracle):
         wb = wl.scaled(w, batch=1)
         check_selection(oracle, dict(q=d["q"][b:b + 1], K=Kc, V=Vc, seq_lens=n_idx[b:b + 1]), wb, index.pages_cap,
                         gp, None, None)
+
+
+@pytest.mark.parametrize("pages,k1,why", [(2550, 128, "pages in registers: one launch"), (2590, 49, "254 KiB of rows: one launch"),
+                                          (2590, 64, "332 KiB of rows: append, score, top-k and attention launches")])
+def test_routes_over_an_index(env, oracle, pages, k1, why):
+    """A step that takes in a token and the one after it, on either side of the lines between one launch and several."""
+    torch, rk, dev = env
+    B, S, T = 2, 3000, 200
+    say("multi-turn routes", pages, k1, why)
+    w = small("tiny", batch=B, context=S, page_size=1, channel_budget=k1, token_budget=T, n_heavy=8)
+    d = wl.generate(w)
+    cache, _ = to_device_cache(rk, torch, d, w.n_q_heads, 16, dev, pages_cap=S // 16 + 8, v_layout=TM)
+    index = rk.alloc_index(cache, 1, pages + 4)
+    assert index.pages_cap > 2560 or "registers" in why
+    rng = np.random.default_rng(pages + k1)
+    idx = np.full((B, w.n_kv_heads, index.pages_cap), -1, dtype=np.int32)
+    for b in range(B):
+        for g in range(w.n_kv_heads):
+            idx[b, g, :pages] = np.sort(rng.choice(S, size=pages, replace=False))
+    index.token_index.copy_(torch.from_numpy(idx).to(dev))
+    index.n_indexed.fill_(pages)
+    kmax, kmin = rk.alloc_index_summaries(cache, index)
+    rk.mt_build_page_summaries(cache, index, kmax, kmin)
+    ws = rk.mt_alloc_workspace(cache, index, T)
+    kn = wl.f32_to_bf16_bits(rng.standard_normal((B, w.n_kv_heads, 1, 128)).astype(np.float32))
+    vn = wl.f32_to_bf16_bits(rng.standard_normal((B, w.n_kv_heads, 1, 128)).astype(np.float32))
+    out = torch.empty((B, w.n_q_heads, 128), dtype=torch.bfloat16, device=dev)
+    listed = torch.empty((B, w.n_kv_heads, T), dtype=torch.int32, device=dev)
+    rk.mt_hsa_decode_append(cache, index, wl.from_bits(d["q"], dev), wl.from_bits(kn[:, :, 0], dev), wl.from_bits(vn[:, :, 0], dev),
+                            kmax, kmin, k1, T, 1, out, None, listed, None, ws)
+    torch.cuda.synchronize()
+    assert index.n_indexed.tolist() == [pages + 1] * B and cache.seq_lens.tolist() == [S + 1] * B
+    K, V = np.concatenate([d["K"], kn], axis=2), np.concatenate([d["V"], vn], axis=2)
+    nl = np.full(B, pages + 1, dtype=np.int32)
+    ids = index.token_index.cpu().numpy()
+    assert (ids[:, :, pages] == S).all() and np.array_equal(ids[:, :, :pages], idx[:, :, :pages])
+    Kc, Vc = gather(K, ids, nl), gather(V, ids, nl)
+    gp = listed.cpu().numpy()
+    assert (gp[:, :, -1] == pages).all()  # the newest page is forced in
+    check_selection(oracle, dict(q=d["q"], K=Kc, V=Vc, seq_lens=nl), w, index.pages_cap, gp, None, None, 1)
+    want, _ = oracle.attend_given(d["q"], Kc, Vc, nl, 1, gp)
+    assert_attention_close(wl.to_bits(out), want, "y of the appending step")
+    decode_check(env, oracle, (cache, index, kmax, kmin, ws), w, d["q"], K, V)
