@@ -1,7 +1,7 @@
 // Stage 1 of RocketKV (Section 3.3 of arXiv 2502.14051; window / kernel sizes from Appendix A.3):
 // GQA-aware SnapKV.  Per (sequence, KV head):
 //   pass 1  row statistics (max, sum-exp) of the causal softmax of every (head, window row) over the
-//           whole prompt, split along the key axis, then merged;
+//           whole prompt, split along the key axis, then merged (by a launch or in pass 2);
 //   pass 2  probabilities recomputed from the statistics and summed over heads and window rows into
 //           one vote per prefix token;
 //   pool    stride-1 max-pool of the votes (odd kernel, clipped at the ends), written as votes and as
@@ -72,6 +72,9 @@ constexpr int kSnapMaxChunkPages = 128;   // pages per workgroup
 constexpr int kRowsBytes = 4 * kHeadDim * (int)sizeof(bf16_t) + 16;  // four rows in LDS, and what shifts the next four's banks
 constexpr int kTileBytes = 4 * kRowsBytes, kSlotBytes = 2 * kTileBytes;
 constexpr int kRingBytes = 4 * 2 * kSlotBytes;
+constexpr int kMergeLoads = 16;            // chunk statistics a thread of pass 2 has in flight
+constexpr int kMergeStats = 64 * 128;      // statistics of a unit that pass 2 merges itself, at most
+constexpr int kMergeWorkgroups = 1024;     // in up to this many workgroups, two rounds over the chip
 constexpr int kSnapStatBytes = 2 * 4 * kSnapCols * (int)sizeof(float);
 constexpr int kSnapVoteBytes = 2 * kSnapSegPairs * 4 * 2 * kAttnPage * (int)sizeof(float);
 
@@ -108,6 +111,11 @@ __device__ __forceinline__ float half_wave_sums(float (&x)[16], int lane) {
   return x[0] + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x[0]), 0xB1, 0xf, 0xf, true));  // quad_perm 1,0,3,2
 }
 
+// MERGE (pass 2): the statistics of pass 1's chunks are merged by every workgroup for itself, not by a launch in between.
+// That launch takes 4-5 us whatever there is to merge; here up to 64 KiB come from L2 beside the queries.  us a call
+// with the summaries, by a launch / so: 1 x 2048 tokens 36.6 / 35.1, 1 x 8192 48.6 / 46.0, 1 x 16384 53.0 / 51.4, 1 x 32768
+// 70.8 / 69.4, 4 x 16000 89.3 / 86.5, 8 x 32000 unequal 179.8 / 177.5 (1024 workgroups), 16 x 32768 541.3 / 543.6 (2048), and
+// with more to merge (128 KiB) 64 query heads 1 x 32000 82.1 / 84.6.
 // NB: blocks of 32 softmax rows every wavefront works through (blocks without any hold zero queries and are
 // discarded).  A wavefront takes 32 tokens, a pair of neighbouring pages, at a time, against one block after the
 // other: a 32 x 32 product leaves a lane one softmax row and sixteen of the tokens.
@@ -120,7 +128,7 @@ __device__ __forceinline__ float half_wave_sums(float (&x)[16], int lane) {
 // 32768 175 -> 168 / 171 -> 162, 1 x 131072 164 -> 154 / 156 -> 152, 1 x 32768 81.5 -> 78 / 74.2 -> 74.3, 1 x 8192
 // 56 -> 51 / 53.5 -> 48.8.  Under the long set-up loop of the benchmark, where the clock drops, 16 x 32768 stays at
 // 580-595 a layer.  (Bare stream of 16 x 32768 keys: 161 us a pass.)
-template <bool PASS2, int NB>
+template <bool PASS2, int NB, bool MERGE = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void snap_score_kernel(CacheView c, SnapArgs a) {
   typedef uint32_t ring_u32x4 __attribute__((ext_vector_type(4)));
@@ -350,7 +358,29 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
   const auto block_at = [&](int x) {  // where block x of 16 lies: tile x / 4 of the second slot of wavefront x % 4
     return s_ring + (x % 4 * 2 + 1) * kSlotBytes + x / 4 * kTileBytes;
   };
-  if (PASS2) {  // requested ahead of the queries: one round trip for both
+  // MERGE: this workgroup merges the chunks' statistics itself, requested ahead of the queries.  A softmax row's chunks are
+  // dealt to `parts` threads, in an order that is the same in every workgroup; the partial results meet in LDS behind the
+  // queries' barrier.
+  const auto merge = [](float& mm, float& zz, float mo, float zo) {
+    const float mn = fmaxf(mm, mo);
+    zz = zz * exp2_fast(mm - mn) + zo * exp2_fast(mo - mn);
+    mm = mn;
+  };
+  const int ncp = a.NC <= 64 ? 64 : a.NC <= 128 ? 128 : 256, parts = 256 / ncp;  // NC <= 256 (host)
+  const int my_row = tid & (ncp - 1), my_part = tid / ncp;
+  const int chunks = ((S + kAttnPage - 1) / kAttnPage + a.chunk_pages - 1) / a.chunk_pages;
+  float2 first_stats[MERGE ? kMergeLoads : 1];
+  const auto fetch_stats = [&](int ch0) {
+    const float2* row = reinterpret_cast<const float2*>(a.stats_part) + (int64_t)unit * a.n_chunks * a.NC + my_row;
+#pragma unroll
+    for (int u = 0; u < kMergeLoads; ++u) {
+      const int ch = ch0 + my_part + u * parts;
+      first_stats[u] = make_float2(kNegBigS, 0.f);
+      if (ch < chunks && my_row < a.NC) first_stats[u] = row[(int64_t)ch * a.NC];
+    }
+  };
+  if (MERGE) fetch_stats(0);
+  if (PASS2 && !MERGE) {  // requested ahead of the queries: one round trip for both
 #pragma unroll
     for (int cb = 0; cb < NB; ++cb) {
       const int col = cgi * kSnapCols + cb * 32 + lane % 32;
@@ -372,6 +402,18 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
     }
     if (cg == 0) {
       issue(0);
+      if (MERGE) {
+        float mm = kNegBigS, zz = 0.f;
+        for (int ch0 = 0;;) {
+#pragma unroll
+          for (int u = 0; u < kMergeLoads; ++u) merge(mm, zz, first_stats[u].x, first_stats[u].y);
+          ch0 += kMergeLoads * parts;
+          if (ch0 >= chunks) break;
+          fetch_stats(ch0);
+        }
+        s_out[tid] = mm;
+        s_out[256 + tid] = zz;
+      }
       asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // all but the first pair of key tiles
     } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -388,6 +430,17 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
       }
     }
   }
+  if (MERGE) {
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      const int col = cgi * kSnapCols + cb * 32 + lane % 32;
+      float mm = kNegBigS, zz = 0.f;
+      if (col < a.NC)
+        for (int p = 0; p < parts; ++p) merge(mm, zz, s_out[p * ncp + col], s_out[256 + p * ncp + col]);
+      M2[cb] = col < a.NC ? mm : 0.f;
+      invZ[cb] = zz > 0.f ? 1.f / zz : 0.f;
+    }
+  }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __syncthreads();  // the blocks have been read: their slots take key tiles now
   issue(1);
@@ -396,6 +449,11 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
   // the last refills (unused) land before the workgroup's LDS is given back
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (PASS2) return;
+  if (chunk == 0) {  // the pool, which counts into these, is at least a launch away
+    if (tid == 0) a.n_runs[unit * kCountStride] = 0;
+    uint4* hist = reinterpret_cast<uint4*>(a.hist + (int64_t)unit * kSelBins);
+    for (int i = tid; i < kSelBins / 4; i += 256) hist[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
   // ---- pass 1: merge statistics over the half wavefronts and the wavefronts, and hand the chunk's partial out
   float (*sM)[kSnapCols] = reinterpret_cast<float (*)[kSnapCols]>(s_out);
   float (*sZ)[kSnapCols] = sM + 4;
@@ -426,10 +484,10 @@ void snap_score_kernel(CacheView c, SnapArgs a) {
   }
 }
 
-// merge the per-chunk statistics of one unit.  A long prompt has hundreds of chunks: the chunks of a
-// softmax row are dealt to 1024 / ncp threads (ncp = the row count rounded up to a power of two),
-// each merges its share with eight loads in flight, and one thread per row merges the partial
-// results in a fixed order.
+// merge the per-chunk statistics of one unit, where there are too many for pass 2 (MERGE above).  A long
+// prompt has hundreds of chunks: the chunks of a softmax row are dealt to 1024 / ncp threads (ncp = the row
+// count rounded up to a power of two), each merges its share with eight loads in flight, and one thread per
+// row merges the partial results in a fixed order.
 constexpr int kStatsT = 1024;
 __global__ __launch_bounds__(kStatsT) void snap_stats_kernel(CacheView c, SnapArgs a) {
   __shared__ float pm[kStatsT], pz[kStatsT];
@@ -438,9 +496,6 @@ __global__ __launch_bounds__(kStatsT) void snap_stats_kernel(CacheView c, SnapAr
   const int b = unit / c.n_kv_heads;
   const int S = c.seq_lens[b];
   if (S <= a.keep || S > c.pages_cap * kAttnPage) return;
-  // the pool, two launches on, counts into these
-  if (tid == 0) a.n_runs[unit * kCountStride] = 0;
-  for (int i = tid; i < kSelBins; i += kStatsT) a.hist[(int64_t)unit * kSelBins + i] = 0;
   const int chunks = ((S + kAttnPage - 1) / kAttnPage + a.chunk_pages - 1) / a.chunk_pages;
   int ncp = 64;
   while (ncp < a.NC) ncp <<= 1;  // NC <= 256 (host)
@@ -1044,11 +1099,14 @@ hipError_t launch_snapkv(const bf16_t* q_obs, const CacheView& src, int window, 
     hipLaunchKernelGGL((snap_score_kernel<false, 4>), sgrid, dim3(256), kRingBytes + kSnapStatBytes, st, src, a);
   else
     hipLaunchKernelGGL((snap_score_kernel<false, 2>), sgrid, dim3(256), kRingBytes + kSnapStatBytes, st, src, a);
-  hipLaunchKernelGGL(snap_stats_kernel, dim3(units), dim3(kStatsT), 0, st, src, a);
-  if (wide)
-    hipLaunchKernelGGL((snap_score_kernel<true, 4>), sgrid, dim3(256), kRingBytes + kSnapVoteBytes, st, src, a);
-  else
-    hipLaunchKernelGGL((snap_score_kernel<true, 2>), sgrid, dim3(256), kRingBytes + kSnapVoteBytes, st, src, a);
+  const bool merge = plan.n_chunks * a.NC <= kMergeStats && plan.n_chunks * units <= kMergeWorkgroups;
+  if (!merge) hipLaunchKernelGGL(snap_stats_kernel, dim3(units), dim3(kStatsT), 0, st, src, a);
+  const auto pass2 = [&](auto kernel) { hipLaunchKernelGGL(kernel, sgrid, dim3(256), kRingBytes + kSnapVoteBytes, st, src, a); };
+  if (merge) {
+    if (wide) pass2(snap_score_kernel<true, 4, true>); else pass2(snap_score_kernel<true, 2, true>);
+  } else {
+    if (wide) pass2(snap_score_kernel<true, 4>); else pass2(snap_score_kernel<true, 2>);
+  }
   const dim3 pgrid((a.s_cap + kPoolTile - 1) / kPoolTile, units);
   const size_t pool_groups = kPoolT + 2 * ((a.pool_r + 7) / 8);
   hipLaunchKernelGGL(snap_pool_kernel, pgrid, dim3(kPoolT), pool_groups * 10 * sizeof(float), st, src, a);

@@ -58,3 +58,11 @@ def test_short_chunks(oracle, hq, hkv, W, cap, chunk):
     """Capacities at which four units' workgroups are just as many as compute units, and the next longer ones."""
     t = 16 * chunk  # tokens a workgroup scores
     check(oracle, hq, hkv, W, tuple(x + W for x in (3 * t, 3 * t + 1, 5 * t - 1, 4 * t + 17))[:4 // hkv], cap, 200)
+
+
+@pytest.mark.parametrize("hq,cap", [(64, 2560), (16, 2304), (32, 6400), (32, 8192), (32, 8320), (16, 8320)])
+def test_merged_statistics(oracle, hq, cap):
+    """Chunks of 128 pages in sixteen units: more of them than a thread of the second pass merges at a time (20 of 256 softmax
+    rows, 50 of 128), 18 of 64 rows dealt to four threads, as many statistics and workgroups as it merges at most (64 of 128
+    rows), one chunk more, and one more with fewer rows."""
+    check(oracle, hq, 4, 16, (33000, 2064, 18 * 2048 + 16 if cap == 2304 else 20 * 2048, 300), cap, 200)
