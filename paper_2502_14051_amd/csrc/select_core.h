@@ -451,9 +451,13 @@ __device__ __forceinline__ int select_pages_any(const CacheView& c, const Select
 // Step 2, second half, for caches of at most ROUNDS * NT pages (every fused decode launch of the usual
 // shapes): the same result as select_pages_any, arranged for latency.  The routine sits in front of the
 // K/V stream with HBM idle, so what counts is the number of dependent steps, not the work:
-//   - eight neighbouring lanes share an eight-page run and split the picked rows between them; the
-//     row sums meet in three lane-exchange steps (no LDS, no barrier) and lane r keeps page r of the
-//     run, so thread t holds the scores of pages t, NT + t, ... (one per round);
+//   - eight lanes of a wavefront share an eight-page run and split the picked rows between them; the row sums meet in three
+//     lane-exchange steps and a permutation, so that thread t holds the scores of pages t, NT + t, ... (one per round).
+//     Eight neighbouring lanes read the same row, i.e. 128 contiguous bytes: with the lanes of a run side by side a load
+//     touched eight rows per eight lanes, and the rows came in at the rate the first-level cache looks up lines.  us a
+//     layer, so / now: one sequence of 16000 tokens 15.7 / 15.2, of 24000 17.3 / 16.4, of 32700 (rows of whole cache lines)
+//     19.7 / 17.4, of 32768 18.8 / 17.6, 7 with 1856 pages at 68 channels 28.0 / 24.9, 16 with 1488 at 81 28.5 / 27.9; with
+//     one round (16 of 4122) 22.3 / 22.3;
 //   - the kp-th largest score is found by counting into 256 or 512 equal-width value bins between the
 //     smallest and the largest finite score (the forced recent pages, +inf, in the top bin): one
 //     histogram, scanned by every wavefront for itself.  Binning is monotone, so every page above the
@@ -489,7 +493,7 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
   const int n_rec = min(a.n_recent, kp);  // no more forced pages than pages picked: the newest ones win
   const int n_oct = (P + 7) / 8;
   const int64_t rows = (int64_t)unit * kHeadDim;
-  const int o = tid / 8, r = tid % 8;
+  const int o = wave * 8 + lane % 8, r = lane / 8;  // this lane's run of a round, and its rows
   // the wavefront's first run of a round: a wavefront without any skips the round's arithmetic (a scalar branch)
   const int o_wave = __builtin_amdgcn_readfirstlane(tid / kWave) * (kWave / 8);
   // scratch words in sh.partial (unused by the channel pick): candidate keys, their counter, the
@@ -532,10 +536,13 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
       }
     }
   }
-  // ---- s1: page scores.  Thread (o, r) = (tid / 8, tid % 8) takes the rows r, r + 8, ... of the picked
+  // ---- s1: page scores.  Lane (o, r) takes the rows r, r + 8, ... of the picked
   // channels for the runs o, o + kRuns, ... (one per round); the loads of every round go out before the
   // first is used, so the rounds share one memory round trip.
   float score[kRounds];
+  const auto plus_ror8 = [](float keep, float give) {  // `give` of the lane eight away in its row of sixteen
+    return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), 0x128, 0xf, 0xf, true));
+  };
   {
     constexpr int kBatch = 4;  // rows of a thread whose loads are in flight together, for every round (registers)
     float acc[kRounds][8];
@@ -580,25 +587,25 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
         }
       }
     }
-    // the eight lanes of a run add up their row groups: lane pairs, quads, then the two quads; every
-    // lane ends with the same sums, formed in the same order; lane r keeps page r of the run
-    const auto lanes8 = [](float x) {
-      x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xf, 0xf, false));   // quad_perm 1,0,3,2
-      x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xf, 0xf, false));   // quad_perm 2,3,0,1
-      x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xf, 0xf, false));  // row_half_mirror
-      return x;
-    };
+    // The eight lanes of a run add up their row groups: r and r + 4, then r and r + 2, then r and r + 1, each step leaving a
+    // lane with half of its pages; lane (r, o) ends with page r of its run, and passes it to the lane whose own page it is.
 #pragma unroll
     for (int i = 0; i < kRounds; ++i) {
       score[i] = 0.f;
       if (i * kRuns + o_wave < n_oct) {
-        float mine = lanes8(acc[i][0]);
+        float x[4];
 #pragma unroll
-        for (int e = 1; e < 8; ++e) {
-          const float x = lanes8(acc[i][e]);
-          mine = r == e ? x : mine;
+        for (int e = 0; e < 4; ++e) {
+          const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][e]), __float_as_uint(acc[i][e + 4]), false, false);
+          x[e] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
         }
-        score[i] = mine;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[e]), __float_as_uint(x[e + 2]), false, false);
+          x[e] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        }
+        const bool up = (lane & 8) != 0;
+        score[i] = __shfl(plus_ror8(up ? x[1] : x[0], up ? x[0] : x[1]), lane % 8 * 8 + lane / 8);
       }
     }
     if (tail_wave) {
@@ -628,7 +635,11 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
           for (int t = 0; t < 4; ++t) sum = fmaf(wt[t], ft[t], sum);
         }
       }
-      sum = lanes8(sum);
+      SwapPair sw = swap_rows32(__float_as_uint(sum));
+      sum = __uint_as_float(sw.a) + __uint_as_float(sw.b);
+      sw = swap_rows16(__float_as_uint(sum));
+      sum = __uint_as_float(sw.a) + __uint_as_float(sw.b);
+      sum = plus_ror8(sum, sum);
       if (has_tail) score[kRounds - 1] = sum;
     }
   }
