@@ -124,27 +124,31 @@ void hsa_decode_tok_kernel(CacheView c, CacheView lc, SelectArgs sa, AttendArgs 
 }
 
 // Whether a decode step over token-major caches is this one launch, or selects in launches of its own.  Here every workgroup
-// of a unit streams all of its picked summary rows for itself; there they are divided between workgroups, for a launch
-// boundary and the hand-over of the scores.  The line lies where the rows of a unit take as long as that, us a layer in
-// one launch / in two (8 KV heads a sequence, pages of 2 to 4 tokens, rows of a unit in KiB):
-//   1 sequence    179 20.9 / 24.9, 242 22.4 / 25.1, 240 23.6 / 24.7, 320 25.9 / 25.0, 503 29.2 / 25.4
-//   4 sequences   242 23.6 / 26.8, 320 26.5 / 26.6, 352 29.6 / 26.3
-//   8             240 25.2 / 27.3, 320 27.3 / 28.2, 400 30.3 / 29.4
-//   16            189 26.1 / 30.1, 241 27.2 / 31.2, 300 32.1 / 33.1, 352 33.6 / 33.0, 400 34.8 / 34.5
-//   64 (four wavefronts)  146 56.9 / 68.1, 241 69.7 / 76.4
-// so 256 KiB for up to eight sequences of eight heads, 320 KiB from there on.  Past five pages a thread the scores go through
-// LDS and radix passes, and two launches are ahead from fewer bytes on (one sequence, 4032 pages: 28.7 / 24.7 at 258); with
-// four wavefronts they are not.
-// Through an index the alternative is an append, two selection launches and the attention: 2088 pages of one sequence at 32
-// channels 23.6 / 28.6, of 16 at 128 channels 43.1 / 56.0; 4160 pages of four sequences at 32 32.1 / 36.8, of one at 64
-// (520 KiB) 37.9 / 31.8.
+// of a unit reads all of its picked summary rows for itself; there they are divided between workgroups, for a launch
+// boundary and the hand-over of the scores.  What the rows cost here goes by the number of loads a thread has one after the
+// other: its rounds of pages, times the batches of 32 rows.  us a layer in one launch / in two, 8 KV heads a sequence, by
+// rounds x batches:
+//   1 sequence    3x3 22.6 / 25.0, 4x3 23.8 / 25.3, 5x2 23.9 / 24.9, 6x2 24.7 / 24.9, 7x2 25.9 / 25.3, 5x3 25.9 / 25.3, 8x2 27.4 / 25.0
+//   4 sequences   4x3 25.8 / 27.6, 6x2 26.6 / 27.5, 7x2 28.0 / 27.8, 5x3 28.3 / 27.7, 8x2 29.4 / 27.6
+//   8             4x4 28.6 / 30.3, 5x3 29.2 / 30.9, 5x4 31.8 / 31.9, 7x3 32.8 / 32.2
+//   16            4x4 37.2 / 39.5, 5x3 38.6 / 40.3, 8x2 37.3 / 37.6, 5x4 45.2 / 43.6, 7x3 45.2 / 44.1
+//   32            4x4 60.8 / 59.9, 5x4 68.4 / 75.4, 7x3 68.6 / 74.3
+//   40, 64 (four wavefronts)  6x2 51.0 / 64.1, 6x3 71.7 / 80.7, 8x3 63.1 / 75.0
+// so 12 for up to four sequences of eight heads, 16 up to sixteen, 24 beyond.  With more pages than the register selection
+// holds the scores go through LDS and radix passes: two launches from 128 KiB of rows on, with four wavefronts from 320
+// KiB on (40 sequences of 2424 pages at 40 channels 59.8 / 73.2, at 60 68.9 / 76.3).
+// Through an index the alternative is an append, two selection launches and the attention: 8x4 of one sequence 38.4 / 36.1,
+// of four 41.2 / 42.1, 6x4 of one 32.6 / 34.7; in LDS 4160 pages of four sequences at 32 channels (260 KiB) 32.1 / 36.8, of
+// one at 64 37.9 / 31.8.
 bool decode_tok_one_launch(const CacheView& lc, bool indexed, int k1, int row_len, const AttendPlan& plan) {
   if (lc.pages_cap > kSingleSelectPages || fused_decode_tok_lds_bytes(lc, row_len, plan) + 64 > kMaxLdsBytes) return false;
   const int64_t rows = (int64_t)k1 * lc.pages_cap * (int64_t)sizeof(bf16_t);
-  const int64_t line = ((int64_t)lc.batch * lc.n_kv_heads > 64 ? 320 : 256) * 1024;
-  const bool in_registers = select_rounds(lc.pages_cap, plan.waves * kWave) != 0;
-  if (indexed) return in_registers || rows <= line;
-  return rows <= (in_registers || plan.waves == 4 ? line : kSplitSummaryBytes - 1);
+  if (rows < kSplitSummaryBytes) return true;
+  const int rounds = select_rounds(lc.pages_cap, plan.waves * kWave), units = lc.batch * lc.n_kv_heads;
+  if (rounds == 0) return (indexed || plan.waves == 4) && rows <= 320 * 1024;
+  const int loads = rounds * ((k1 + 31) / 32);
+  if (indexed) return loads <= 24 || units >= 32;
+  return loads <= (units <= 32 ? 12 : units <= 128 ? 16 : 24);
 }
 
 size_t fused_decode_tok_lds_bytes(const CacheView& lc, int row_len, const AttendPlan& plan) {

@@ -834,8 +834,11 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
 // branches over 1, 2, 5 rounds / a kernel per form over 1, 2, 3, 4, 5: one sequence of 4096 tokens (one round) 15.1 /
 // 14.7, of 16000 (two) 16.8 / 16.5, of 24000 (three) 19.2 / 18.0, of 32000 (four) 19.9 / 19.2, four of 24000 20.2 / 19.0,
 // 16 of 4122 22.9 / 22.9.
+// Six to eight rounds against select_pages_any: one sequence of 42000 tokens 24.6 / 20.1, of 50000 25.4 / 21.0, of 64000
+// 27.5 / 22.2, 13 of 50000 35.0 / 30.8, 40 of 25000 (256 threads) 60.0 / 55.8.  A thread's counts leave a lane each for at
+// most eight rounds of eight wavefronts.
 __host__ __device__ constexpr int select_rounds(int pages_cap, int nt) {
-  return pages_cap <= 5 * nt ? (pages_cap + nt - 1) / nt : 0;
+  return pages_cap <= 8 * nt ? (pages_cap + nt - 1) / nt : 0;
 }
 
 template <int NT, int ROUNDS>
@@ -855,6 +858,9 @@ inline void with_select_rounds(int pages_cap, int nt, const Fn& fn) {
     case 3: fn(std::integral_constant<int, 3>{}); break;
     case 4: fn(std::integral_constant<int, 4>{}); break;
     case 5: fn(std::integral_constant<int, 5>{}); break;
+    case 6: fn(std::integral_constant<int, 6>{}); break;
+    case 7: fn(std::integral_constant<int, 7>{}); break;
+    case 8: fn(std::integral_constant<int, 8>{}); break;
     default: fn(std::integral_constant<int, 0>{});
   }
 }
@@ -1170,7 +1176,8 @@ __device__ __forceinline__ void select_block(const CacheView& c, const SelectArg
   uint32_t qv[kMaxGroup];
   load_q_column(c, a, unit, qv);
   select_channels<NT>(c, a, unit, sh, true, qv);
-  switch (select_rounds(c.pages_cap, NT)) {  // (the same for the whole launch)
+  // (the same for the whole launch)
+  switch (select_rounds(c.pages_cap, NT)) {
     case 1: select_pages<NT, 1>(c, a, unit, n, sh, keys, nullptr, true, none); break;
     case 2: select_pages<NT, 2>(c, a, unit, n, sh, keys, nullptr, true, none); break;
     case 3:

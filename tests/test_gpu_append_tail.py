@@ -123,10 +123,17 @@ def test_score_launch(cap, tail, ps, k1):
     run(4, 4, cap, tail, ps, k1, TM, 0)
 
 
-# either side of the lines between one launch and several: 256 KiB of picked rows up to 64 (sequence, KV head) units, 320
-# KiB beyond; more pages than the register selection holds, where it is 128 KiB, and with four wavefronts 320 again
-@pytest.mark.parametrize("batch,hkv,cap,k1", [(4, 4, 1024, 128), (4, 4, 1088, 128), (4, 4, 2560, 51), (4, 4, 2560, 52), (17, 4, 1280, 128),
-                                              (17, 4, 1288, 128), (4, 4, 2568, 25), (4, 4, 2568, 26), (257, 1, 1288, 127),
-                                              (257, 1, 1288, 128)])
+# either side of the lines between one launch and several: loads one after the other (rounds of pages x batches of 32
+# channels) 12 up to 32 (sequence, KV head) units, 16 up to 128, 24 beyond; past the register selection 128 KiB of picked rows,
+# 320 with four wavefronts
+@pytest.mark.parametrize("batch,hkv,cap,k1", [(4, 4, 2048, 96), (4, 4, 2048, 97), (17, 4, 2048, 128), (17, 4, 2560, 97),
+                                              (33, 4, 4096, 96), (33, 4, 4096, 97), (257, 1, 2048, 96), (257, 1, 2048, 97),
+                                              (4, 4, 4104, 15), (4, 4, 4104, 16), (257, 1, 2064, 79), (257, 1, 2064, 80)])
 def test_one_launch_or_several(batch, hkv, cap, k1):
     run(batch, hkv, cap, cap - 1, 2, k1, TM, 0)
+
+
+# six, seven and eight rounds, full and not
+@pytest.mark.parametrize("cap,tail", [(3072, 3071), (3080, 3079), (3584, 3583), (3592, 1500), (4096, 4095)])
+def test_six_to_eight_rounds(cap, tail):
+    run(4, 4, cap, tail, 16, 32, CM, 0)

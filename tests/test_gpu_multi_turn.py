@@ -263,18 +263,20 @@ def test_empty_and_full_logical_sequences(env, oracle):
                         gp, None, None)
 
 
-@pytest.mark.parametrize("pages,k1,why", [(2550, 128, "pages in registers: one launch"), (2590, 49, "254 KiB of rows: one launch"),
-                                          (2590, 64, "332 KiB of rows: append, score, top-k and attention launches")])
+@pytest.mark.parametrize("pages,k1,why", [(2550, 128, "pages in registers, 5 x 4 loads: one launch"),
+                                          (2990, 128, "6 x 4 loads: one launch"),
+                                          (3590, 97, "8 x 4 loads of few units: append, score, top-k and attention launches"),
+                                          (4100, 39, "313 KiB of rows, scores in LDS: one launch"),
+                                          (4100, 40, "321 KiB: append, score, top-k and attention launches")])
 def test_routes_over_an_index(env, oracle, pages, k1, why):
     """A step that takes in a token and the one after it, on either side of the lines between one launch and several."""
     torch, rk, dev = env
-    B, S, T = 2, 3000, 200
+    B, S, T = 2, 4200, 200
     say("multi-turn routes", pages, k1, why)
     w = small("tiny", batch=B, context=S, page_size=1, channel_budget=k1, token_budget=T, n_heavy=8)
     d = wl.generate(w)
     cache, _ = to_device_cache(rk, torch, d, w.n_q_heads, 16, dev, pages_cap=S // 16 + 8, v_layout=TM)
     index = rk.alloc_index(cache, 1, pages + 4)
-    assert index.pages_cap > 2560 or "registers" in why
     rng = np.random.default_rng(pages + k1)
     idx = np.full((B, w.n_kv_heads, index.pages_cap), -1, dtype=np.int32)
     for b in range(B):
