@@ -254,7 +254,8 @@ int32_t rocketkv_append_kv(const rocketkv_cache_t* cache, const void* k_new, con
  *        `window` prompt positions.
  * src needs page_size 16; dst may have any page size when its V is token-major.
  * kept_idx: optional int32 [batch][n_kv_heads][keep_budget], -1 padded.
- * workspace: rocketkv_workspace_bytes(ROCKETKV_OP_SNAPKV, src, window, keep_budget).
+ * workspace: rocketkv_workspace_bytes(ROCKETKV_OP_SNAPKV, src, window, keep_budget), which never shrinks as
+ *            src->pages_cap grows: one sized for the longest cache serves every shorter one.
  */
 int32_t rocketkv_snapkv_compress(const void* q_obs, const rocketkv_cache_t* src, int32_t window,
                                  int32_t pool_kernel, int32_t keep_budget,

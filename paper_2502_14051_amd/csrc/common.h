@@ -346,7 +346,7 @@ hipError_t launch_append(const CacheView& c, const bf16_t* k_new, const bf16_t* 
                          bf16_t* kmin, hipStream_t st);
 
 struct SnapPlan {
-  size_t stats_off, votes_off, pooled_off, kept_off, runs_off, total_bytes;
+  size_t stats_off, stats_part_off, votes_off, pooled_off, kept_off, runs_off, counts_off, total_bytes;
   int sel_split;  // workgroups per unit in the select
   int n_chunks;  // key-axis chunks per (sequence, head group) in the two score passes
   int chunk_pages;

@@ -12,6 +12,7 @@
 // The two score passes are the one dense contraction of the method (G*W query rows against every
 // key): they run on the matrix cores with the (head, window-row) index as the MFMA column, so a lane
 // owns a fixed set of softmax rows and their statistics stay in registers.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -31,7 +32,7 @@ constexpr int kCountStride = 64;  // uint32 between the run counters of two unit
 struct SnapArgs {
   const bf16_t* qobs;
   int W, NC, CG, n_chunks, chunk_pages, keep, s_cap, pool_r;
-  float* stats_part;  // [units][n_chunks][NC][2]
+  float* stats_part;  // [units][n_chunks][NC][2], where pooled, kept and runs are written later
   float* stats;       // [units][NC][2]   (max in log2 domain, 1/sum)
   float* votes;       // [units][s_cap]
   float* pooled;      // [units][s_cap]
@@ -1046,7 +1047,7 @@ SnapPlan plan_snapkv(const CacheView& src, int window, int keep) {
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   size_t off = 0;
   p.stats_off = off;
-  off += up(units * p.n_chunks * NC * 2 * sizeof(float)) + up(units * NC * 2 * sizeof(float));
+  off += up(units * NC * 2 * sizeof(float));
   p.votes_off = off;
   off += up(units * s_cap * sizeof(float));
   p.pooled_off = off;
@@ -1058,7 +1059,18 @@ SnapPlan plan_snapkv(const CacheView& src, int window, int keep) {
   p.sel_split = (int)(units >= 256 ? 1 : 256 / units);
   if ((size_t)p.sel_split > slices) p.sel_split = (int)slices;
   p.runs_off = off;
-  off += up(units * s_cap * sizeof(uint2)) + up(units * (kCountStride + kSelBins) * sizeof(uint32_t));
+  off += up(units * s_cap * sizeof(uint2));
+  // The chunk statistics lie where the pool and the select write, launches after their last reader: 192 bytes a page
+  // and the kept indices, which up to 192 softmax rows fit at any chunk.  More rows take up to 256 bytes a page.  What is
+  // reserved then is what the rule above reaches for this capacity or any smaller one (256 workgroups of 8 or 16
+  // pages, 512 of 32 or 64), and not what this capacity's chunks take: a workspace sized for the longest prompt serves
+  // every shorter one.
+  p.stats_part_off = p.pooled_off;
+  const size_t most = std::max({std::min<size_t>(workgroups(8), 256), std::min<size_t>(workgroups(32), 512),
+                                (size_t)workgroups(kSnapMaxChunkPages)});
+  off = std::max(off, p.stats_part_off + up(most * NC * 2 * sizeof(float)));
+  p.counts_off = off;
+  off += up(units * (kCountStride + kSelBins) * sizeof(uint32_t));
   p.total_bytes = off;
   return p;
 }
@@ -1068,7 +1080,6 @@ hipError_t launch_snapkv(const bf16_t* q_obs, const CacheView& src, int window, 
                          int32_t* n_out, void* ws, const SnapPlan& plan, hipStream_t st) {
   const int units = src.batch * src.n_kv_heads;
   char* base = static_cast<char*>(ws);
-  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   SnapArgs a;
   a.qobs = q_obs;
   a.W = window;
@@ -1079,9 +1090,8 @@ hipError_t launch_snapkv(const bf16_t* q_obs, const CacheView& src, int window, 
   a.keep = keep;
   a.s_cap = src.pages_cap * kAttnPage;
   a.pool_r = (pool_kernel - 1) / 2;
-  a.stats_part = reinterpret_cast<float*>(base + plan.stats_off);
-  a.stats = reinterpret_cast<float*>(base + plan.stats_off +
-                                     up((size_t)units * plan.n_chunks * a.NC * 2 * sizeof(float)));
+  a.stats_part = reinterpret_cast<float*>(base + plan.stats_part_off);
+  a.stats = reinterpret_cast<float*>(base + plan.stats_off);
   a.votes = reinterpret_cast<float*>(base + plan.votes_off);
   a.pooled = reinterpret_cast<float*>(base + plan.pooled_off);
   a.kept = reinterpret_cast<int32_t*>(base + plan.kept_off);
@@ -1089,7 +1099,7 @@ hipError_t launch_snapkv(const bf16_t* q_obs, const CacheView& src, int window, 
   a.kept_stride = kept_stride;
   a.n_out = n_out;
   a.runs = reinterpret_cast<uint2*>(base + plan.runs_off);
-  a.n_runs = reinterpret_cast<uint32_t*>(base + plan.runs_off + up((size_t)units * a.s_cap * sizeof(uint2)));
+  a.n_runs = reinterpret_cast<uint32_t*>(base + plan.counts_off);
   a.hist = a.n_runs + (size_t)units * kCountStride;
   a.sel_split = plan.sel_split;
 

@@ -57,6 +57,27 @@ def test_workspace_query_needs_no_device(L):
     assert L.rocketkv_workspace_bytes(rk.OP_SNAPKV, C.byref(st), 32, 32) == 0
 
 
+@pytest.mark.parametrize("batch,hq,hkv", [(1, 8, 1), (1, 32, 8), (1, 64, 8), (4, 32, 8), (16, 16, 4), (40, 32, 8), (3, 5, 1)])
+@pytest.mark.parametrize("window,keep", [(16, 17), (32, 512), (32, 33), (16, 4096)])
+def test_snapkv_workspace_of_a_longer_cache_serves_a_shorter_one(L, batch, hq, hkv, window, keep):
+    """Sizes never shrink as the capacity grows, and stay within one set of chunk statistics (chunks of 32 pages or more,
+    twice as long while there are more than 512 of them) on top of the other buffers."""
+    nc, units = hq // hkv * window, batch * hkv
+    up = lambda x: (x + 255) // 256 * 256
+    last = 0
+    for cap in list(range(8, 4200, 8)) + [8192, 8200, 16384, 32768]:
+        st = fake_cache(batch=batch, n_q_heads=hq, n_kv_heads=hkv, pages_cap=cap)
+        n = L.rocketkv_workspace_bytes(rk.OP_SNAPKV, C.byref(st), window, keep)
+        assert n >= last, f"{cap} pages need {n} bytes, {last} do for fewer"
+        last = n
+        chunk = 32
+        while chunk < 128 and units * -(-cap // chunk) > 512:
+            chunk *= 2
+        room = (up(units * -(-cap // chunk) * nc * 8) + up(units * nc * 8) + 2 * up(units * cap * 64) + up(units * keep * 4) +
+                up(units * cap * 128) + up(units * (64 + 4096) * 4))
+        assert n <= room, f"{cap} pages"
+
+
 BAD_CACHES = [
     (dict(n_q_heads=30), rk.INVALID_ARG, "multiple"),
     (dict(head_dim=64), rk.UNSUPPORTED, "head_dim"),

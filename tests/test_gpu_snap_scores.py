@@ -29,8 +29,11 @@ def check(oracle, hq, hkv, W, lens, cap, keep):
     src.block_table[:, :held.shape[1]] = held
     dst = rk.alloc_cache(len(lens), hq, hkv, 128, 16, (keep + 15) // 16, dev, zero=True)
     kept = torch.full((len(lens), hkv, keep), -9, dtype=torch.int32, device=dev)
-    rk.snapkv_compress(wl.from_bits(d["qobs"], dev), src, W, 1, keep, dst, kept, rk.alloc_workspace(rk.OP_SNAPKV, src, W, keep))
+    size = rk.workspace_bytes(rk.OP_SNAPKV, src, W, keep)
+    ws = torch.full((size + 4096,), 0xCD, dtype=torch.uint8, device=dev)  # what lies behind the workspace stays as it is
+    rk.snapkv_compress(wl.from_bits(d["qobs"], dev), src, W, 1, keep, dst, kept, ws[:size])
     torch.cuda.synchronize()
+    assert (ws[size:] == 0xCD).all()
     got, ref = kept.cpu().numpy(), oracle.snapkv(d["qobs"], d["K"], d["seq_lens"], 1, keep, want_votes=True)
     for b, S in enumerate(lens):
         for g in range(hkv):
@@ -66,3 +69,10 @@ def test_merged_statistics(oracle, hq, cap):
     rows, 50 of 128), 18 of 64 rows dealt to four threads, as many statistics and workgroups as it merges at most (64 of 128
     rows), one chunk more, and one more with fewer rows."""
     check(oracle, hq, 4, 16, (33000, 2064, 18 * 2048 + 16 if cap == 2304 else 20 * 2048, 300), cap, 200)
+
+
+@pytest.mark.parametrize("hkv,lens,cap", [(2, (4096, 4000, 1500, 2100), 256), (1, (32768,), 2048)])
+def test_most_chunk_statistics(oracle, hkv, lens, cap):
+    """256 softmax rows in 256 workgroups of 8 pages, whose statistics take more room than the buffers they share; merged by the
+    second pass (eight units) and by a launch (one unit)."""
+    check(oracle, hkv * 8, hkv, 32, lens, cap, 100)
