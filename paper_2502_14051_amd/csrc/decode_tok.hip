@@ -12,6 +12,7 @@
 // index) are bumped once every workgroup of the sequence has read the old ones (see report_read).
 #include "attend_tok_core.h"
 #include "select_core.h"
+#include "tok_route.h"
 
 namespace rkv {
 
@@ -123,35 +124,20 @@ void hsa_decode_tok_kernel(CacheView c, CacheView lc, SelectArgs sa, AttendArgs 
   }
 }
 
-// Whether a decode step over token-major caches is this one launch, or selects in launches of its own.  Here every workgroup
-// of a unit reads all of its picked summary rows for itself; there they are divided between workgroups, for a launch
-// boundary and the hand-over of the scores.  What the rows cost here goes by the number of loads a thread has one after the
-// other: its rounds of pages, times the batches of 32 rows; and, with summaries that are in no cache, whether two launches
-// leave compute units idle.  us a layer in one launch / in two, 8 KV heads a sequence, as many layers as exceed the last-level
-// cache (of the few layers that do not, one launch is ahead to 12 loads for four sequences and to 16 for sixteen), by
-// rounds x batches:
-//   1 sequence    3x2 20.9 / 24.9, 3x3 22.6 / 25.0 (four layers)
-//   4 sequences   3x2 23.3 / 26.5 (four layers), 5x2 26.4 / 24.6, 4x3 25.5 / 25.2, 6x2 28.3 / 25.2
-//   8             5x2 28.0 / 26.9, 4x3 27.3 / 26.9, 4x4 29.8 / 28.3
-//   16            3x2 29.5 / 32.2, 3x3 31.8 / 34.1, 3x4 34.4 / 36.1, 4x2 32.4 / 33.7, 4x3 36.7 / 36.6, 5x2 34.6 / 34.9, 6x2 36.9 / 36.1
-//   32            3x3 43.7 / 50.9, 4x3 48.8 / 55.0, 5x3 52.2 / 64.7
-//   40 (four wavefronts)  6x2 58.0 / 73.0, 6x3 62.3 / 78.0, 8x3 69.8 / 83.7
-// so 9 for up to eight sequences of eight heads; up to sixteen, 10 and all of three rounds; 24 beyond.  With more pages than
-// the register selection holds the scores go through LDS and radix passes: two launches from 128 KiB of rows on, with four
-// wavefronts from 320 KiB on (40 sequences of 2424 pages at 40 channels 59.8 / 73.2, at 60 68.9 / 76.3, two layers).
-// Through an index the alternative is an append, two selection launches and the attention: 8x4 of one sequence 38.4 / 36.1,
-// of four 41.2 / 42.1, 6x4 of one 32.6 / 34.7; in LDS 4160 pages of four sequences at 32 channels (260 KiB) 32.1 / 36.8, of
-// one at 64 37.9 / 31.8.
 bool decode_tok_one_launch(const CacheView& lc, bool indexed, int k1, int row_len, const AttendPlan& plan) {
   if (lc.pages_cap > kSingleSelectPages || fused_decode_tok_lds_bytes(lc, row_len, plan) + 64 > kMaxLdsBytes) return false;
-  const int64_t rows = (int64_t)k1 * lc.pages_cap * (int64_t)sizeof(bf16_t);
-  if (rows < kSplitSummaryBytes) return true;
-  const int rounds = select_rounds(lc.pages_cap, plan.waves * kWave), units = lc.batch * lc.n_kv_heads;
-  if (rounds == 0) return (indexed || plan.waves == 4) && rows <= 320 * 1024;
-  const int loads = rounds * ((k1 + 31) / 32);
-  if (indexed) return loads <= 24 || units >= 32;
-  if (units > 128) return loads <= 24;
-  return loads <= (units <= 64 ? 9 : 10) || (units > 64 && rounds <= 3);
+  if ((int64_t)k1 * lc.pages_cap * (int64_t)sizeof(bf16_t) < kSplitSummaryBytes) return true;
+  TokRoute r;
+  r.units = lc.batch * lc.n_kv_heads;
+  r.pages_cap = lc.pages_cap;
+  r.k1 = k1;
+  r.rounds = select_rounds(lc.pages_cap, plan.waves * kWave);
+  r.waves = plan.waves;
+  r.n_split = plan.n_split;
+  r.chunk = plan.chunk;
+  r.entries = (int)((int64_t)row_len * lc.page_size / kAttnPage);  // as attend_plan_for counts them
+  r.indexed = indexed;
+  return tok_one_launch(r);
 }
 
 size_t fused_decode_tok_lds_bytes(const CacheView& lc, int row_len, const AttendPlan& plan) {

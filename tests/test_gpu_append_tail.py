@@ -123,13 +123,14 @@ def test_score_launch(cap, tail, ps, k1):
     run(4, 4, cap, tail, ps, k1, TM, 0)
 
 
-# either side of the lines between one launch and several: loads one after the other (rounds of pages x batches of 32
-# channels) 9 up to 64 (sequence, KV head) units, 10 or three rounds up to 128, 24 beyond; past the register selection 128 KiB
-# of picked rows, 320 with four wavefronts
+# either side of the lines between one launch and several (csrc/tok_route.h): rounds of pages x (batches of 32 channels + 1)
+# 12 up to 128 (sequence, KV head) units, 32 beyond; past the register selection 128 KiB of picked rows, 320 with more than
+# 256 units
 @pytest.mark.parametrize("batch,hkv,cap,k1", [(4, 4, 1536, 96), (4, 4, 1536, 97), (4, 4, 2560, 33), (17, 4, 1536, 128),
                                               (17, 4, 2560, 64), (17, 4, 2560, 65), (33, 4, 4096, 96), (33, 4, 4096, 97),
                                               (257, 1, 2048, 96), (257, 1, 2048, 97), (4, 4, 4104, 15), (4, 4, 4104, 16),
-                                              (257, 1, 2064, 79), (257, 1, 2064, 80)])
+                                              (257, 1, 2064, 79), (257, 1, 2064, 80),
+                                              (4, 4, 2048, 64), (4, 4, 2048, 65), (32, 4, 3072, 32), (32, 4, 3584, 32)])
 def test_one_launch_or_several(batch, hkv, cap, k1):
     run(batch, hkv, cap, cap - 1, 2, k1, TM, 0)
 

@@ -263,9 +263,10 @@ def test_empty_and_full_logical_sequences(env, oracle):
                         gp, None, None)
 
 
-@pytest.mark.parametrize("pages,k1,why", [(2550, 128, "pages in registers, 5 x 4 loads: one launch"),
-                                          (2990, 128, "6 x 4 loads: one launch"),
-                                          (3590, 97, "8 x 4 loads of few units: append, score, top-k and attention launches"),
+@pytest.mark.parametrize("pages,k1,why", [(2550, 128, "pages in registers, 5 x (4 + 1) steps: one launch"),
+                                          (2990, 96, "6 x (3 + 1) steps: one launch"),
+                                          (2990, 128, "6 x (4 + 1) steps: append, score, top-k and attention launches"),
+                                          (3590, 97, "8 x (4 + 1) steps: append, score, top-k and attention launches"),
                                           (4100, 39, "313 KiB of rows, scores in LDS: one launch"),
                                           (4100, 40, "321 KiB: append, score, top-k and attention launches")])
 def test_routes_over_an_index(env, oracle, pages, k1, why):
