@@ -107,13 +107,23 @@ def test_many_sequences(batch, hkv, layout):
     run(batch, hkv, 40, 39, 16, 32, layout, 0)
 
 
-# more pages than the register selection holds: scores through LDS, with eight-page runs for some of the threads, for all
-# of them, and more than one each
+# six to eight pages per thread, full and not, and the first cache whose scores go through LDS
 @pytest.mark.parametrize("batch,hkv,cap,tail", [(4, 4, 2568, 2567), (4, 4, 2568, 300), (4, 4, 4088, 4087), (4, 4, 4104, 4103),
                                                 (257, 1, 1288, 1287), (257, 1, 2056, 2055)])
 @pytest.mark.parametrize("k1", [32, 81])
 def test_more_pages(batch, hkv, cap, tail, k1):
     run(batch, hkv, cap, tail, 16, k1, CM, 0)
+
+
+# more pages than the register selection holds: scores through LDS.  Sequences with eight-page runs for some of the threads
+# (the threads then share the rows of a run), for all but one of them, for each of them, and more than one each
+@pytest.mark.parametrize("batch,hkv,cap,tail,k1,layout", [
+    (4, 4, 4104, 300, 32, CM), (4, 4, 4104, 300, 81, CM), (4, 4, 4104, 2567, 81, CM), (4, 4, 4104, 4087, 32, CM),
+    (4, 4, 4104, 4088, 81, CM), (4, 4, 4104, 4095, 32, CM), (1, 2, 8192, 8191, 32, CM), (1, 2, 8192, 20, 128, CM),
+    (257, 1, 2056, 300, 32, CM), (257, 1, 2056, 300, 81, CM), (257, 1, 2056, 2039, 81, CM), (257, 1, 2056, 2040, 32, CM),
+    (4, 4, 4104, 300, 15, TM), (257, 1, 2056, 300, 31, TM)])
+def test_scores_through_lds(batch, hkv, cap, tail, k1, layout):
+    run(batch, hkv, cap, tail, 16, k1, layout, 0)
 
 
 # large summaries, scored by several workgroups: the receiving page in the last slot, and at either side of a share's edge
