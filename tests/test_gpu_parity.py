@@ -328,17 +328,30 @@ DECODE_CASES = [
     ("tiny", dict(n_q_heads=2, n_kv_heads=1, context=32768 * 16 - 5, token_budget=4096, n_heavy=32), None, 1, False),
     # more (sequence, KV head) units than compute units: the four-wavefront launch geometry
     ("tiny", dict(batch=40, n_q_heads=32, n_kv_heads=8, context=1100, token_budget=512, n_heavy=4), None, 0, True),
-    # the page counts at which the selection changes its form, on either side of each step: one, two and five pages per
-    # thread in registers, then scores through LDS (512-thread workgroups: 512 / 1024 / 2560 pages) ...
+    # page counts at which the selection changes its form, on either side: a kernel for each number of pages per thread up
+    # to eight, then scores through LDS (512-thread workgroups: multiples of 512 up to 4096 pages) ...
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=512 * 16, token_budget=1024, n_heavy=16), None, 0, False),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=513 * 16 - 3, token_budget=1024, n_heavy=16), None, 1, True),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=1024 * 16, token_budget=1024, n_heavy=16), None, 0, False),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=1025 * 16 - 3, token_budget=1024, n_heavy=16), None, 1, True),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=2560 * 16, token_budget=1024, n_heavy=16), None, 0, True),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=2561 * 16 - 9, token_budget=1024, n_heavy=16), None, 2, False),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=1536 * 16, token_budget=1024, n_heavy=16), None, 0, False),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=1537 * 16 - 3, token_budget=1024, n_heavy=16), None, 1, True),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=2048 * 16, token_budget=1024, n_heavy=16), None, 0, True),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=2049 * 16 - 3, token_budget=1024, n_heavy=16), None, 2, False),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=3072 * 16, token_budget=1024, n_heavy=16), None, 0, False),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=3073 * 16 - 9, token_budget=1024, n_heavy=16), None, 1, False),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=3584 * 16, token_budget=1024, n_heavy=16), None, 1, True),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=3585 * 16 - 1, token_budget=1024, n_heavy=16), None, 0, False),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=4096 * 16, token_budget=1024, n_heavy=16), None, 0, True),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=4097 * 16 - 3, token_budget=1024, n_heavy=16), None, 1, False),
+    ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=4104 * 16, token_budget=1024, n_heavy=16), None, 0, True),
+    # (a long cache with a short sequence beside a long one: run groups through LDS)
+    ("tiny", dict(batch=2, n_q_heads=4, n_kv_heads=2, context=4500 * 16, token_budget=1024, n_heavy=16), (4500 * 16, 700 * 16 - 5), 1, True),
     ("tiny", dict(n_q_heads=4, n_kv_heads=2, context=8192 * 16, token_budget=2048, n_heavy=16), None, 0, False),
     # ... and the same steps for the 256-thread workgroups of launches with more than 256 units
-    # (256 / 512 / 1280 pages; `tile`: the host generator draws a third of the batch and the rest are copies,
+    # (multiples of 256 up to 2048 pages; `tile`: the host generator draws a third of the batch and the rest are copies,
     # which keeps it to seconds at 264 units)
     ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=256 * 16, token_budget=512, n_heavy=4), None, 0, False),
     ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=257 * 16 - 1, token_budget=512, n_heavy=4), None, 1, False),
@@ -346,6 +359,12 @@ DECODE_CASES = [
     ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=513 * 16 - 1, token_budget=512, n_heavy=4), None, 1, False),
     ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=1280 * 16, token_budget=512, n_heavy=4), None, 0, False),
     ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=1281 * 16 - 7, token_budget=512, n_heavy=4), None, 0, False),
+    ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=768 * 16, token_budget=512, n_heavy=4), None, 0, False),
+    ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=1025 * 16 - 1, token_budget=512, n_heavy=4), None, 1, False),
+    ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=1536 * 16, token_budget=512, n_heavy=4), None, 0, False),
+    ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=1793 * 16 - 3, token_budget=512, n_heavy=4), None, 1, False),
+    ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=2048 * 16, token_budget=512, n_heavy=4), None, 0, False),
+    ("tiny", dict(batch=33, tile=11, n_q_heads=8, n_kv_heads=8, context=2049 * 16 - 7, token_budget=512, n_heavy=4), None, 0, False),
 ]
 
 
@@ -575,8 +594,10 @@ def test_snapkv_then_decode_pipeline(env, oracle):
     ("tiny", dict(batch=2, context=700 * 16 + 40, token_budget=512, n_heavy=8), (700 * 16 - 10, 520 * 16 + 3), False),
     # five rounds: receiving pages in rounds 2 and 4
     ("tiny", dict(batch=2, context=2100 * 16 + 40, token_budget=512, n_heavy=8), (1500 * 16 - 10, 2100 * 16 - 3), True),
-    # scores through LDS (more than 2560 pages)
+    # six rounds
     ("tiny", dict(batch=2, context=3000 * 16 + 40, token_budget=512, n_heavy=8), (3000 * 16 - 10, 2600 * 16), False),
+    # scores through LDS (more than 4096 pages): more runs of eight pages than threads, and fewer
+    ("tiny", dict(batch=2, context=4200 * 16 + 40, token_budget=512, n_heavy=8), (4150 * 16 - 10, 2600 * 16), False),
     # more than 256 units: the four-wavefront kernel, which takes the receiving page's old bounds from the
     # page's own rows; every slot of a page and both sides of a page boundary, with and without a block table
     ("tiny", dict(batch=33, n_q_heads=8, n_kv_heads=8, context=420, token_budget=128, n_heavy=2),
