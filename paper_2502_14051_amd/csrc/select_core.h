@@ -829,11 +829,13 @@ __device__ __forceinline__ int select_pages_small(const CacheView& c, const Sele
 }
 
 // Step 2, second half, with the form chosen by the cache's capacity: ROUNDS of select_rounds().  The fused kernels have
-// it as a template parameter and are instantiated per form.  With all forms behind branches in one kernel the longest
-// one set the registers of them all, and adding the forms of three and four rounds cost the others 4 %.  us a layer,
-// branches over 1, 2, 5 rounds / a kernel per form over 1, 2, 3, 4, 5: one sequence of 4096 tokens (one round) 15.1 /
-// 14.7, of 16000 (two) 16.8 / 16.5, of 24000 (three) 19.2 / 18.0, of 32000 (four) 19.9 / 19.2, four of 24000 20.2 / 19.0,
-// 16 of 4122 22.9 / 22.9.
+// it as a template parameter and are instantiated per form.  us a layer, forms 1 to 6 behind branches in one kernel / a kernel
+// per form, the step with a token taken in: one sequence of 4096 tokens (one round) 14.2 / 13.4, of 16000 (two) 15.8 / 14.9, of
+// 24000 (three) 16.9 / 16.1, of 32700 (four) 18.0 / 17.1, of 40000 (five) 19.2 / 18.2, four of 24000 18.5 / 17.5, 8 of 4122 at a
+// budget of 256 13.7 / 13.0; without the token one of 24000 14.2 / 13.8.  That is where half of the output channels are a
+// workgroup's share; with all of them the two are the same within 1 % (8 of 4122 16.7 / 16.6, 16 22.0 / 22.1, with all eight
+// forms behind branches 64 of 4122 56.6 / 56.4, 40 of 8000 51.7 / 51.8, 13 unequal ones 20.9 / 20.7).  It is not the registers,
+// which are as many in both (171; 215 with forms 7 and 8 beside the others, at the same times).
 // Six to eight rounds against select_pages_any: one sequence of 42000 tokens 24.6 / 20.1, of 50000 25.4 / 21.0, of 64000
 // 27.5 / 22.2, 13 of 50000 35.0 / 30.8, 40 of 25000 (256 threads) 60.0 / 55.8.  A thread's counts leave a lane each for at
 // most eight rounds of eight wavefronts.
@@ -1176,7 +1178,10 @@ __device__ __forceinline__ void select_block(const CacheView& c, const SelectArg
   uint32_t qv[kMaxGroup];
   load_q_column(c, a, unit, qv);
   select_channels<NT>(c, a, unit, sh, true, qv);
-  // (the same for the whole launch)
+  // (the same for the whole launch)  One kernel for every capacity, in which the forms of three, four and six to eight rounds
+  // have not been built.  What they would give, us a launch of 256 threads a unit, so / with them: one sequence of 9000 tokens
+  // (three rounds) 7.8 / 6.9, of 16000 (four) 8.1 / 7.7, of 21000 (six) 13.1 / 9.1, of 32000 (eight) 14.9 / 10.7, sixteen of
+  // 32000 17.7 / 14.0, 64 of 16000 15.6 / 14.9, at 216 registers instead of 142.
   switch (select_rounds(c.pages_cap, NT)) {
     case 1: select_pages<NT, 1>(c, a, unit, n, sh, keys, nullptr, true, none); break;
     case 2: select_pages<NT, 2>(c, a, unit, n, sh, keys, nullptr, true, none); break;
