@@ -116,9 +116,13 @@ __device__ __forceinline__ float half_wave_sums(float (&x)[16], int lane) {
 // That launch takes 4-5 us whatever there is to merge; here up to 64 KiB come from L2 beside the queries.  us a call
 // with the summaries, by a launch / so: 1 x 2048 tokens 36.6 / 35.1, 1 x 8192 48.6 / 46.0, 1 x 16384 53.0 / 51.4, 1 x 32768
 // 70.8 / 69.4, 4 x 16000 89.3 / 86.5, 8 x 32000 unequal 179.8 / 177.5 (1024 workgroups), 16 x 32768 541.3 / 543.6 (2048).
-// The two meet between 64 and 128 KiB a unit, kMergeStats the lower end: with 80 KiB 1 x 20000 with 64 query heads 75.2 / 74.4,
-// 1 x 5000 with 8 on one KV head 42.5 / 41.4; 94 1 x 24000 77.7 / 77.2; 98 1 x 200000 239.3 / 238.0, 1 x 50000 with 16 on four 66.3 /
-// 65.8; 110 1 x 28000 80.8 / 81.6; 120 2 x 120000 364.0 / 372.3; 126 1 x 32000 88.3 / 89.3, 1 x 8000 on one 42.5 / 42.6.
+// The two meet between 64 and 128 KiB of statistics a unit, of which kMergeStats is the lower end.  By KiB a unit, a launch / so:
+//    80  1 x 20000 with 64 query heads 75.2 / 74.4, 1 x 5000 with 8 query heads and one KV head 42.5 / 41.4
+//    94  1 x 24000 with 64 77.7 / 77.2
+//    98  1 x 200000 with 32 239.3 / 238.0, 1 x 50000 with 16 and four KV heads 66.3 / 65.8
+//   110  1 x 28000 with 64 80.8 / 81.6
+//   118  2 x 120000 with 64 364.0 / 372.3
+//   126  1 x 32000 with 64 88.3 / 89.3, 1 x 8000 with 8 and one KV head 42.5 / 42.6
 // NB: blocks of 32 softmax rows every wavefront works through (blocks without any hold zero queries and are
 // discarded).  A wavefront takes 32 tokens, a pair of neighbouring pages, at a time, against one block after the
 // other: a 32 x 32 product leaves a lane one softmax row and sixteen of the tokens.
